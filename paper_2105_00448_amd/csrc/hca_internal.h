@@ -39,7 +39,10 @@ inline void hca_launch(F kernel, dim3 grid, dim3 block, unsigned shmem, hipStrea
 }
 
 constexpr int kBlock = 256;        // threads per workgroup (all kernels but the two below)
-constexpr int kF3Block = 512;      // level 0's fused smoothing passes (tiles tx x 512/tx)
+constexpr int kF3Block = 768;      // most threads of the multigrid's fused smoothing passes
+constexpr int kRzBlock = 512;      // precision 32: columns of an r.z partial
+constexpr int kF3Group = 8;        // planes per r.z partial of level 0's post-smoothing
+constexpr int kStripPad = 4;       // values that a strip load may reach past its array's ends
 constexpr int kFlatChunk = 1024;   // voxels per flat work item (4 per thread)
 constexpr int kMaxFlatBlocksPerRep = 2048;
 
@@ -94,7 +97,7 @@ struct RepDev {
   unsigned long long seed;
   int flat_b0, flat_nb;       // range in the flat block table
   int tile_b0, tile_nb;       // range in the stencil tile table
-  int ftile_b0, ftile_nb;     // systems: range in level 0's fused-smoothing tile table
+  int fpart_b0, fpart_nb;     // systems: range of the r.z partials of level 0's fused smoothing
   int ndose[3];
   int dose_off;               // into the dose arrays (3*HCA_MAX_DOSES per rep)
   int tx;                     // stencil tile width (tile = tx x (kBlock/tx) columns)
@@ -112,7 +115,8 @@ struct Tile {
   int rep;
   short x0, y0;
   short z0, z1;
-  int pad;
+  int part;                   // level 0's fused tiles: the first of the tile's r.z partials (precision 32: the
+                              // column sum of (x, y) = (0, 0) over the tile's planes)
 };
 
 // Per-replicate scalars of one conjugate-gradient solve.
@@ -174,13 +178,6 @@ inline int grid_tiles(int n, int max_blocks) {
   else if (g % 8 == 0)
     g += 1;
   return g;
-}
-
-// Grid of a launch over the n fused-smoothing tiles: one workgroup per tile,
-// a multiple of 8 runs of `chunk` tiles (see ftile_of).
-inline int grid_ftiles(int n, int chunk) {
-  const int r = 8 * chunk;
-  return (n + r - 1) / r * r;
 }
 
 // Grid of a launch over n work items, at most max_blocks workgroups.
@@ -250,7 +247,8 @@ template <typename T>
 struct SolverBufsT {
   T *r, *z, *p0, *p1, *q;        // z: Jacobi preconditioner only
   float* z32;                    // z of the multigrid preconditioner (FP32 result)
-  float* r32;                    // FP32 copy of r for the multigrid's fine level
+  float* r32;                    // scaled FP32 copy of r for the multigrid; null in precision 32 with the fused
+                                 // passes, which scale r (FP32 already) as they read it
   T* dinv;                    // 1/diag(A), written by the start kernel (Jacobi)
   int jacobi;                 // 1: Jacobi preconditioner inside the update kernel
   double* partial;            // per work item
@@ -270,6 +268,9 @@ enum ReduceKind { RED_START = 0, RED_APPLY = 1, RED_UPDATE = 2, RED_RZ = 3, RED_
 template <typename T>
 void launch_cg_reduce(hipStream_t s, const Work& w, const SolverBufsT<T>& sb, int kind, double rtol,
                       int maxit, unsigned field_mask = 7u, int nrep = 1);
+// r32 = r sc of the systems still iterating.
+template <typename T>
+void launch_cg_r32(hipStream_t s, const Work& w, const SolverBufsT<T>& sb);
 // One iteration is launch_cg_apply (with the iteration's parity: the
 // direction p alternates between p0 and p1) then launch_cg_update.  The apply
 // also makes the previous iteration's x += alpha p (x: the solved field), so
@@ -314,6 +315,7 @@ struct MgRep {
   int tile_b0, tile_nb;     // smoothing tiles (active levels)
   int rtile_b0, rtile_nb;   // tiles of the cells this level receives by restriction
   int tx;
+  int fe, frpw, fty;        // fused tiles: strips per row (halo strips included), rows per wavefront, output rows
   float a;                  // face coupling D/h^2 of the system's field
 };
 
@@ -323,9 +325,12 @@ struct MgLevel {
   int ntiles;
   const Tile* rtiles;       // restriction-target tiles, reps with 1 <= k <= kc
   int nrtiles;
-  const Tile* ftiles;       // level 0: tiles of the fused smoothing passes (deeper in z)
+  const Tile* ftiles;       // tiles of the fused smoothing passes, dealt to the XCDs (rep < 0: none)
   int nftiles;
-  int fchunk;               // level 0: fused tiles per XCD run (about eight rows of tiles)
+  const Tile* rztiles;      // level 0, precision 32: columns of each r.z partial
+  int nrztiles;
+  int fthreads;             // threads of a fused pass's workgroup
+  int uniform;              // every cell of every system is a full 2^k-cube
   float *c, *dinv, *r, *u, *ualt;
 };
 
@@ -355,13 +360,15 @@ struct MgBufs {
   int coarse_lds_bytes;
   float w_a, w_b;            // Jacobi weights: pre-sweeps (w_a, w_b), post-sweeps (w_b, w_a)
   float w0[3];              // level 0: pre-sweeps (w0[0], w0[1], w0[2]), post-sweeps reversed
-  int fused;                // fused smoothing passes (k_mg_prefused, k_mg_postfused): level 0, and
-                            // the coarser levels with ftiles
+  int fused;                // fused smoothing passes (k_mg_prefused, k_mg_postfused) on every level
+  double* colsum;           // precision 32: r.z of each column over a fused tile's planes
   float** lev_c;            // device arrays of the per-level pointers
   float** lev_r;
   float** lev_u;
 };
 
+// Allow the fused passes their dynamic LDS (above 64 KiB).
+hipError_t mg_set_fused_lds();
 // Allow the coarse-solve kernels `bytes` of dynamic LDS (above 64 KiB).
 hipError_t mg_set_coarse_lds(int bytes);
 template <typename T>

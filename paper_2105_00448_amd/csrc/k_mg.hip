@@ -27,6 +27,8 @@
 //            Jacobi(u3)
 //   post2    u5 = Jacobi(u4); at level 0 u5 is the CG's z, and the same kernel
 //            reduces r.z and finishes beta of the flexible CG.
+#include <type_traits>
+
 #include "dev_util.h"
 
 namespace hca {
@@ -675,375 +677,664 @@ __global__ void __launch_bounds__(kBlock) k_mg_post2(MgLevel Lk, float omega, co
   }
 }
 
-// ---- level 0: three stencil stages per pass (temporal blocking) ---------------
+// ---- fused smoothing passes (temporal blocking) --------------------------------
 //
-// Level 0's couplings are uniform (a), so a sweep needs only the sum of the
-// six neighbours.  Each kernel below runs three dependent stencil stages over
-// a tile in one pass.  A tile of tx x ty output columns (kF3Block of them)
-// over [z0, z1) is extended by three rings of columns in x and y
-// (EX = tx + 6, EY = ty + 6).  Stage 0 forms its values on every column from
-// global memory; stage s = 1, 2, 3 on the columns of rings < 4 - s (ring 0:
-// the tile's own columns), from stage s-1's values.  In the step for plane z
-// the stages work on the planes z+3, z+2, z+1 and z.
+// A pass makes S dependent Jacobi sweeps over a tile without leaving the
+// workgroup (S = 3 on level 0, 2 below):
+//   pre:  stage 0 u1 = w0 D^-1 r; stages 1 .. S-1 sweeps, the last written to
+//         the level's u; stage S the residual r - A u, summed over the 2 x 2 x 2
+//         children into the next level's r.
+//   post: stage 0 u + P e; stages 1 .. S sweeps; on level 0 the last one is the
+//         CG's z (FP32, scaled) and feeds its r.z partial.
 //
-// Each thread owns one tile column (lane layout of the other stencil
-// kernels) and at most one ring column: ring columns go to the threads in
-// order, ring 1 first, so that a wavefront's ring columns mostly share a ring
-// and the wavefront skips the stages its ring does not need (dealt round
-// robin over the wavefronts instead, every wavefront ran all three).  A column's values of the planes around the current ones (its
-// own z-neighbours, and r and D^-1 of the four planes in flight) stay in the
-// owner's registers; only the x/y neighbours go through LDS, one plane per
-// stage, double buffered: stage s in step z reads the plane stage s-1 wrote in
-// step z-1, so one barrier per step orders everything.  Values outside the
-// lattice are 0, which makes the neighbour sum the sum over the existing
-// faces.
-//   pre:  stage 0 u1 = w0 D^-1 r; stages 1, 2 sweeps (w1, w2), u3 written to
-//         level 0's u; stage 3 the residual r - A u3, summed over the 2 x 2 x 2
-//         children into level 1's r.
-//   post: stage 0 u3 + P e; stages 1, 2, 3 sweeps (w2, w1, w0); stage 3's
-//         plane is the CG's z (FP32, scaled) and feeds its r.z partial.
-// The intermediate iterates never leave the workgroup: the pre-smoothing
-// reads r and D^-1 once and writes u3 and r1 (12.5 B per voxel instead of
-// 40.5 B over three kernels), the post-smoothing reads u3, e, r, D^-1 and the
-// stored r once and writes z (16.5 B + one stored value, instead of 44.5 B +
-// one).  Ring columns are computed by every tile that needs them, with the
-// same arithmetic.  The fused tiles are dealt to the XCDs in runs of about
-// eight tile rows (ftile_of), so neighbouring tiles' halo reads meet in L2.
-constexpr int kF3Max = 848;   // extended plane: (32 + 6)(16 + 6) = (16 + 6)(32 + 6) = 836
+// Layout.  A thread owns a strip of four cells in x, so that a stage's
+// neighbours in x are its own registers and, at the strip's ends, the adjacent
+// lanes' (one DPP move each); only the two neighbour rows go through LDS, as
+// 16-byte reads.  A wavefront holds frpw rows of fe strips, a workgroup of
+// eight wavefronts 8 frpw rows: the tile's columns extended by one strip on
+// either side in x and by S rows in y.  Stage s is valid on the rings up to
+// S - s; the lanes beyond compute values that no valid cell reads, so no stage
+// is masked.  D^-1, r and u are 0 outside the lattice, which keeps every
+// stage's value there 0 and makes the neighbour sum the sum over the existing
+// faces.  The tile marches through z: in the step for plane z the stages work
+// on the planes z + S, ..., z.  A stage reads its neighbours' rows of the plane
+// that the stage before wrote one step earlier, so one barrier per step orders
+// everything; a cell's own values in z, and r and D^-1 of the S + 1 planes in
+// flight, stay in registers, in slots that are compile-time constants since
+// the march is unrolled by four planes (indexed by the plane number mod 4).
+// The next plane's operands are loaded one step ahead.
+//
+// What bounds it: on large lattices HBM (halo rows mostly meet in the L2: the
+// pre pass fetches 10.1 B per cell of its 8, the post pass 28 of 20.5), on
+// small ones the latency of a step (LDS read, S dependent stages, barrier) at
+// 12 wavefronts per CU.  Measured on one 384^3 lattice's three systems, all
+// iterating: pre 705 -> 643 us, post 1475 -> 1051 us per V-cycle against one
+// cell per thread with the ring columns dealt to a second slot, which was bound
+// by its vector and scalar instructions (2.3 and 2.2 per cell and plane; now
+// 0.8 and 0.4).  Workgroups of 384 threads, two per CU, took 705 and 1064 us
+// (more halo); at four wavefronts per SIMD (128 registers) the post pass spills.
+constexpr int kF3MaxStrips = 32;   // strips per row of the extended tile
+// Strips of a plane in LDS for `threads` threads: the tile's rows, a row above
+// and below, and slots that the lanes without a strip write to (with their
+// neighbours' slots).  The 2 S stage planes are interleaved by strip
+// (kF3Stride 16-byte values: 6, or 5 of which 4 are used, both free of bank
+// conflicts), so that their offsets are constants at any workgroup size.
+__host__ __device__ constexpr int f3_idle(int threads) { return threads + 2 * kF3MaxStrips; }
+__host__ __device__ constexpr int f3_strips(int threads) { return f3_idle(threads) + 64 + kF3MaxStrips; }
+template <int S>
+struct F3Lds {
+  static constexpr int kStride = S == 3 ? 6 : 5;
+  static constexpr int kPlane = 16 * kStride;
+};
+template <int S>
+int f3_lds_pre(int threads) { return f3_strips(threads) * (F3Lds<S>::kPlane + 16); }
+template <int S>
+int f3_lds_post(int threads) { return f3_strips(threads) * F3Lds<S>::kPlane + threads * 32; }
 
 // Weights of a fused pass's sweeps, in stage order.
 struct F3W {
   float w[3];
 };
 
-struct F3Own {
-  int EX;
-  int p[2];      // LDS index of the owned columns: tile column, ring column (-1: none)
-  int ring1;     // ring of the ring column (1..R; R + 1: none)
-  int col[2];    // column within a plane (-1: outside the lattice)
-};
+// Strip accesses are buffer instructions on the extended tile's part of a plane:
+// a lane without a strip has the offset kNoLane, whose loads the hardware's
+// range check turns into 0 and whose stores it drops, and a plane past the
+// lattice's last has a range of 0.  So every step issues the same memory
+// instructions with no branch around them, and the compiler's waits for a
+// load count exactly the instructions issued after it (with branches it
+// assumes the shortest path and waits for younger loads too, which undoes
+// the loads' lead of two planes).  A strip is read whole at any alignment;
+// cells past the lattice's end are zeroed by the reader.
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+constexpr unsigned kNoLane = 0x80000000u;
 
-// Ring column k (rings 1..R in turn; each ring top row, bottom row, left and
-// right column) of a tx x ty tile extended by R rings: LDS index and ring,
-// or ring R + 1 if none.
-__device__ inline void f3_ring_cell(int k, int tx, int ty, int R, int EX, int& p, int& ring) {
-  for (int rho = 1; rho <= R; ++rho) {
-    const int w = tx + 2 * rho, h = ty + 2 * rho - 2, n = 2 * w + 2 * h;
-    if (k < n) {
-      const int o = R - rho;   // the ring's first row and column in the extended tile
-      int hx, hy;
-      if (k < w) {
-        hx = o + k;
-        hy = o;
-      } else if (k < 2 * w) {
-        hx = o + k - w;
-        hy = o + h + 1;
-      } else if (k < 2 * w + h) {
-        hx = o;
-        hy = o + 1 + k - 2 * w;
-      } else {
-        hx = o + w - 1;
-        hy = o + 1 + k - 2 * w - h;
-      }
-      p = hy * EX + hx;
-      ring = rho;
-      return;
-    }
-    k -= n;
+__device__ inline __amdgpu_buffer_rsrc_t strip_buf(const void* p, bool in) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, in ? 0x7fffffff : 0, 0x00020000);
+}
+__device__ inline f4 strip_load(__amdgpu_buffer_rsrc_t b, unsigned off) {
+  return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, 0));
+}
+template <typename T>
+struct StripVal;   // four stored values of r
+template <>
+struct StripVal<float> {
+  f4 v;
+  __device__ inline void load(__amdgpu_buffer_rsrc_t b, unsigned off) { v = strip_load(b, off); }
+  __device__ inline float operator[](int i) const { return v[i]; }
+  __device__ inline void clear(int i) { v[i] = 0.f; }
+};
+template <>
+struct StripVal<double> {
+  d2 a, b;
+  __device__ inline void load(__amdgpu_buffer_rsrc_t buf, unsigned off) {
+    a = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)off, 0, 0));
+    b = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)(off + 16u), 0, 0));
   }
-  p = -1;
-  ring = R + 1;
+  __device__ inline double operator[](int i) const { return i < 2 ? a[i & 1] : b[i & 1]; }
+  __device__ inline void clear(int i) {
+    if (i < 2)
+      a[i & 1] = 0.0;
+    else
+      b[i & 1] = 0.0;
+  }
+};
+// Stores a strip (off: kNoLane on lanes that hold none); nv: its cells inside
+// the lattice, read only where a strip of the wavefront is ragged.
+__device__ inline void strip_store(__amdgpu_buffer_rsrc_t b, unsigned off, const float (&v)[4], int nv, bool ragged) {
+  if (!ragged) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, f4{v[0], v[1], v[2], v[3]}), b, (int)off, 0, 0);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[i]), b, (int)(i < nv ? off + 4u * i : kNoLane), 0, 0);
+  }
 }
 
-__device__ inline F3Own f3_own(const Tile& t, const MgRep& m, int R) {
+// The value of the lane below / above (0 at the wavefront's ends).
+__device__ inline float lane_below(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));   // wave_shr:1
+}
+__device__ inline float lane_above(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));   // wave_shl:1
+}
+
+// A thread's place in its extended tile.
+struct F3Own {
+  int p;          // LDS strip index (one pad row above the first)
+  unsigned vo;    // first cell, from the extended tile's first cell within a plane
+  int x, y;       // first cell
+  int nv;         // cells of the strip inside the lattice (0: none)
+  bool active;    // the lane holds a strip
+  bool inner;     // the strip belongs to the tile proper and to the lattice
+};
+
+__device__ inline F3Own f3_own(const Tile& t, const MgRep& m, int S) {
   F3Own f;
-  const int tx = m.tx, ty = kF3Block / tx;
-  f.EX = tx + 2 * R;
-  const int q = (int)threadIdx.x;
-  f.p[0] = (q / tx + R) * f.EX + q % tx + R;
-  f3_ring_cell(q, tx, ty, R, f.EX, f.p[1], f.ring1);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    f.col[j] = -1;
-    if (f.p[j] >= 0) {
-      const int x = t.x0 + f.p[j] % f.EX - R, y = t.y0 + f.p[j] / f.EX - R;
-      if (x >= 0 && x < m.nx && y >= 0 && y < m.ny) f.col[j] = x + m.nx * y;
-    }
-  }
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  const int rw = lane / m.fe, e = lane - rw * m.fe;
+  const int row = wave * m.frpw + rw;
+  f.active = rw < m.frpw && row < m.fty + 2 * S;
+  f.x = t.x0 + 4 * (e - 1);
+  f.y = t.y0 + row - S;
+  f.p = f.active ? (row + 1) * m.fe + e : f3_idle((int)blockDim.x) + lane;
+  f.vo = (unsigned)(4 * e + m.nx * row);
+  const bool in = f.active && f.x >= 0 && f.x < m.nx && f.y >= 0 && f.y < m.ny;
+  f.nv = in ? min(4, m.nx - f.x) : 0;
+  f.inner = in && e > 0 && e + 1 < m.fe && row >= S && row < S + m.fty;
   return f;
 }
 
-// Shift a plane history (index 0 the newest).  (Unrolling the steps so that
-// the history slots become compile-time indices removes these moves but holds
-// more registers, and measured slower; so did compile-time tile widths.)
-template <int N>
-__device__ inline void f3_push(float (&h)[N], float v) {
+// Face couplings of a strip.  UNI: every cell is a full 2^k-cube, so a face
+// couples with a 2^k (folded into `a`).  Otherwise the finite-volume coupling
+// a (area / centre distance) of the cells' extents (ragged last cells),
+// separable per axis; on full cubes the two agree bit for bit (every factor is
+// a power of two).
+template <bool UNI>
+struct F3Geo {
+  float a;
+  __device__ inline void init(const Geo<false>&, const F3Own&, float a_) { a = a_; }
+  __device__ inline void plane(const Geo<false>&, int) {}
+  __device__ inline float nb(int, float xm, float xp, float ym, float yp, float zm, float zp) const {
+    return ((xm + xp) + (ym + yp)) + (zm + zp);
+  }
+};
+template <>
+struct F3Geo<false> {
+  float a;
+  float ex[4], X[5], ey, Ym, Yp;   // extents; inverse centre distances (X[i]: between x - 1 + i and x + i)
+  float ez, Zm, Zp;
+  __device__ static inline float ext(int I, int n, int k, int n0) {
+    return (I >= 0 && I < n) ? (float)(min((I + 1) << k, n0) - (I << k)) : (float)(1 << k);
+  }
+  __device__ inline void init(const Geo<false>& G, const F3Own& f, float a_) {
+    a = a_;
+    float e[6];
 #pragma unroll
-  for (int k = N - 1; k > 0; --k) h[k] = h[k - 1];
-  h[0] = v;
+    for (int i = 0; i < 6; ++i) e[i] = ext(f.x - 1 + i, G.nx, G.k, G.n0x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ex[i] = e[i + 1];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) X[i] = 2.f / (e[i] + e[i + 1]);
+    ey = ext(f.y, G.ny, G.k, G.n0y);
+    Ym = 2.f / (ext(f.y - 1, G.ny, G.k, G.n0y) + ey);
+    Yp = 2.f / (ey + ext(f.y + 1, G.ny, G.k, G.n0y));
+  }
+  // factors of the plane z that a stage works on
+  __device__ inline void plane(const Geo<false>& G, int z) {
+    ez = ext(z, G.nz, G.k, G.n0z);
+    Zm = 2.f / (ext(z - 1, G.nz, G.k, G.n0z) + ez);
+    Zp = 2.f / (ez + ext(z + 1, G.nz, G.k, G.n0z));
+  }
+  __device__ inline float nb(int i, float xm, float xp, float ym, float yp, float zm, float zp) const {
+    const float sx = fmaf(X[i + 1], xp, X[i] * xm);
+    const float sy = fmaf(Yp, yp, Ym * ym);
+    const float sz = fmaf(Zp, zp, Zm * zm);
+    return fmaf(ex[i] * ey, sz, fmaf(ex[i] * ez, sy, (ey * ez) * sx));
+  }
+};
+
+// The marching of both passes over a tile [z0, z1): stage 0's planes in groups
+// of four, each plane's step specialised for the plane number mod 4.  From
+// the four planes below the tile (the lattice's first plane where there are
+// none: the planes below it are 0) to the S above it.  A stage's first planes
+// are computed from zeros instead of the planes that were left out; no plane
+// of the tile depends on them.
+template <int S, typename STEP>
+__device__ inline void f3_march(int z0, int z1, bool active, STEP step) {
+  const int zf = max(z0 - 4, 0) & ~3;
+  if (active) {
+    for (int z = zf; z < z1 + S; z += 4) {
+      step(z, std::integral_constant<int, 0>());
+      step(z + 1, std::integral_constant<int, 1>());
+      step(z + 2, std::integral_constant<int, 2>());
+      step(z + 3, std::integral_constant<int, 3>());
+    }
+  } else {
+    for (int z = zf; z < z1 + S; z += 4)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) __syncthreads();
+  }
 }
 
-// Sum of the x/y neighbours of LDS cell p in plane buffer b.
-__device__ inline float f3_xy(const float* b, int p, int EX) {
-  return (b[p - 1] + b[p + 1]) + (b[p - EX] + b[p + EX]);
+// Sum of the six neighbours' stage values of cell i: `u` the strip's own
+// values in the plane, rows from LDS, z neighbours below and above.
+#define F3_NB(i, u, lo, hi, ym, yp, zm, zp)                                                             \
+  geo.nb(i, (i) == 0 ? (lo) : (u)[(i) == 0 ? 0 : (i)-1], (i) == 3 ? (hi) : (u)[(i) == 3 ? 3 : (i) + 1], \
+         (ym)[i], (yp)[i], (zm)[i], (zp)[i])
+
+// One weighted-Jacobi sweep of a cell: u + w (D^-1 (r + a nb) - u).  P32
+// (precision 32): in the form (1 - w) u + (w D^-1) (r + a nb) and with the
+// roundings of one kernel per cell, which the stored fields' last bits follow.
+template <bool P32>
+__device__ inline float f3_sweep(float w, float d, float r, float a, float nb, float u) {
+  const float t = fmaf(a, nb, r);
+  return P32 ? fmaf(1.f - w, u, (w * d) * t) : fmaf(w, fmaf(d, t, -u), u);
 }
 
-// ring of slot j's column (slot 0: the tile column)
-#define F3_RING(j) ((j) == 0 ? 0 : f.ring1)
+// The first sweep from zero, w D^-1 r, rounded (not contracted into the sums
+// that take it).
+__device__ inline float f3_first(float w, float d, float r) {
+#pragma clang fp contract(off)
+  return w * d * r;
+}
 
-// Pre-smoothing and restriction of a uniform level (level 0, or a coarser
-// level whose cells are all full 2^k-cubes: coupling a 2^k) in one pass: S
-// stages (S = 3 at level 0, 2 below): u1 = w[0] D^-1 r, then sweeps w[1..S-1]
-// (the last one's tile cells written to u), then the residual r - A u summed
-// over the 2 x 2 x 2 children into the next level's r.
-template <int S>
-__global__ void __launch_bounds__(kF3Block) k_mg_prefused(MgLevel Lk, MgLevel Lc, F3W w, float ascale,
-                                                          const float* __restrict__ r, const SolveScal* ss) {
-  __shared__ float sV[S][2][kF3Max];
-  const int ti = ftile_of(Lk.nftiles, Lk.fchunk);
-  if (ti < 0) return;
-  const Tile t = Lk.ftiles[ti];
-  if (ss[t.rep].done) return;
+// Pre-smoothing and restriction of one level.  On level 0 in precision 32
+// (whose r is FP32 already) r is scaled by the system's power of two here;
+// otherwise it is the scaled FP32 copy or a coarser level's r.
+template <int S, bool UNI, bool P32>
+__global__ void __launch_bounds__(kF3Block, 3) k_mg_prefused(MgLevel Lk, MgLevel Lc, F3W w, float ascale,
+                                                             const float* __restrict__ r, const SolveScal* ss) {
+  extern __shared__ __attribute__((aligned(16))) float4 lds_f3[];
+  constexpr int kSt = F3Lds<S>::kStride;
+  float4* const sV = lds_f3;   // [strip][stage][parity]
+  const int nstrips = f3_strips((int)blockDim.x);
+  float2* const sQ = reinterpret_cast<float2*>(lds_f3 + nstrips * kSt);   // [strip][parity]: residual sums over x
+                                                                          // pairs of the odd rows
+  const Tile t = Lk.ftiles[blockIdx.x];
+  if (t.rep < 0 || ss[t.rep].done) return;
   const MgRep m = Lk.reps[t.rep];
   const MgRep mc = Lc.reps[t.rep];
   const F3Own f = f3_own(t, m, S);
-  const int EX = f.EX, nz = m.nz, tx = m.tx;
-  const float a = m.a * ascale;
-  const int plane = m.nx * m.ny;   // a system's level holds < 2^31 cells
-  const float* __restrict__ rS = r + m.off;
-  const float* __restrict__ dS = Lk.dinv + m.off;
-  float* __restrict__ uS = Lk.u + m.off;
+  const int fe = m.fe, nz = m.nz;
+  const Geo<false> G = geo_of<false>(m);
+  F3Geo<UNI> geo;
+  geo.init(G, f, UNI ? m.a * ascale : m.a);
+  const long long plane = (long long)m.nx * m.ny;
+  // the extended tile's first cell in the plane that is loaded next (uniform,
+  // and kept opaque to the compiler, which would otherwise carry one pointer
+  // per array and unrolled plane), and the strip's byte offsets from it
+  long long at = m.off + t.x0 - 4 + (long long)m.nx * (t.y0 - S) + plane * (max(t.z0 - 4, 0) & ~3);
+  const unsigned vo = f.nv > 0 ? 4u * f.vo : kNoLane;
+  const unsigned io = f.inner ? 4u * f.vo : kNoLane;
+  const int sce = P32 && S == 3 ? ilogb(ss[t.rep].sc) : 0;
   const int z0 = t.z0, z1 = t.z1;
-  float rh[2][S + 1], dh[2][S + 1];   // r, D^-1 of planes z+S .. z (newest first)
-  float hs[S][2][3];                  // stage outputs, newest first
+  for (int k = threadIdx.x; k < nstrips * (kSt + 1); k += blockDim.x) lds_f3[k] = float4{0.f, 0.f, 0.f, 0.f};
+  const bool wact = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) * m.frpw < m.fty + 2 * S);
+  const bool ragged = __ballot(f.nv > 0 && f.nv < 4) != 0;   // a strip of the wavefront straddles the lattice's end
+  const bool lead = f.inner && ((f.y & 1) == 0), odd = f.inner && ((f.y & 1) != 0);
+  float h[S][2][4];        // a stage's values at the two newest planes, by plane parity
+  float rh[4][4], dh[4][4];   // r, D^-1 by plane mod 4
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int i = 0; i < 4; ++i) {
 #pragma unroll
-    for (int k = 0; k <= S; ++k) rh[j][k] = dh[j][k] = 0.f;
+    for (int s = 0; s < S; ++s) h[s][0][i] = h[s][1][i] = 0.f;
 #pragma unroll
-    for (int st = 0; st < S; ++st)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) hs[st][j][k] = 0.f;
+    for (int k = 0; k < 4; ++k) rh[k][i] = dh[k][i] = 0.f;
   }
-  float nr[2], nd[2];   // stage-0 operands of the next plane
-  auto fetch = [&](int z) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      nr[j] = 0.f;
-      nd[j] = 0.f;
-      if (f.col[j] >= 0 && z >= 0 && z < nz) {
-        const int i = plane * z + f.col[j];
-        nr[j] = rS[i];
-        nd[j] = dS[i];
-      }
+  // operands of the next two planes, by plane parity
+  f4 nr[2], nd[2];
+  auto fetch = [&](int z, int q) {   // plane z, at `at`, into slot q
+    const bool in = z < nz;
+    nr[q] = strip_load(strip_buf(r + at, in), vo);
+    nd[q] = strip_load(strip_buf(Lk.dinv + at, in), vo);
+  };
+  float q0 = 0.f, q1 = 0.f, acc0 = 0.f, acc1 = 0.f;
+  // the residual sums of plane z, complete once the odd rows' are in LDS; the
+  // coarse cells' after their second plane
+  const unsigned c0 = lead ? 4u * (unsigned)(((f.x - t.x0) >> 1) + mc.nx * ((f.y - t.y0) >> 1)) : kNoLane;
+  const unsigned c1 = lead && f.x + 2 < m.nx ? c0 + 4u : kNoLane;
+  const long long cat = mc.off + (t.x0 >> 1) + (long long)mc.nx * (t.y0 >> 1);
+  auto take_pair = [&](int z, int q, bool last) {
+    const float2 o = sQ[2 * (f.p + fe) + q];
+    acc0 += q0 + o.x;
+    acc1 += q1 + o.y;
+    if (last) {
+      const auto b = strip_buf(Lc.r + (cat + (long long)mc.nx * mc.ny * (z >> 1)), true);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc0), b, (int)c0, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc1), b, (int)c1, 0, 0);
+      acc0 = acc1 = 0.f;
     }
   };
-  const int lx = (int)threadIdx.x % tx, ly = (int)threadIdx.x / tx;
-  const int x = t.x0 + lx, y = t.y0 + ly;
-  const bool lead = ((lx | ly) & 1) == 0 && f.col[0] >= 0;
-  float acc = 0.f;
-  fetch(z0 - S);
-  for (int zz = z0 - 2 * S; zz < z1; ++zz) {
-    const int wb = (zz + 2 * S) & 1, rb = wb ^ 1;   // write this step's planes, read the last step's
-    {   // stage 0 at plane zz + S
-      const int z = zz + S;
+  {
+    const int zf = max(z0 - 4, 0) & ~3;
+    fetch(zf, 0);
+    at += plane;
+    fetch(zf + 1, 1);
+  }
+  __syncthreads();
+  auto step = [&](int z, auto K) {   // z: stage 0's plane
+    constexpr int k = decltype(K)::value, wb = k & 1, rb = wb ^ 1;
+    {
+      float nv[4];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if (F3_RING(j) > S) continue;
-        f3_push(rh[j], nr[j]);
-        f3_push(dh[j], nd[j]);
-        const float v = w.w[0] * nd[j] * nr[j];
-        f3_push(hs[0][j], v);
-        sV[0][wb][f.p[j]] = v;
+      for (int i = 0; i < 4; ++i) {
+        rh[k][i] = P32 && S == 3 ? ldexpf(nr[wb][i], sce) : nr[wb][i];
+        dh[k][i] = nd[wb][i];
       }
-      if (z + 1 <= z1 + S - 1) fetch(z + 1);
-    }
+      if (ragged) {
 #pragma unroll
-    for (int st = 1; st < S; ++st) {   // sweep st at plane zz + S - st (rings 0 .. S - st)
-      const int z = zz + S - st;
-      if (z >= z0 - (S - st) && z <= z1 - 1 + (S - st)) {
-        const bool in = z >= 0 && z < nz;
+        for (int i = 1; i < 4; ++i)
+          if (i >= f.nv) rh[k][i] = dh[k][i] = 0.f;
+      }
+      at += plane;
+      asm volatile("" : "+s"(at));
+      fetch(z + 2, wb);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          if (F3_RING(j) > S - st) continue;
-          const float nb = f3_xy(sV[st - 1][rb], f.p[j], EX) + (hs[st - 1][j][2] + hs[st - 1][j][0]);
-          float v = (1.f - w.w[st]) * hs[st - 1][j][1] + w.w[st] * dh[j][st] * (rh[j][st] + a * nb);
-          const bool ok = in && f.col[j] >= 0;
-          v = ok ? v : 0.f;
-          if (st == S - 1 && j == 0 && ok && z >= z0 && z < z1) uS[plane * z + f.col[0]] = v;
-          f3_push(hs[st][j], v);
-          sV[st][wb][f.p[j]] = v;
+      for (int i = 0; i < 4; ++i) nv[i] = f3_first(w.w[0], dh[k][i], rh[k][i]);
+#pragma unroll
+      for (int s = 1; s <= S; ++s) {   // stage s at plane z - s, from stage s - 1
+        constexpr int kk[4] = {k, (k + 3) & 3, (k + 2) & 3, (k + 1) & 3};
+        const int zs = z - s;
+        float out[4];
+        {
+          const float4 ym4 = sV[(f.p - fe) * kSt + 2 * (s - 1) + rb], yp4 = sV[(f.p + fe) * kSt + 2 * (s - 1) + rb];
+          const float ym[4] = {ym4.x, ym4.y, ym4.z, ym4.w}, yp[4] = {yp4.x, yp4.y, yp4.z, yp4.w};
+          const float* u = h[s - 1][rb];
+          const float lo = lane_below(u[3]), hi = lane_above(u[0]);
+          geo.plane(G, zs);
+          if (s < S) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              out[i] = f3_sweep<P32>(w.w[s], dh[kk[s]][i], rh[kk[s]][i], geo.a,
+                                     F3_NB(i, u, lo, hi, ym, yp, h[s - 1][wb], nv), u[i]);
+            if (s == S - 1)
+              strip_store(strip_buf(Lk.u + (at - (s + 2) * plane), zs >= z0 && zs < z1), io, out, f.nv, ragged);
+          } else if (zs >= z0 && zs < z1) {   // residual, summed over x pairs
+            if (zs > z0) take_pair(zs - 1, rb, ((k - S) & 1) == 0);   // zs - 1 odd
+            float res[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float c = fmaf(-u[i], __builtin_amdgcn_rcpf(dh[kk[s]][i]), rh[kk[s]][i]);
+              res[i] = fmaf(geo.a, F3_NB(i, u, lo, hi, ym, yp, h[s - 1][wb], nv), c);
+            }
+            if (ragged) {
+#pragma unroll
+              for (int i = 1; i < 4; ++i)
+                if (i >= f.nv) res[i] = 0.f;
+            }
+            q0 = res[0] + res[1];
+            q1 = res[2] + res[3];
+            if (odd) sQ[2 * f.p + wb] = float2{q0, q1};
+          }
         }
-      }
-    }
-    if (zz >= z0) {   // stage S at plane zz: r - A u, summed into the next level's r
-      const int z = zz;
-      float res = 0.f;
-      if (f.col[0] >= 0) {
-        const float nb = f3_xy(sV[S - 1][rb], f.p[0], EX) + (hs[S - 1][0][2] + hs[S - 1][0][0]);
-        res = rh[0][S] - hs[S - 1][0][1] * __builtin_amdgcn_rcpf(dh[0][S]) + a * nb;
-      }
-      float q = res + __shfl_xor(res, 1, 64);
-      q = q + __shfl_xor(q, tx, 64);
-      acc += q;
-      if ((z & 1) || z + 1 == nz) {
-        if (lead)
-          Lc.r[mc.off + (x >> 1) + (long long)mc.nx * ((y >> 1) + (long long)mc.ny * (z >> 1))] = acc;
-        acc = 0.f;
+        // stage s - 1's new plane: registers and LDS
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[s - 1][wb][i] = nv[i];
+        sV[f.p * kSt + 2 * (s - 1) + wb] = float4{nv[0], nv[1], nv[2], nv[3]};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nv[i] = out[i];
       }
     }
     __syncthreads();
-  }
+  };
+  f3_march<S>(z0, z1, wact, step);
+  if (wact) take_pair(z1 - 1, (z1 + S - 1) & 1, true);
 }
 
-// Prolongation and post-smoothing of a uniform level in one pass: stage 0
-// u + P e (e the next level's correction), then S sweeps w[0..S-1].  ZOUT
-// (level 0): the last sweep is the CG's z (FP32, scaled) and feeds the tile's
-// r.z partial; otherwise it is written to out.
-template <int S, bool ZOUT, typename RT, typename ST>
-__global__ void __launch_bounds__(kF3Block) k_mg_postfused(MgLevel Lk, MgLevel Lc, const float* __restrict__ e,
-                                                           F3W w, float ascale, const float* __restrict__ r,
-                                                           const RT* __restrict__ r64, float* __restrict__ out,
-                                                           SolverBufsT<ST> sb) {
-  __shared__ double lds8[kF3Block / 64];
-  __shared__ float sV[S][2][kF3Max];
-  __shared__ float sE[4][kF3Max];   // coarse plane Z interpolated in x, y (slot Z & 3); owner-private
-  const int ti = ftile_of(Lk.nftiles, Lk.fchunk);
-  if (ti < 0) return;
-  const Tile t = Lk.ftiles[ti];
-  if (sb.ss[t.rep].done) return;
+// Prolongation and post-smoothing of one level; e the next level's
+// correction.  The prolongation is the cell-centred linear interpolation of
+// lin_axis: where an axis takes its own aggregate alone, the other
+// aggregate's value is replaced by it.
+template <int S, bool UNI, bool ZOUT, bool P32, typename ST>
+__global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLevel Lc, const float* __restrict__ e,
+                                                              F3W w, float ascale, const float* __restrict__ r,
+                                                              float* __restrict__ out, SolverBufsT<ST> sb,
+                                                              double* __restrict__ colsum) {
+  __shared__ double sRz[kF3Block / 64];
+  extern __shared__ __attribute__((aligned(16))) float4 lds_f3[];
+  constexpr int kSt = F3Lds<S>::kStride;
+  float4* const sV = lds_f3;   // [strip][stage][parity]
+  const int nstrips = f3_strips((int)blockDim.x);
+  float4* const sE = lds_f3 + nstrips * kSt + 2 * threadIdx.x;   // the strip's correction on its two coarse planes
+                                                                  // (by plane parity; its owner's alone)
+  const Tile t = Lk.ftiles[blockIdx.x];
+  if (t.rep < 0 || sb.ss[t.rep].done) return;
   const MgRep m = Lk.reps[t.rep];
   const MgRep mc = Lc.reps[t.rep];
   const F3Own f = f3_own(t, m, S);
-  const int EX = f.EX, nz = m.nz;
-  const float a = m.a * ascale;
-  const int plane = m.nx * m.ny;
-  const float* __restrict__ rS = r + m.off;
-  const float* __restrict__ dS = Lk.dinv + m.off;
-  const float* __restrict__ uS = Lk.u + m.off;
+  const int fe = m.fe, nz = m.nz;
+  const Geo<false> G = geo_of<false>(m);
+  F3Geo<UNI> geo;
+  geo.init(G, f, UNI ? m.a * ascale : m.a);
+  const long long plane = (long long)m.nx * m.ny;
+  // the extended tile's first cell in the plane that is loaded next (uniform,
+  // and kept opaque to the compiler, which would otherwise carry one pointer
+  // per array and unrolled plane), and the strip's byte offsets from it
+  long long at = m.off + t.x0 - 4 + (long long)m.nx * (t.y0 - S) + plane * (max(t.z0 - 4, 0) & ~3);
+  const unsigned vo = f.nv > 0 ? 4u * f.vo : kNoLane;
+  const unsigned io = f.inner ? 4u * f.vo : kNoLane;
+  const int sce = P32 && S == 3 ? ilogb(sb.ss[t.rep].sc) : 0;
   const int z0 = t.z0, z1 = t.z1;
-  const double isc = ZOUT ? sb.ss[t.rep].isc : 1.0;
-  const float* __restrict__ eb = e + mc.off;
-  const int csz = mc.nx * mc.ny;
-  // E of coarse plane Z at the owned columns
-  auto make_e = [&](int Z) {
-    const float* b = eb + csz * Z;
+  for (int k = threadIdx.x; k < nstrips * kSt; k += blockDim.x) lds_f3[k] = float4{0.f, 0.f, 0.f, 0.f};
+  if (ZOUT && threadIdx.x < kF3Block / 64) sRz[threadIdx.x] = 0.0;
+  const bool wact = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) * m.frpw < m.fty + 2 * S);
+  const bool ragged = __ballot(f.nv > 0 && f.nv < 4) != 0;
+  // the strip's coarse cells: x / 2 - 1 .. x / 2 + 2 of the rows Iy and Jy
+  const int I0 = f.x >> 1;
+  bool own[4], owny = true;   // the cell takes its own aggregate alone in x, in y
+  // byte offsets of the rows from the first aggregate of the extended tile
+  // in a coarse plane, which is at `eat` in the plane to load next
+  const int X0 = t.x0 / 2 - 3, Y0 = max(0, (t.y0 - S) / 2 - 1);
+  unsigned e0 = kNoLane, e1 = kNoLane;
+  long long eat = mc.off + X0 + (long long)mc.nx * Y0;
+  {
+    int I, J;
+    float wj;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (f.col[j] < 0) continue;
-      int Ix, Jx, Iy, Jy;
-      float wx, wy;
-      lin_axis(t.x0 + f.p[j] % EX - S, m.nx, mc.nx, Ix, Jx, wx);
-      lin_axis(t.y0 + f.p[j] / EX - S, m.ny, mc.ny, Iy, Jy, wy);
-      const float g0 = b[Iy * mc.nx + Ix], g1 = b[Iy * mc.nx + Jx];
-      const float g2 = b[Jy * mc.nx + Ix], g3 = b[Jy * mc.nx + Jx];
-      const float e0 = (1.f - wx) * g0 + wx * g1;
-      const float e1 = (1.f - wx) * g2 + wx * g3;
-      sE[Z & 3][f.p[j]] = (1.f - wy) * e0 + wy * e1;
+    for (int i = 0; i < 4; ++i) {
+      lin_axis(f.x + i, m.nx, mc.nx, I, J, wj);
+      own[i] = J == I;
     }
-  };
-  int ehi = -(1 << 20);   // highest coarse plane in sE
-  float rh[2][S + 1], dh[2][S + 1];
-  float hs[S][2][3];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-#pragma unroll
-    for (int k = 0; k <= S; ++k) rh[j][k] = dh[j][k] = 0.f;
-#pragma unroll
-    for (int st = 0; st < S; ++st)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) hs[st][j][k] = 0.f;
+    if (f.nv > 0) {
+      lin_axis(f.y, m.ny, mc.ny, I, J, wj);
+      owny = J == I;
+      e0 = 4u * (unsigned)(mc.nx * (I - Y0) + I0 - 1 - X0);
+      e1 = 4u * (unsigned)(mc.nx * (J - Y0) + I0 - 1 - X0);
+    }
   }
-  float nu[2], nr[2], nd[2];
-  auto fetch = [&](int z) {
+  const long long cplane = (long long)mc.nx * mc.ny;
+  const int ncz = mc.nz;
+  f4 g0, g1;   // coarse values in flight (one coarse plane)
+  auto fetch_e = [&](int Z) {   // at `eat` (planes past the last are never taken)
+    const auto b = strip_buf(e + eat, Z < ncz);
+    g0 = strip_load(b, e0);
+    g1 = strip_load(b, e1);
+  };
+  auto make_e = [&](int q) {   // the correction interpolated in x and y
+
+    auto line = [&](const f4& g, float (&v)[4]) {
+      v[0] = own[0] ? g[1] : fmaf(0.75f, g[1], 0.25f * g[0]);
+      v[1] = own[1] ? g[1] : fmaf(0.75f, g[1], 0.25f * g[2]);
+      v[2] = own[2] ? g[2] : fmaf(0.75f, g[2], 0.25f * g[1]);
+      v[3] = own[3] ? g[2] : fmaf(0.75f, g[2], 0.25f * g[3]);
+    };
+    float a[4], b[4];
+    line(g0, a);
+    line(g1, b);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      nu[j] = 0.f;
-      nr[j] = 0.f;
-      nd[j] = 0.f;
-      if (f.col[j] >= 0 && z >= 0 && z < nz) {
-        const int i = plane * z + f.col[j];
-        nu[j] = uS[i];
-        nr[j] = rS[i];
-        nd[j] = dS[i];
-      }
-    }
+    for (int i = 0; i < 4; ++i) a[i] = owny ? a[i] : fmaf(0.75f, a[i], 0.25f * b[i]);
+    const float4 o{a[0], a[1], a[2], a[3]};
+    sE[q] = o;
   };
-  RT r64n = (RT)0;   // the stored r of the tile column, next output plane
-  auto fetch64 = [&](int z) {
-    if (ZOUT && f.col[0] >= 0 && z >= z0 && z < z1) r64n = r64[m.off + plane * z + f.col[0]];
+  float h[S][2][4];
+  f4 rh[4], dh[4];   // by plane mod 4; a plane's are loaded when the plane four below is done with
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) h[s][0][i] = h[s][1][i] = 0.f;
+  }
+  // u of the next two planes, by plane parity; the stored r of the tile's own
+  // cells for r.z, one plane ahead
+  f4 nu[2];
+  StripVal<ST> rq;
+  auto fetch_u = [&](int z, int q) { nu[q] = strip_load(strip_buf(Lk.u + at, z < nz), vo); };   // plane z is at `at`
+  auto fetch_rd = [&](int z, int q) {   // plane z is one below `at`
+    rh[q] = strip_load(strip_buf(r + (at - plane), z < nz), vo);
+    dh[q] = strip_load(strip_buf(Lk.dinv + (at - plane), z < nz), vo);
   };
+#pragma unroll
+  for (int k = 0; k < 4; ++k) rh[k] = dh[k] = 0.f;
+  const unsigned ir = f.inner ? (unsigned)sizeof(ST) * f.vo : kNoLane;
+  if constexpr (ZOUT) rq.load(strip_buf(sb.r + at, false), ir);
   double rz = 0.0;
-  fetch(z0 - S);
-  for (int zz = z0 - 2 * S; zz < z1; ++zz) {
-    const int wb = (zz + 2 * S) & 1, rb = wb ^ 1;
-    const RT r64c = r64n;
-    fetch64(zz + 1);
-    {   // stage 0 at plane zz + S: u + P e
-      const int z = zz + S;
-      int Iz = 0, Jz = 0;
-      float wz = 0.f;
-      const bool in = z >= 0 && z < nz;
-      if (in) {
-        lin_axis(z, nz, mc.nz, Iz, Jz, wz);
-        if (ehi < min(Iz, Jz) - 1) ehi = min(Iz, Jz) - 1;
-        while (ehi < max(Iz, Jz)) make_e(++ehi);
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if (F3_RING(j) > S) continue;
-        f3_push(rh[j], nr[j]);
-        f3_push(dh[j], nd[j]);
-        // branch-free: with Jz == Iz, wz is 0 and the sum is eI exactly
-        const float eI = sE[Iz & 3][f.p[j]], eJ = sE[Jz & 3][f.p[j]];
-        float v = nu[j] + ((1.f - wz) * eI + wz * eJ);
-        v = (in && f.col[j] >= 0) ? v : 0.f;
-        f3_push(hs[0][j], v);
-        sV[0][wb][f.p[j]] = v;
-      }
-      if (z + 1 <= z1 + S - 1) fetch(z + 1);
-    }
-#pragma unroll
-    for (int st = 1; st < S; ++st) {   // sweep st at plane zz + S - st (rings 0 .. S - st)
-      const int z = zz + S - st;
-      if (z >= z0 - (S - st) && z <= z1 - 1 + (S - st)) {
-        const bool in = z >= 0 && z < nz;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          if (F3_RING(j) > S - st) continue;
-          const float nb = f3_xy(sV[st - 1][rb], f.p[j], EX) + (hs[st - 1][j][2] + hs[st - 1][j][0]);
-          float v = (1.f - w.w[st - 1]) * hs[st - 1][j][1] + w.w[st - 1] * dh[j][st] * (rh[j][st] + a * nb);
-          v = (in && f.col[j] >= 0) ? v : 0.f;
-          f3_push(hs[st][j], v);
-          sV[st][wb][f.p[j]] = v;
-        }
-      }
-    }
-    if (zz >= z0 && f.col[0] >= 0) {   // the last sweep at plane zz
-      const float nb = f3_xy(sV[S - 1][rb], f.p[0], EX) + (hs[S - 1][0][2] + hs[S - 1][0][0]);
-      const float v = (1.f - w.w[S - 1]) * hs[S - 1][0][1] + w.w[S - 1] * dh[0][S] * (rh[0][S] + a * nb);
-      if constexpr (ZOUT) {
-        sb.z32[m.off + plane * zz + f.col[0]] = v;
-        rz += (double)r64c * ((double)v * isc);
-      } else {
-        out[m.off + plane * zz + f.col[0]] = v;
-      }
-    }
-    __syncthreads();
+  double rzc[4] = {0.0, 0.0, 0.0, 0.0};   // precision 32: per column
+  const int zf = max(z0 - 4, 0) & ~3;
+  const bool zrag = (nz & 1) != 0;
+  // E of zf's own coarse plane and of the one below
+  if (zf > 0) {
+    eat += cplane * ((zf >> 1) - 1);
+    fetch_e((zf >> 1) - 1);
+    make_e(1);
+    eat += cplane;
+  } else {
+    sE[1] = float4{0.f, 0.f, 0.f, 0.f};
   }
-  if constexpr (ZOUT) {   // the tile's r.z partial (fixed order)
-    for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
-    if ((threadIdx.x & 63) == 0) lds8[threadIdx.x >> 6] = rz;
-    __syncthreads();
+  fetch_e(zf >> 1);
+  make_e(0);
+  eat += cplane;
+  fetch_e((zf >> 1) + 1);   // for the first odd plane's step
+  fetch_u(zf, 0);
+  at += plane;
+  fetch_rd(zf, 0);
+  fetch_u(zf + 1, 1);
+  __syncthreads();
+  // r.z of the group of planes that ends with z: one partial per kF3Group
+  // planes of a tile column, whatever the tile's depth, so that the sum does
+  // not depend on how the batch's lattices are cut in z
+  auto put_rz = [&](int z) {
     if (threadIdx.x == 0) {
       double tsum = 0.0;
-      for (int k = 0; k < kF3Block / 64; ++k) tsum += lds8[k];
-      store_partials(sb.partial + (size_t)ti * 3, tsum, 0.0, 0.0);
+      for (int k = 0; k < kF3Block / 64; ++k) tsum += sRz[k];
+      store_partials(sb.partial + (size_t)(t.part + (z - z0) / kF3Group) * 3, tsum * sb.ss[t.rep].isc, 0.0, 0.0);
     }
+  };
+  auto step = [&](int z, auto K) {
+    constexpr int k = decltype(K)::value, wb = k & 1, rb = wb ^ 1;
+    {
+      constexpr int eI = k >> 1, eJ = eI ^ 1;   // E of plane z / 2 and of the other one z takes
+      const int Z = z >> 1;
+      if (k & 1) {   // plane Z + 1, loaded two steps before
+        make_e(eJ);
+        eat += cplane;
+        asm volatile("" : "+s"(eat));
+        fetch_e(Z + 2);
+      }
+      float nv[4];
+      {
+        const int J = (k & 1) ? Z + 1 : Z - 1;
+        const bool alone = J < 0 || J >= ncz || (zrag && (Z == ncz - 1 || J == ncz - 1));
+        // weights of E (0 past the last plane; lanes without a strip have E = 0)
+        const float wJ = z >= nz || alone ? 0.f : 0.25f, wI = z >= nz ? 0.f : 1.f - wJ;
+        const float4 eI4 = sE[eI], eJ4 = sE[eJ];
+        const float E[2][4] = {{eI4.x, eI4.y, eI4.z, eI4.w}, {eJ4.x, eJ4.y, eJ4.z, eJ4.w}};
+        constexpr int k1 = (k + 3) & 3;   // the plane below, whose r and D^-1 stage 1 takes now
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (P32 && S == 3) rh[k1][i] = ldexpf(rh[k1][i], sce);
+          nv[i] = nu[wb][i] + fmaf(wI, E[0][i], wJ * E[1][i]);
+        }
+        if (ragged) {
+#pragma unroll
+          for (int i = 1; i < 4; ++i)
+            if (i >= f.nv) rh[k1][i] = dh[k1][i] = nv[i] = 0.f;
+        }
+      }
+      at += plane;
+      asm volatile("" : "+s"(at));
+      fetch_u(z + 2, wb);
+#pragma unroll
+      for (int s = 1; s <= S; ++s) {
+        constexpr int kk[4] = {k, (k + 3) & 3, (k + 2) & 3, (k + 1) & 3};
+        const int zs = z - s;
+        float v[4];
+        {
+          const float4 ym4 = sV[(f.p - fe) * kSt + 2 * (s - 1) + rb], yp4 = sV[(f.p + fe) * kSt + 2 * (s - 1) + rb];
+          const float ym[4] = {ym4.x, ym4.y, ym4.z, ym4.w}, yp[4] = {yp4.x, yp4.y, yp4.z, yp4.w};
+          const float* u = h[s - 1][rb];
+          const float lo = lane_below(u[3]), hi = lane_above(u[0]);
+          geo.plane(G, zs);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            v[i] = f3_sweep<P32>(w.w[s - 1], dh[kk[s]][i], rh[kk[s]][i], geo.a,
+                                 F3_NB(i, u, lo, hi, ym, yp, h[s - 1][wb], nv), u[i]);
+          if (s == S) {
+            const bool mine = zs >= z0 && zs < z1;
+            strip_store(strip_buf((ZOUT ? sb.z32 : out) + (at - (S + 2) * plane), mine), io, v, f.nv, ragged);
+            if constexpr (ZOUT) {
+              // (lanes and planes that are not the tile's have r = 0 here)
+              if (ragged) {
+#pragma unroll
+                for (int i = 1; i < 4; ++i)
+                  if (i >= f.nv) rq.clear(i);
+              }
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                if (P32)
+                  rzc[i] = fma((double)rq[i], (double)v[i], rzc[i]);
+                else
+                  rz = fma((double)rq[i], (double)v[i], rz);
+              }
+            }
+            fetch_rd(z + 1, (k + 1) & 3);
+            if constexpr (ZOUT)
+              rq.load(strip_buf(sb.r + (at - (S + 1) * plane), zs + 1 >= z0 && zs + 1 < z1), ir);   // the next plane's
+          }
+          if constexpr (ZOUT && !P32) {
+            // zs is the last plane of a group in one step of four at most
+            if (s == S && ((k - S) & 3) == 3 && zs % kF3Group == kF3Group - 1 && zs >= z0 && zs < z1) {
+              for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
+              if ((threadIdx.x & 63) == 0) sRz[threadIdx.x >> 6] = rz;
+              rz = 0.0;
+            }
+            if (s == S && ((k - S) & 3) == 0 && zs % kF3Group == 0 && zs > z0 && zs < z1) put_rz(zs - 1);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[s - 1][wb][i] = nv[i];
+        sV[f.p * kSt + 2 * (s - 1) + wb] = float4{nv[0], nv[1], nv[2], nv[3]};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nv[i] = v[i];
+      }
+    }
+    __syncthreads();
+  };
+  f3_march<S>(z0, z1, wact, step);
+  if constexpr (ZOUT && P32) {
+    if (f.inner) {
+      double* o = colsum + t.part + f.x + (long long)m.nx * f.y;
+      const double isc = sb.ss[t.rep].isc;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < f.nv) o[i] = rzc[i] * isc;
+    }
+  }
+  if constexpr (ZOUT && !P32) {
+    if (z1 % kF3Group != 0) {   // the lattice's last, shorter group
+      for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
+      if ((threadIdx.x & 63) == 0) sRz[threadIdx.x >> 6] = rz;
+      __syncthreads();
+    }
+    put_rz(z1 - 1);
   }
 }
 
-#undef F3_RING
+// Precision 32: r.z summed from the post pass's column sums (over the depth of
+// its tiles) per tile of tx x 512 / tx columns, wavefront butterfly, then the
+// wavefronts in turn.  Its rounding reaches the stored fields: FP32 storage
+// turns the last bit of beta into flipped last bits of a field, which the
+// fitted guess of the next solves spreads over the lattice, so this order is
+// kept whatever the smoothing tiles are.
+__global__ void __launch_bounds__(kRzBlock) k_mg_rz32(MgLevel L0, const double* __restrict__ colsum,
+                                                      double* __restrict__ partial, const SolveScal* ss) {
+  __shared__ double sum[kRzBlock / 64];
+  const Tile t = L0.rztiles[blockIdx.x];
+  if (ss[t.rep].done) return;
+  const MgRep m = L0.reps[t.rep];
+  const int x = t.x0 + (int)threadIdx.x % m.tx, y = t.y0 + (int)threadIdx.x / m.tx;
+  double rz = x < m.nx && y < m.ny ? colsum[t.part + x + (long long)m.nx * y] : 0.0;
+  for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
+  if ((threadIdx.x & 63) == 0) sum[threadIdx.x >> 6] = rz;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double tsum = 0.0;
+    for (int k = 0; k < kRzBlock / 64; ++k) tsum += sum[k];
+    store_partials(partial + (size_t)blockIdx.x * 3, tsum, 0.0, 0.0);
+  }
+}
+
+#undef F3_NB
 
 // ---- coarse levels: one workgroup per system, in LDS --------------------------
 
@@ -1397,6 +1688,27 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const MgCoarseRep*
 
 // ---- launchers -------------------------------------------------------------
 
+hipError_t mg_set_fused_lds() {
+  const void* pre3[] = {(const void*)k_mg_prefused<3, true, false>, (const void*)k_mg_prefused<3, true, true>};
+  const void* pre2[] = {(const void*)k_mg_prefused<2, true, false>, (const void*)k_mg_prefused<2, false, false>,
+                        (const void*)k_mg_prefused<2, true, true>, (const void*)k_mg_prefused<2, false, true>};
+  const void* post3[] = {(const void*)k_mg_postfused<3, true, true, false, double>,
+                         (const void*)k_mg_postfused<3, true, true, true, float>};
+  const void* post2[] = {(const void*)k_mg_postfused<2, true, false, false, double>,
+                         (const void*)k_mg_postfused<2, false, false, false, double>,
+                         (const void*)k_mg_postfused<2, true, false, true, float>,
+                         (const void*)k_mg_postfused<2, false, false, true, float>};
+  hipError_t e = hipSuccess;
+  auto set = [&](const void* f, int bytes) {
+    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  };
+  for (const void* f : pre3) set(f, f3_lds_pre<3>(kF3Block));
+  for (const void* f : pre2) set(f, f3_lds_pre<2>(kF3Block));
+  for (const void* f : post3) set(f, f3_lds_post<3>(kF3Block));
+  for (const void* f : post2) set(f, f3_lds_post<2>(kF3Block));
+  return e;
+}
+
 hipError_t mg_set_coarse_lds(int bytes) {
   hipError_t e = hipFuncSetAttribute((const void*)k_mg_coarse, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
@@ -1429,6 +1741,10 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
   const float wa = mg.w_a, wb = mg.w_b;
   const float* w0 = mg.w0;
   const SolveScal* ss = sb.ss;
+  // level 0's residual for the fused passes: the scaled FP32 copy, or (stored
+  // in FP32 anyway) r itself, scaled as it is read
+  constexpr bool kP32 = sizeof(T) == 4;
+  const float* r0 = kP32 ? (const float*)sb.r : sb.r32;
   auto H = [&](int seg, int begin) {
     if (hook) hook(hctx, seg, begin);
   };
@@ -1440,8 +1756,8 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
     const MgLevel& L = mg.lev[0];
     const MgLevel& C = mg.lev[1];
     H(MG_PRE3_0, 1);
-    hca_launch(k_mg_prefused<3>, dim3(grid_ftiles(L.nftiles, L.fchunk)), dim3(kF3Block), 0, s, L, C,
-               F3W{{w0[0], w0[1], w0[2]}}, 1.f, (const float*)sb.r32, ss);
+    hca_launch((k_mg_prefused<3, true, kP32>), dim3(L.nftiles), dim3(L.fthreads), f3_lds_pre<3>(L.fthreads), s, L, C,
+               F3W{{w0[0], w0[1], w0[2]}}, 1.f, r0, ss);
     H(MG_PRE3_0, 0);
   } else {
     const MgLevel& L = mg.lev[0];
@@ -1466,8 +1782,8 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
       const MgLevel& C = mg.lev[k + 1];
       if (!L.ntiles) continue;
       if (mg.fused && L.nftiles) {
-        hca_launch(k_mg_prefused<2>, dim3(grid_ftiles(L.nftiles, L.fchunk)), dim3(kF3Block), 0, s, L, C,
-                   F3W{{wa, wb, 0.f}}, (float)(1 << k), (const float*)L.r, ss);
+        hca_launch(L.uniform ? k_mg_prefused<2, true, kP32> : k_mg_prefused<2, false, kP32>, dim3(L.nftiles),
+                   dim3(L.fthreads), f3_lds_pre<2>(L.fthreads), s, L, C, F3W{{wa, wb, 0.f}}, (float)(1 << k), (const float*)L.r, ss);
         continue;
       }
       hca_launch((k_mg_pre<false, float>), dim3(grid_tiles(L.ntiles, w.max_blocks)), dim3(kBlock), 0, s, L, wa, wb,
@@ -1488,9 +1804,9 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
       const MgLevel& C = mg.lev[k + 1];
       if (!L.ntiles) continue;
       if (mg.fused && L.nftiles) {
-        hca_launch((k_mg_postfused<2, false, T, T>), dim3(grid_ftiles(L.nftiles, L.fchunk)), dim3(kF3Block), 0, s,
-                   L, C, corr(k + 1), F3W{{wb, wa, 0.f}}, (float)(1 << k), (const float*)L.r, (const T*)nullptr,
-                   L.ualt, sb);
+        hca_launch(L.uniform ? k_mg_postfused<2, true, false, kP32, T> : k_mg_postfused<2, false, false, kP32, T>,
+                   dim3(L.nftiles), dim3(L.fthreads), f3_lds_post<2>(L.fthreads), s, L, C, corr(k + 1), F3W{{wb, wa, 0.f}}, (float)(1 << k),
+                   (const float*)L.r, L.ualt, sb, (double*)nullptr);
         continue;
       }
       hca_launch((k_mg_post1<false, float>), dim3(grid_tiles(L.ntiles, w.max_blocks)), dim3(kBlock), 0, s, L, C,
@@ -1504,9 +1820,11 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
     const MgLevel& L = mg.lev[0];
     const MgLevel& C = mg.lev[1];
     H(MG_POST3_0, 1);
-    hca_launch((k_mg_postfused<3, true, T, T>), dim3(grid_ftiles(L.nftiles, L.fchunk)), dim3(kF3Block), 0, s, L,
-               C, corr(1), F3W{{w0[2], w0[1], w0[0]}}, 1.f, (const float*)sb.r32, (const T*)sb.r,
-               (float*)nullptr, sb);
+    hca_launch((k_mg_postfused<3, true, true, kP32, T>), dim3(L.nftiles), dim3(L.fthreads),
+               f3_lds_post<3>(L.fthreads), s, L, C, corr(1),
+               F3W{{w0[2], w0[1], w0[0]}}, 1.f, r0, (float*)nullptr, sb, mg.colsum);
+    if (kP32)
+      hca_launch(k_mg_rz32, dim3(L.nrztiles), dim3(kRzBlock), 0, s, L, (const double*)mg.colsum, sb.partial, ss);
     H(MG_POST3_0, 0);
     launch_cg_reduce(s, w, sb, RED_RZF, 0.0, 0);
   } else {

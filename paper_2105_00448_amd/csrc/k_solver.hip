@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Work w, const T* __restric
         if (i >= end) continue;
         const double r = (double)(T)(rv[u] - alpha * qv[u]);
         sb.r[i] = (T)r;
-        if (!jac) sb.r32[i] = (float)(r * sc);   // the multigrid's scaled copy
+        if (!jac && sb.r32) sb.r32[i] = (float)(r * sc);   // the multigrid's scaled copy
         rr += r * r;
         rzo += r * zo[u];
         if (jac) {
@@ -729,7 +729,7 @@ __device__ inline double residual_scale(double rr, long long n) {
   return exp2(-rint(0.5 * log2(rr / (double)n)));
 }
 
-// r32 = r sc of the systems still iterating (after the start reduce).
+// r32 = r sc of the systems still iterating.
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_cg_r32(Work w, SolverBufsT<T> sb) {
   int b0, b1;
@@ -773,8 +773,8 @@ __global__ void __launch_bounds__(kBlock) k_cg_reduce(Work w, SolverBufsT<T> sb,
   }
   const RepDev rp = w.reps[rep];
   const bool tiles = KIND != RED_UPDATE;
-  const int b0 = KIND == RED_RZF ? rp.ftile_b0 : tiles ? rp.tile_b0 : rp.flat_b0;
-  const int nb = KIND == RED_RZF ? rp.ftile_nb : tiles ? rp.tile_nb : rp.flat_nb;
+  const int b0 = KIND == RED_RZF ? rp.fpart_b0 : tiles ? rp.tile_b0 : rp.flat_b0;
+  const int nb = KIND == RED_RZF ? rp.fpart_nb : tiles ? rp.tile_nb : rp.flat_nb;
   const double t0 = sum_partials(sb.partial, b0, nb, 0, lds4);
   const double t1 = (KIND == RED_START || KIND == RED_UPDATE) ? sum_partials(sb.partial, b0, nb, 1, lds4) : 0.0;
   const double t2 = (KIND == RED_START || KIND == RED_UPDATE) ? sum_partials(sb.partial, b0, nb, 2, lds4) : 0.0;
@@ -859,14 +859,18 @@ void launch_cg_reduce(hipStream_t s, const Work& w, const SolverBufsT<T>& sb, in
 }
 
 template <typename T>
+void launch_cg_r32(hipStream_t s, const Work& w, const SolverBufsT<T>& sb) {
+  hca_launch(k_cg_r32<T>, dim3(grid_for(w.nflat, w.max_blocks)), dim3(kBlock), 0, s, w, sb);
+}
+
+template <typename T>
 void launch_cg_start(hipStream_t s, const Work& w, double rtol, int maxit, const T* c, const T* b,
                      const T* x, const SolverBufsT<T>& sb, unsigned field_mask, int nrep) {
   hca_launch(k_cg_start<T>, dim3(grid_tiles(w.ntiles, w.max_blocks)), dim3(kBlock), 0, s, w, c, b, x,
              sb);
   hca_launch(k_zero_int, dim3(1), dim3(1), 0, s, sb.ndone);   // before the start reduce counts
   launch_cg_reduce(s, w, sb, RED_START, rtol, maxit, field_mask, nrep);
-  if (!sb.jacobi)
-    hca_launch(k_cg_r32<T>, dim3(grid_for(w.nflat, w.max_blocks)), dim3(kBlock), 0, s, w, sb);
+  if (sb.r32) launch_cg_r32(s, w, sb);
 }
 
 template <typename T>
@@ -915,6 +919,7 @@ void launch_cg_finish(hipStream_t s, const Work& w, T* x, const SolverBufsT<T>& 
                                    int);                                                           \
   template void launch_cg_update<T>(hipStream_t, const Work&, double, int, const SolverBufsT<T>&);  \
   template void launch_cg_finish<T>(hipStream_t, const Work&, T*, const SolverBufsT<T>&);        \
+  template void launch_cg_r32<T>(hipStream_t, const Work&, const SolverBufsT<T>&);                 \
   template void launch_guess_projection<T>(hipStream_t, const Work&, const T*, const T*, T*, T*, T*, \
                                            double*, double*, unsigned, int, int);
 HCA_SOLVER_INST(double)

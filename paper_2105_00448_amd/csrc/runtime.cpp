@@ -106,7 +106,7 @@ const double kBytesPerVoxel[KC_COUNT] = {
     9.0 + kE,       // vessel: read L, w, V (writes only where a vessel changes)
     16.0,           // mg sweep L0: read u (4), r (4), dinv (4); write u' (4)
     12.5,           // mg prefused L0: read r (4), dinv (4); write u3 (4), r1 (1/8 of 4)
-    16.5 + kE,      // mg postfused L0: read u3 (4), e (1/8), r (4), dinv (4), r (stored); write z (4)
+    kE == 8 ? 24.5 : 16.5,   // mg postfused L0: read u3 (4), e (1/8), r (4), dinv (4), r (FP64); write z (4)
     3 * kE,         // cg_finish: read x, p; write x (once per solve)
     11 * kE};       // guess fit, per voxel of one fitted field: read x1, x2, x3, c, b (the products);
                     // read x1, x2, x3; write x0, x1, x2 (the shifted history; x0 and x1 alone
@@ -184,9 +184,14 @@ struct Ctx : ::hca_ctx {
   RepDev* d_sys = nullptr;
   FlatBlk* d_sflat = nullptr;
   Tile* d_stiles = nullptr;
-  Tile* d_ftiles = nullptr;        // level 0's fused-smoothing tiles (systems)
+  Tile* d_ftiles = nullptr;        // level 0's fused-smoothing tiles (all systems, the oxygen systems)
+  Tile* d_ftiles1 = nullptr;
   int nftiles_all = 0, nftiles1 = 0;
-  int fchunk = 16;                 // fused tiles per XCD run
+  Tile* d_rztiles = nullptr;       // precision 32: columns of each r.z partial; their sums
+  int nrz_all = 0, nrz1 = 0;
+  long long ncol = 0;
+  int fthreads = 64;               // threads of their workgroups
+  int nfparts = 0;                 // r.z partials of level 0's fused smoothing
   Work sys_all{}, sys1{};
   std::vector<long long> sys_n;
   Counters* d_cnt = nullptr;
@@ -947,26 +952,129 @@ int even_depth(int tz, int nz) {
   return std::max(2, tz & ~1);
 }
 
-// Depth of level 0's fused-smoothing tiles: each tile recomputes three planes
-// below and above its own, so deeper tiles (up to 64 planes) while a system
-// still has about g_fused_target of them (HCA_FUSED_TARGET), and at least
-// g_fused_min planes (HCA_FUSED_MIN).  Measured (same GPU, two passes): the
-// 128^3 workload 2.319 ms per step at depth 8, 2.34 at 12, 2.26 at 16, 2.36
-// at 20; the 64-replicate ensemble within 0.2 % for depths 8 to 64; the
-// 4 x 384^3 lattices take 64.
-double g_fused_target = 256.0;
-int g_fused_min = 16;
-// Coarser levels smooth in fused passes from this many cells over all systems
-// (HCA_FUSE_MIN_CELLS).  Measured per V-cycle segment: one 384^3 lattice's
-// levels >= 1 take 214 us unfused, 184 us with level 1 (21 M cells) fused,
-// 178 us with level 2 (2.7 M) too; the 128^3 lattice's level 1 (0.8 M) runs
-// at 25 us unfused and 33 us fused.
+// Tiles of the fused smoothing passes (S sweeps per pass): fe strips of four
+// cells per row, of which the first and last are halo, frpw rows per
+// wavefront, fty output rows; a function of the lattice alone.  Taken is the
+// shape with the least work and reads over the lattice's plane: 256 cells per
+// wavefront, and half the cells of its rows, each with a 128-byte line (of
+// FP64 values) more for its unaligned ends.  (A wide tile has less halo in x
+// but leaves fewer rows per wavefront and so more halo in y.)
+// Where three systems of the lattice would not give half of the chip's 1024
+// SIMDs a wavefront, tiles take one wavefront per SIMD at most.
+struct FusedShape {
+  int fe = 3, frpw = 21, fty = 2, tx = 4, ntx = 1, nty = 1, waves = 1;
+};
+FusedShape fused_shape(int nx, int ny, int nz, int S) {
+  FusedShape best;
+  const long long groups = (nz + kF3Group - 1) / kF3Group;
+  for (int max_waves : {kF3Block / 64, 4}) {
+    double best_cost = -1.0;
+    for (int fe = 3; fe <= 32; ++fe) {
+      const int rpw = 64 / fe, tx = 4 * (fe - 2);
+      const int ty_max = (max_waves * rpw - 2 * S) & ~1;
+      if (ty_max < 2) continue;
+      const int ntx = (nx + tx - 1) / tx, n = (ny + ty_max - 1) / ty_max;
+      const int ty = std::max(2, ((ny + n - 1) / n + 1) & ~1);   // the rows dealt evenly
+      const int nty = (ny + ty - 1) / ty, waves = (ty + 2 * S + rpw - 1) / rpw;
+      const double cost = (double)ntx * nty * (256.0 * waves + 0.5 * (ty + 2 * S) * (4 * fe + 16));
+      if (best_cost < 0.0 || cost < best_cost) {
+        best_cost = cost;
+        best.fe = fe;
+        best.frpw = rpw;
+        best.fty = ty;
+        best.tx = tx;
+        best.ntx = ntx;
+        best.nty = nty;
+        best.waves = waves;
+      }
+    }
+    if (3LL * best.ntx * best.nty * best.waves * groups >= 512) break;
+  }
+  return best;
+}
+
+// Planes that a fused tile of depth d marches through above the lattice's
+// bottom (k_mg.hip, f3_march).
+int fused_steps(int d, int S, bool bottom) { return (d + S + (bottom ? 0 : 4) + 3) & ~3; }
+
+// Depth of a level's fused tiles, for the whole batch (HCA_FUSED_DEPTH
+// overrides; a multiple of kF3Group: the r.z partials, and so every result,
+// do not depend on it): the fewest microseconds by a model of the pass, the
+// wavefront steps of the batch dealt over 1024 SIMDs at g_fused_work each,
+// plus the longest tile's steps at g_fused_step each (the latency that a small
+// batch is bound by).  Measured, pre + post of level 0, all systems iterating,
+// at depths 8 / 16 / 24 / 32 / 48 / 64: one 128^3 lattice 91 / 72 / 86 / 99 /
+// 132 / 165 us (16 taken), 181 x 150 x 133 158 / 153 / 168 / 143 / 186 / 222 us
+// (16), the 64-replicate ensemble 1171 / 982 / 942 / 936 / 1322 / 1310 us (32).
+int g_fused_depth = 0;
+// Precision 32: coarser levels smooth in fused passes from this many cells over
+// all systems (HCA_FUSE_MIN_CELLS).
 long long g_fuse_min_cells = 2LL << 20;
-int fused_depth(int nx, int ny, int nz, int tx) {
-  const int ty = kF3Block / tx;
-  const double nxy = (double)((nx + tx - 1) / tx) * (double)((ny + ty - 1) / ty);
-  const int tz = (int)std::floor(nz * nxy / g_fused_target);
-  return even_depth(std::max(g_fused_min, std::min(64, tz)), nz);
+double g_fused_work = 0.22, g_fused_step = 0.35;
+struct FusedLat {
+  FusedShape f;
+  int nz;
+};
+int fused_depth(const std::vector<FusedLat>& lats, int S) {
+  if (g_fused_depth) return g_fused_depth;
+  int best = kF3Group;
+  double best_us = -1.0;
+  for (int d : {8, 16, 24, 32, 48, 64}) {
+    double work = 0.0;
+    int longest = 0;
+    for (const FusedLat& l : lats) {
+      const int chunks = (l.nz + d - 1) / d;
+      double steps = 0.0;
+      for (int k = 0; k < std::min(chunks, 2); ++k) {   // the first, and the others
+        const int n = fused_steps(std::min(d, l.nz), S, k == 0);
+        steps += k == 0 ? n : (double)n * (chunks - 1);
+        longest = std::max(longest, n);
+      }
+      work += steps * l.f.ntx * l.f.nty * l.f.waves;
+    }
+    const double us = work * g_fused_work / 1024.0 + longest * g_fused_step;
+    if (best_us < 0.0 || us < best_us) {
+      best_us = us;
+      best = d;
+    }
+  }
+  return best;
+}
+
+// Precision 32: the planes of an r.z column sum, which fix the depth of level
+// 0's fused tiles there (a function of the lattice alone, like the order of
+// the sums; k_mg.hip, k_mg_rz32).
+int rz32_depth(const RepHost& H) {
+  const int ty = kRzBlock / H.tx;
+  const double nxy = (double)((H.nx + H.tx - 1) / H.tx) * (double)((H.ny + ty - 1) / ty);
+  return even_depth(std::max(16, std::min(64, (int)std::floor(H.nz * nxy / 256.0))), H.nz);
+}
+
+// Tiles in launch order: workgroup b runs on XCD b mod 8.  Each system's tiles
+// (consecutive in `in`, z-slab major) are cut into eight runs, one per XCD, so
+// that the tiles running at one time on an XCD are neighbours, whose halo
+// reads meet in its L2, and each system's work spreads over all XCDs (systems
+// finish at different iterations).  Slots left over have rep = -1.
+std::vector<Tile> deal_tiles(const std::vector<Tile>& in) {
+  std::vector<Tile> xcd[8];
+  int first = 0;   // XCD of the system's first run (systems of few tiles)
+  for (size_t b = 0; b < in.size();) {
+    size_t e = b;
+    while (e < in.size() && in[e].rep == in[b].rep) ++e;
+    const size_t n = e - b;
+    for (size_t x = 0; x < 8; ++x)
+      for (size_t k = b + x * n / 8; k < b + (x + 1) * n / 8; ++k) xcd[(first + (int)x) & 7].push_back(in[k]);
+    first = (first + (int)(n & 7)) & 7;
+    b = e;
+  }
+  size_t len = 0;
+  for (const auto& x : xcd) len = std::max(len, x.size());
+  Tile none{};
+  none.rep = -1;
+  std::vector<Tile> out(8 * len, none);
+  for (size_t x = 0; x < 8; ++x)
+    for (size_t j = 0; j < xcd[x].size(); ++j) out[8 * j + x] = xcd[x][j];
+  return out;
 }
 
 int pick_tz(int nx, int ny, int nz, int tx, double target) {
@@ -1178,15 +1286,11 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
   if (const char* e = getenv("HCA_TILE_REMAP")) g_tile_remap = atoi(e) != 0;
   if (const char* e = getenv("HCA_TILE_DEPTH")) g_tile_depth = std::max(0, atoi(e));
   if (const char* e = getenv("HCA_SOLVE_LEAD")) g_solve_lead = std::max(-8, std::min(8, atoi(e)));
-  if (const char* e = getenv("HCA_FUSED_TARGET")) {
-    const double v = atof(e);
-    if (v >= 1.0) g_fused_target = v;
-  }
-  if (const char* e = getenv("HCA_FUSED_MIN")) g_fused_min = std::max(2, std::min(64, atoi(e)));
   {
     const char* e = getenv("HCA_FUSE_MIN_CELLS");
     g_fuse_min_cells = e ? std::max(1LL, atoll(e)) : (2LL << 20);
   }
+  if (const char* e = getenv("HCA_FUSED_DEPTH")) g_fused_depth = std::max(0, std::min(1024, atoi(e))) / kF3Group * kF3Group;
   if (const char* e = getenv("HCA_MG_TILE_TARGET")) {
     const double v = atof(e);
     if (v >= 1.0) g_mg_tile_target = v;
@@ -1227,20 +1331,47 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
   {
     std::vector<RepDev> sd;
     std::vector<FlatBlk> flat;
-    std::vector<Tile> tiles, ftiles;
-    int nflat1 = 0, ntiles1 = 0, nftiles1 = 0;
+    std::vector<Tile> tiles, ftiles, rztiles;
+    int nrz1 = 0;
+    long long ncol = 0;
+    int nflat1 = 0, ntiles1 = 0, npart = 0;
+    size_t nf1 = 0;
+    std::vector<FusedLat> lats;
+    for (int r = 0; r < R; ++r) {
+      const RepHost& H = c->reps[r];
+      lats.insert(lats.end(), c->dp.nf, FusedLat{fused_shape(H.nx, H.ny, H.nz, 3), H.nz});
+    }
+    const int fdepth = fused_depth(lats, 3);
     c->sys_n.clear();
     for (int f = 0; f < c->dp.nf; ++f) {
       for (int r = 0; r < R; ++r) {
         RepDev d = lattice_entry(c->reps[r], (long long)f * c->ntot + c->reps[r].off, f * R + r,
                                  flat, tiles);
         const RepHost& H = c->reps[r];
-        d.ftile_b0 = (int)ftiles.size();
-        add_tiles(ftiles, f * R + r, H.nx, H.ny, H.nz, H.tx, fused_depth(H.nx, H.ny, H.nz, H.tx),
-                  kF3Block / H.tx);
-        d.ftile_nb = (int)ftiles.size() - d.ftile_b0;
-        const int ftx = (H.nx + H.tx - 1) / H.tx;   // tiles per row
-        c->fchunk = std::max(c->fchunk, std::min(8 * ftx, 256));
+        const FusedShape& fs = lats[(size_t)r * c->dp.nf].f;
+        const size_t first = ftiles.size();
+        if (kPrecision == 64) {
+          const int groups = (H.nz + kF3Group - 1) / kF3Group;
+          d.fpart_b0 = npart;
+          d.fpart_nb = fs.ntx * fs.nty * groups;
+          add_tiles(ftiles, f * R + r, H.nx, H.ny, H.nz, fs.tx, fdepth, fs.fty);
+          for (size_t k = first; k < ftiles.size(); ++k) {
+            Tile& t = ftiles[k];
+            t.part = npart + (t.y0 / fs.fty * fs.ntx + t.x0 / fs.tx) * groups + t.z0 / kF3Group;
+          }
+        } else {
+          const int depth = rz32_depth(H);
+          const long long plane = (long long)H.nx * H.ny;
+          const size_t rz0 = rztiles.size();
+          add_tiles(ftiles, f * R + r, H.nx, H.ny, H.nz, fs.tx, depth, fs.fty);
+          add_tiles(rztiles, f * R + r, H.nx, H.ny, H.nz, H.tx, depth, kRzBlock / H.tx);
+          for (size_t k = first; k < ftiles.size(); ++k) ftiles[k].part = (int)(ncol + ftiles[k].z0 / depth * plane);
+          for (size_t k = rz0; k < rztiles.size(); ++k) rztiles[k].part = (int)(ncol + rztiles[k].z0 / depth * plane);
+          ncol += (H.nz + depth - 1) / depth * plane;
+          d.fpart_b0 = npart;
+          d.fpart_nb = (int)(rztiles.size() - rz0);
+        }
+        npart += d.fpart_nb;
         // the theta scheme's implicit coupling
         d.a = (f == 0 ? c->dp.aK : (c->dp.vegf && f == c->dp.fV) ? c->dp.aV : c->dp.aG) * c->dp.theta;
         sd.push_back(d);
@@ -1249,15 +1380,26 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
       if (f == 0) {
         nflat1 = (int)flat.size();
         ntiles1 = (int)tiles.size();
-        nftiles1 = (int)ftiles.size();
+        nf1 = ftiles.size();
+        nrz1 = (int)rztiles.size();
       }
     }
+    if (ncol > 0x7fffffffLL) return fail(c, HCA_E_NOMEM, "too many r.z column sums");
+    const std::vector<Tile> dealt = deal_tiles(ftiles);
+    const std::vector<Tile> dealt1 = deal_tiles(std::vector<Tile>(ftiles.begin(), ftiles.begin() + nf1));
     hca_status st;
     if ((st = upload(c, &c->d_sys, sd)) != HCA_OK || (st = upload(c, &c->d_sflat, flat)) != HCA_OK ||
-        (st = upload(c, &c->d_stiles, tiles)) != HCA_OK || (st = upload(c, &c->d_ftiles, ftiles)) != HCA_OK)
+        (st = upload(c, &c->d_stiles, tiles)) != HCA_OK || (st = upload(c, &c->d_ftiles, dealt)) != HCA_OK ||
+        (st = upload(c, &c->d_ftiles1, dealt1)) != HCA_OK)
       return st;
-    c->nftiles_all = (int)ftiles.size();
-    c->nftiles1 = nftiles1;
+    if (!rztiles.empty() && (st = upload(c, &c->d_rztiles, rztiles)) != HCA_OK) return st;
+    c->nrz_all = (int)rztiles.size();
+    c->nrz1 = nrz1;
+    c->ncol = ncol;
+    c->nftiles_all = (int)dealt.size();
+    c->nftiles1 = (int)dealt1.size();
+    c->nfparts = npart;
+    for (const FusedLat& l : lats) c->fthreads = std::max(c->fthreads, 64 * l.f.waves);
     c->sys_all.nreps = c->dp.nf * R;
     c->sys_all.reps = c->d_sys;
     c->sys_all.flat = c->d_sflat;
@@ -1293,11 +1435,12 @@ hca_status alloc_all(Ctx* c) {
   for (double** p : f1)
     if ((st = big(p, n)) != HCA_OK) return st;
   Real** f3[] = {&c->F, &c->c, &c->b, &c->sb.r, &c->sb.p0, &c->sb.p1, &c->sb.q};
-  for (Real** p : f3)
-    if ((st = big(p, n3)) != HCA_OK) return st;
+  for (Real** p : f3)   // (strip loads of the multigrid read up to kStripPad values past a row)
+    if ((st = big(p, n3 + kStripPad)) != HCA_OK) return st;
   if (c->use_mg) {
-    for (float** p : {&c->sb.z32, &c->sb.r32}) {
-      hipError_t e = dalloc(p, n3);
+    for (float** p : {&c->sb.z32, &c->sb.r32}) {   // (strip loads: as above)
+      if (p == &c->sb.r32 && sizeof(Real) == 4 && c->prm.mg_fuse) continue;   // the fused passes scale r themselves
+      hipError_t e = dalloc(p, n3 + kStripPad);
       if (e == hipErrorOutOfMemory) return fail(c, HCA_E_NOMEM, "device memory exhausted");
       HIPCHK(c, e);
     }
@@ -1310,7 +1453,7 @@ hca_status alloc_all(Ctx* c) {
     HIPCHK(c, hipMemset(p, 0, sizeof(double) * n));
   for (void* p : {(void*)c->F, (void*)c->c, (void*)c->b, (void*)c->sb.r, (void*)c->sb.p0, (void*)c->sb.p1,
                   (void*)c->sb.q})
-    HIPCHK(c, hipMemset(p, 0, sizeof(Real) * n3));
+    HIPCHK(c, hipMemset(p, 0, sizeof(Real) * (n3 + kStripPad)));
   HIPCHK(c, hipMemset(c->L, 0, n));
   c->K = c->F;
   c->G1 = c->F + n;
@@ -1319,7 +1462,7 @@ hca_status alloc_all(Ctx* c) {
   c->V = c->dp.vegf ? c->F + (size_t)c->dp.fV * n : nullptr;
   c->sb.jacobi = c->use_mg ? 0 : 1;
   if (!c->use_mg && (st = big(&c->sb.dinv, n3)) != HCA_OK) return st;
-  const size_t nwork = (size_t)std::max({c->sys_all.ntiles, c->sys_all.nflat, c->nftiles_all});
+  const size_t nwork = (size_t)std::max({c->sys_all.ntiles, c->sys_all.nflat, c->nfparts});
   HIPCHK(c, dalloc(&c->sb.partial, 3 * nwork));
   HIPCHK(c, dalloc(&c->sb.counter, nsys));
   HIPCHK(c, hipMemset(c->sb.counter, 0, sizeof(unsigned) * nsys));
@@ -1359,6 +1502,17 @@ hca_status mg_alloc(Ctx* c, T** p, size_t count) {
   if (e == hipErrorOutOfMemory) return fail(c, HCA_E_NOMEM, "device memory exhausted (multigrid)");
   HIPCHK(c, e);
   c->mg_mem.push_back((void*)*p);
+  return HCA_OK;
+}
+
+// A level array: kStripPad values before and after it, all 0 (the fused
+// passes' strip loads reach past a row's ends; what they read there is
+// discarded).
+hca_status mg_alloc_level(Ctx* c, float** p, size_t count) {
+  hca_status st = mg_alloc(c, p, count + 2 * kStripPad);
+  if (st != HCA_OK) return st;
+  HIPCHK(c, hipMemset(*p, 0, sizeof(float) * (count + 2 * kStripPad)));
+  *p += kStripPad;
   return HCA_OK;
 }
 
@@ -1440,20 +1594,33 @@ hca_status build_mg(Ctx* c) {
     std::vector<MgRep>& mr = mreps[k];
     mr.resize(S);
     std::vector<Tile> tiles, rtiles, ftiles;
-    int ntiles1 = 0, nrtiles1 = 0, nftiles1 = 0, fchunk = 16;
+    int ntiles1 = 0, nrtiles1 = 0;
+    size_t nf1 = 0;
     long long off = 0;
-    // a coarser level smooths in fused passes when every system iterates on
-    // it, all its cells are full 2^k-cubes (uniform couplings a 2^k) and the
-    // level holds at least g_fuse_min_cells cells over all systems (smaller
-    // levels run faster as one kernel per sweep)
-    bool fuse_k = k >= 1 && c->prm.mg_fuse;
-    long long cells_k = 0;
-    for (int r = 0; fuse_k && r < R; ++r) {
-      for (int i = 0; i < 3; ++i)
-        fuse_k = fuse_k && k < kcr[r] && dims[r][0][i] % (1 << k) == 0;
-      if (fuse_k) cells_k += (long long)dims[r][k][0] * dims[r][k][1] * dims[r][k][2];
+    int uniform = 1;   // all cells of the level are full 2^k-cubes
+    std::vector<FusedLat> lats;
+    for (int s = 0; k >= 1 && s < S; ++s) {
+      const int r = s % R;
+      if (k < kcr[r])
+        lats.push_back(FusedLat{fused_shape(dims[r][k][0], dims[r][k][1], dims[r][k][2], 2), dims[r][k][2]});
     }
-    fuse_k = fuse_k && cells_k * (S / R) >= g_fuse_min_cells;
+    const int fdepth = fused_depth(lats, 2);
+    int fthreads = k == 0 ? c->fthreads : 64;
+    for (const FusedLat& l : lats) fthreads = std::max(fthreads, 64 * l.f.waves);
+    // Every level smooths in fused passes in precision 64.  In precision 32,
+    // whose stored fields' last bits follow the order of a sweep's neighbour sum,
+    // a coarser level does where all systems iterate on it, all its cells are
+    // full 2^k-cubes and it holds at least 2 M cells over all systems; the
+    // smaller ones keep one kernel per sweep and their bits.
+    bool fuse_k = c->prm.mg_fuse != 0;
+    if (fuse_k && k >= 1 && sizeof(Real) == 4) {
+      long long cells_k = 0;
+      for (int r = 0; fuse_k && r < R; ++r) {
+        for (int i = 0; i < 3; ++i) fuse_k = fuse_k && k < kcr[r] && dims[r][0][i] % (1 << k) == 0;
+        if (fuse_k) cells_k += (long long)dims[r][k][0] * dims[r][k][1] * dims[r][k][2];
+      }
+      fuse_k = fuse_k && cells_k * (S / R) >= g_fuse_min_cells;
+    }
     for (int s = 0; s < S; ++s) {
       const int r = s % R;
       MgRep& m = mr[s];
@@ -1468,6 +1635,11 @@ hca_status build_mg(Ctx* c) {
         m.ny = dims[r][k][1];
         m.nz = dims[r][k][2];
         m.active = k < kcr[r];
+        for (int i = 0; m.active && i < 3; ++i) uniform = uniform && dims[r][0][i] % (1 << k) == 0;
+        const FusedShape fs = fused_shape(m.nx, m.ny, m.nz, k == 0 ? 3 : 2);
+        m.fe = fs.fe;
+        m.frpw = fs.frpw;
+        m.fty = fs.fty;
         if (k == 0) {
           m.tx = sd[s].tx;
           m.off = sd[s].off;
@@ -1486,60 +1658,70 @@ hca_status build_mg(Ctx* c) {
           m.rtile_b0 = (int)rtiles.size();
           add_tiles(rtiles, s, m.nx, m.ny, m.nz, m.tx, tz);
           m.rtile_nb = (int)rtiles.size() - m.rtile_b0;
-          if (fuse_k) {
-            add_tiles(ftiles, s, m.nx, m.ny, m.nz, m.tx, fused_depth(m.nx, m.ny, m.nz, m.tx), kF3Block / m.tx);
-            fchunk = std::max(fchunk, std::min(8 * ((m.nx + m.tx - 1) / m.tx), 256));
+          if (m.active && fuse_k) {
+            add_tiles(ftiles, s, m.nx, m.ny, m.nz, fs.tx, fdepth, fs.fty);
           }
         }
       }
       if (s == R - 1) {
         ntiles1 = (int)tiles.size();
         nrtiles1 = (int)rtiles.size();
-        nftiles1 = (int)ftiles.size();
+        nf1 = ftiles.size();
       }
     }
     MgLevel& L = mg.lev[k];
+    Tile *dft = nullptr, *dft1 = c->d_ftiles1;
+    int nftiles1 = c->nftiles1;
     MgRep* d_mr = nullptr;
     hca_status st = mg_upload(c, &d_mr, mr);
     if (st != HCA_OK) return st;
     L.reps = d_mr;
+    L.uniform = uniform;
+    L.fthreads = fthreads;
+    L.rztiles = c->d_rztiles;
+    L.nrztiles = k == 0 ? c->nrz_all : 0;
     if (k == 0) {
       L.tiles = c->d_stiles;
       L.ntiles = c->sys_all.ntiles;
       ntiles1 = c->sys1.ntiles;
       L.ftiles = c->d_ftiles;
       L.nftiles = c->nftiles_all;
-      L.fchunk = c->fchunk;
       const size_t n = (size_t)c->dp.nf * c->ntot;
-      if ((st = mg_alloc(c, &L.dinv, n)) != HCA_OK || (st = mg_alloc(c, &L.u, n)) != HCA_OK ||
-          (st = mg_alloc(c, &L.ualt, n)) != HCA_OK)
+      if ((st = mg_alloc_level(c, &L.dinv, n)) != HCA_OK || (st = mg_alloc_level(c, &L.u, n)) != HCA_OK ||
+          (!c->prm.mg_fuse && (st = mg_alloc_level(c, &L.ualt, n)) != HCA_OK))
         return st;
     } else {
       Tile* dt = nullptr;
       Tile* drt = nullptr;
-      Tile* dft = nullptr;
+      const std::vector<Tile> dealt = deal_tiles(ftiles);
+      const std::vector<Tile> dealt1 = deal_tiles(std::vector<Tile>(ftiles.begin(), ftiles.begin() + nf1));
       if ((st = mg_upload(c, &dt, tiles)) != HCA_OK || (st = mg_upload(c, &drt, rtiles)) != HCA_OK ||
-          (!ftiles.empty() && (st = mg_upload(c, &dft, ftiles)) != HCA_OK))
+          (!ftiles.empty() &&
+           ((st = mg_upload(c, &dft, dealt)) != HCA_OK || (st = mg_upload(c, &dft1, dealt1)) != HCA_OK)))
         return st;
       L.tiles = dt;
       L.ntiles = (int)tiles.size();
       L.rtiles = drt;
       L.nrtiles = (int)rtiles.size();
       L.ftiles = dft;
-      L.nftiles = (int)ftiles.size();
-      L.fchunk = fchunk;
+      L.nftiles = (int)dealt.size();
+      nftiles1 = (int)dealt1.size();
       const size_t n = (size_t)std::max<long long>(off, 1);
-      if ((st = mg_alloc(c, &L.c, n)) != HCA_OK || (st = mg_alloc(c, &L.dinv, n)) != HCA_OK ||
-          (st = mg_alloc(c, &L.r, n)) != HCA_OK || (st = mg_alloc(c, &L.u, n)) != HCA_OK ||
-          (st = mg_alloc(c, &L.ualt, n)) != HCA_OK)
+      if ((st = mg_alloc_level(c, &L.c, n)) != HCA_OK || (st = mg_alloc_level(c, &L.dinv, n)) != HCA_OK ||
+          (st = mg_alloc_level(c, &L.r, n)) != HCA_OK || (st = mg_alloc_level(c, &L.u, n)) != HCA_OK ||
+          (st = mg_alloc_level(c, &L.ualt, n)) != HCA_OK)
         return st;
       pc[k] = L.c;
       pr[k] = L.r;
-      pu[k] = L.u;
+      // a level's correction: its ualt where it smooths in fused passes (for
+      // some of the systems: the others' one-workgroup solves write there too)
+      pu[k] = L.nftiles ? L.ualt : L.u;
     }
     c->mg1.lev[k] = L;
     c->mg1.lev[k].ntiles = ntiles1;
-    c->mg1.lev[k].nftiles = k == 0 ? c->nftiles1 : nftiles1;
+    c->mg1.lev[k].ftiles = dft1;
+    c->mg1.lev[k].nftiles = nftiles1;
+    c->mg1.lev[k].nrztiles = k == 0 ? c->nrz1 : 0;
     c->mg1.lev[k].nrtiles = k == 0 ? 0 : nrtiles1;
   }
   int nglob1 = 1;
@@ -1579,7 +1761,10 @@ hca_status build_mg(Ctx* c) {
   mg.coarse = dcr;
   mg.coarse_lds_bytes = (int)lds_max;
   if (lds_max > 65536) HIPCHK(c, mg_set_coarse_lds((int)lds_max));
+  if (c->prm.mg_fuse) HIPCHK(c, mg_set_fused_lds());
   if ((st = mg_alloc(c, &mg.coarse_pre, (size_t)pre_total)) != HCA_OK) return st;
+  if (c->ncol && c->prm.mg_fuse && (st = mg_alloc(c, &mg.colsum, (size_t)c->ncol)) != HCA_OK) return st;
+  c->mg1.colsum = mg.colsum;
   if ((st = mg_upload(c, &mg.lev_c, pc)) != HCA_OK || (st = mg_upload(c, &mg.lev_r, pr)) != HCA_OK ||
       (st = mg_upload(c, &mg.lev_u, pu)) != HCA_OK)
     return st;
@@ -1624,7 +1809,7 @@ void free_all(Ctx* c) {
   void* bufs[] = {c->L, c->code, c->win, (void*)c->ca_list.cells, (void*)c->ca_list.item_n, c->w, c->P, c->Vc, c->phi, c->F, c->c, c->b,
                   c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
                   c->sb.counter, c->sb.ss, c->sb.ndone, c->dose_t, c->dose_a, c->g0, c->b_o2lin, c->Fprev, c->Fprev2, c->d_gpart, c->d_galpha, (void*)c->d_fin, c->d_step,
-                  c->d_reps, c->d_flat, c->d_tiles, c->d_sys, c->d_sflat, c->d_stiles, c->d_ftiles, c->d_cnt, (void*)c->d_cpart,
+                  c->d_reps, c->d_flat, c->d_tiles, c->d_sys, c->d_sflat, c->d_stiles, c->d_ftiles, c->d_ftiles1, c->d_rztiles, c->d_cnt, (void*)c->d_cpart,
                   c->d_bad, c->d_theta, (void*)c->d_pack, (void*)c->d_gelu, c->before,
                   c->item_cnt, c->item_off};
   for (void* p : bufs)
