@@ -76,10 +76,20 @@ __device__ inline bf16x8 bop(const Hid& H, int kb) {
 
 // ---- packing ----------------------------------------------------------------
 
-// One thread per (MFMA block, lane): the 8 bf16 values lane `lane` feeds as A.
-__global__ void k_mlp_pack(const float* __restrict__ th, bf16x8* __restrict__ pk) {
+__device__ inline float2 gelu_table_entry(int i) {
+  auto Phi = [](int k) { return 0.5 * erfc(-((k - (double)kGeluOrigin) / kGeluScale) * 0.70710678118654752); };
+  const double a = Phi(i);
+  return make_float2((float)a, i < kGeluN ? (float)(Phi(i + 1) - a) : 0.f);
+}
+
+// One thread per (MFMA block, lane): the 8 bf16 values lane `lane` feeds as A;
+// with tab, further threads write the GELU table in the same launch.
+__global__ void k_mlp_pack(const float* __restrict__ th, bf16x8* __restrict__ pk, float2* __restrict__ tab) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= kPackAll) return;
+  if (g >= kPackAll) {
+    if (tab && g - kPackAll <= kGeluN) tab[g - kPackAll] = gelu_table_entry(g - kPackAll);
+    return;
+  }
   const int lane = g & 63, m = lane & 31, h = lane >> 5;
   const int blk = g >> 6;
   float v[8];
@@ -118,17 +128,33 @@ __global__ void k_mlp_pack(const float* __restrict__ th, bf16x8* __restrict__ pk
 
 __global__ void k_mlp_gelu_table(float2* __restrict__ tab) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > kGeluN) return;
-  auto Phi = [](int k) { return 0.5 * erfc(-((k - (double)kGeluOrigin) / kGeluScale) * 0.70710678118654752); };
-  const double a = Phi(i);
-  tab[i] = make_float2((float)a, i < kGeluN ? (float)(Phi(i + 1) - a) : 0.f);
+  if (i <= kGeluN) tab[i] = gelu_table_entry(i);
+}
+
+// Stores parameter p's new value v at its two places in the packed operands
+// (k_mlp_pack's layout; biases have none).
+__device__ inline void pack_param(__bf16* __restrict__ pk, int p, float v) {
+  const __bf16 b = (__bf16)v;
+  auto put = [&](int blk, int lane, int j) { pk[((size_t)blk * 64 + lane) * 8 + j] = b; };
+  // contraction index c -> k-block c / 16, half and element of its slot (perm_slot's inverse)
+  auto half = [](int c) { return (c >> 2) & 1; };
+  auto elem = [](int c) { return (((c >> 3) & 1) << 2) | (c & 3); };
+  if (p < kOb1) {
+    const int o = p / kMlpIn, k = p % kMlpIn;
+    put(kPackL1 / 64 + (o >> 5), o & 31, k);
+  } else if ((p >= kOW2 && p < kOb2) || (p >= kOW3 && p < kOb3)) {
+    const bool l2 = p < kOb2;
+    const int e = p - (l2 ? kOW2 : kOW3), o = e / kMlpHid, i = e % kMlpHid;
+    put((l2 ? kPackL2 : kPackL3) / 64 + (o >> 5) * 4 + (i >> 4), (o & 31) + 32 * half(i), elem(i));
+    put((l2 ? kPackL2T : kPackL3T) / 64 + (i >> 5) * 4 + (o >> 4), (i & 31) + 32 * half(o), elem(o));
+  } else if (p >= kOW4 && p < kOb4) {
+    const int e = p - kOW4, o = e / kMlpHid, i = e % kMlpHid;
+    put(kPackL4 / 64 + (i >> 4), o + 32 * half(i), elem(i));
+    put(kPackL4T / 64 + (i >> 5), i & 31, o);
+  }
 }
 
 // ---- forward of one 32-sample tile (one wavefront) ------------------------------
-
-struct Pre {
-  f32x16 z[3][2];   // hidden pre-activations (training)
-};
 
 // Weight source: A operand of packed block `blk` (kPackL1/64 ...) for this
 // lane.  Bias source: accumulator of layer L (0..2), row tile mt, initialised
@@ -180,20 +206,16 @@ struct LdsNet {
 // xin: layer-1 B operand (lanes of half 0 hold the 6 standardised inputs of
 // sample n = lane).  Returns the output accumulator including b4: outputs in
 // registers 0..2 of lanes 0..31.
-template <bool KEEP, typename NET>
-__device__ inline f32x16 mlp_forward_tile(const NET& net, bf16x8 xin, int lane, Pre* pre, Hid* hs) {
+template <typename NET>
+__device__ inline f32x16 mlp_forward_tile(const NET& net, bf16x8 xin, int lane) {
   const int h = lane >> 5;
   Hid H;
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt) {
     f32x16 acc = mfma16(net.A(kPackL1 / 64 + mt), xin, net.bias(0, mt));
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (KEEP) pre->z[0][mt][j] = acc[j];
-      H.v[mt][j] = (__bf16)net.gelu(acc[j]);
-    }
+    for (int j = 0; j < 16; ++j) H.v[mt][j] = (__bf16)net.gelu(acc[j]);
   }
-  if (KEEP) hs[0] = H;
 #pragma unroll
   for (int L = 1; L < 3; ++L) {
     const int blk = (L == 1 ? kPackL2 : kPackL3) / 64;
@@ -204,13 +226,9 @@ __device__ inline f32x16 mlp_forward_tile(const NET& net, bf16x8 xin, int lane, 
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) acc = mfma16(net.A(blk + mt * 4 + kb), bop(H, kb), acc);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        if (KEEP) pre->z[L][mt][j] = acc[j];
-        Hn.v[mt][j] = (__bf16)net.gelu(acc[j]);
-      }
+      for (int j = 0; j < 16; ++j) Hn.v[mt][j] = (__bf16)net.gelu(acc[j]);
     }
     H = Hn;
-    if (KEEP) hs[L] = H;
   }
   f32x16 out = {};
   if (h == 0) {
@@ -238,8 +256,8 @@ __device__ inline void forward64(const NET& net, const float (&x)[kMlpIn], int l
   float x1[kMlpIn];
 #pragma unroll
   for (int f = 0; f < kMlpIn; ++f) x1[f] = __shfl(x[f], (lane & 31) + 32, 64);
-  const f32x16 o0 = mlp_forward_tile<false>(net, input_operand(x, h), lane, nullptr, nullptr);
-  const f32x16 o1 = mlp_forward_tile<false>(net, input_operand(x1, h), lane, nullptr, nullptr);
+  const f32x16 o0 = mlp_forward_tile(net, input_operand(x, h), lane);
+  const f32x16 o1 = mlp_forward_tile(net, input_operand(x1, h), lane);
 #pragma unroll
   for (int o = 0; o < kMlpOut; ++o) {
     const float t1 = __shfl(o1[o], lane & 31, 64);
@@ -252,7 +270,7 @@ __device__ inline void forward64(const NET& net, const float (&x)[kMlpIn], int l
 template <typename NET>
 __device__ inline void forward32(const NET& net, const float (&x)[kMlpIn], int lane,
                                  float (&y)[kMlpOut]) {
-  const f32x16 o = mlp_forward_tile<false>(net, input_operand(x, lane >> 5), lane, nullptr, nullptr);
+  const f32x16 o = mlp_forward_tile(net, input_operand(x, lane >> 5), lane);
 #pragma unroll
   for (int k = 0; k < kMlpOut; ++k) y[k] = o[k];
 }
@@ -609,30 +627,28 @@ __global__ void k_mlp_init(uint64_t seed, float* __restrict__ th) {
   th[p] = (float)((2.0 * unit53(r.v[0]) - 1.0) * lim);
 }
 
-// Minibatch t: row indices drawn with replacement, Philox counter
+// Row of sample j of minibatch t, drawn with replacement: Philox counter
 // (j, t, 3, 0), key (seed, 0), reduced modulo n.
-__global__ void k_mlp_sample(uint64_t seed, long long t, long long n, int batch, int* __restrict__ idx) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= batch) return;
+__device__ inline long long mlp_sample_row(uint64_t seed, long long t, long long n, int j) {
   const U64x4 r = philox4x64_10((uint64_t)j, (uint64_t)t, 3, 0, seed, 0);
-  idx[j] = (int)(r.v[0] % (uint64_t)n);
+  return (int)(r.v[0] % (uint64_t)n);
 }
 
 // ---- training: forward + backward of 64 samples per workgroup ------------------
 
-constexpr int kTS = 64;   // samples per workgroup (two wavefronts of 32)
+constexpr int kTS = 64;    // samples per workgroup
+constexpr int kTSP = 72;   // their row stride in the LDS tiles (conflict-free 16-byte row reads)
 
-// LDS tiles are [unit][sample] bf16 with 64 samples per row.
-__device__ inline void lds_store_tile(__bf16* base, const Hid& H, int lane, int col0) {
+// LDS tiles are [unit][sample] bf16 with 64 samples per row.  Row tile mt of a
+// wavefront's 32 samples.
+__device__ inline void lds_store_rows(__bf16* base, const __bf16 (&v)[16], int mt, int lane, int col0) {
   const int h = lane >> 5, n = lane & 31;
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) base[drow(mt, j, h) * kTS + col0 + n] = H.v[mt][j];
+  for (int j = 0; j < 16; ++j) base[drow(mt, j, h) * kTSP + col0 + n] = v[j];
 }
 
 __device__ inline bf16x8 lds_row8(const __bf16* base, int row, int col) {
-  return *reinterpret_cast<const bf16x8*>(base + row * kTS + col);
+  return *reinterpret_cast<const bf16x8*>(base + row * kTSP + col);
 }
 
 // Sum over the workgroup's 64 samples of dZ[o][s] H[i][s] for output row
@@ -654,122 +670,176 @@ __device__ inline f32x16 wgrad_tile(const __bf16* dZ, int nrow_dz, const __bf16*
 
 // Per-workgroup gradient of the summed loss over samples idx[64 wg .. 64 wg + 63]
 // (already divided by 3 x batch), and the workgroup's summed squared error.
-// Row indices are clamped to [0, n).
-__global__ void __launch_bounds__(128) k_mlp_grad(const bf16x8* __restrict__ pk,
+// Row indices are clamped to [0, n); without idx the rows are minibatch t's
+// draw.
+//
+// A batch is a few dozen workgroups, so the chain of one workgroup's layers is
+// what the kernel takes: four wavefronts, two per 32 samples, each with one
+// row tile of the hidden units (half of the GELUs); a layer's activations are
+// exchanged as the next layer's B operands (two of its four k-blocks per
+// wavefront) through LDS.  The products and sums of every value are those of
+// one wavefront per 32 samples, which took 16.4 us at 64 workgroups with a
+// launch of 4.7 us more for the draw; now 13.0 us with it.  (The operands loaded
+// layer by layer instead of at once: 13.9 us.)
+__global__ void __launch_bounds__(256) k_mlp_grad(const bf16x8* __restrict__ pk,
                                                   const float* __restrict__ th,
                                                   const float2* __restrict__ tab,
                                                   const float* __restrict__ Xs,
                                                   const float* __restrict__ Ys,
-                                                  const int* __restrict__ idx, int batch,
-                                                  long long nrows, float* __restrict__ partial) {
-  __shared__ __attribute__((aligned(16))) __bf16 sH[3][kMlpHid * kTS];
-  __shared__ __attribute__((aligned(16))) __bf16 sX[8 * kTS];
-  __shared__ __attribute__((aligned(16))) __bf16 sdZ[3][kMlpHid * kTS];
-  __shared__ __attribute__((aligned(16))) __bf16 sdZ4[kMlpOut * kTS];
+                                                  const int* __restrict__ idx, uint64_t seed, long long t,
+                                                  int batch, long long nrows, float* __restrict__ partial) {
+  __shared__ __attribute__((aligned(16))) __bf16 sH[3][kMlpHid * kTSP];
+  __shared__ __attribute__((aligned(16))) __bf16 sX[8 * kTSP];
+  __shared__ __attribute__((aligned(16))) __bf16 sdZ[3][kMlpHid * kTSP];
+  __shared__ __attribute__((aligned(16))) __bf16 sdZ4[kMlpOut * kTSP];
+  __shared__ bf16x8 sB[2][2][4][64];   // [parity of the layer][sample tile][k-block][lane]
   __shared__ float sloss[2];
   __shared__ float2 stab[kGeluN + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
+  const int st = wave & 1, mt = wave >> 1;   // sample tile, row tile
+  const int col0 = 32 * st;
+  const int smp = blockIdx.x * kTS + col0 + n;
+  const GlobalNet net{pk, th, stab, lane};
+  // this wavefront's operands of every layer, loaded at once (one latency)
+  bf16x8 w1, w4t, w2[4], w3[4], w4[4], w3t[4], w2t[4];
+  f32x16 bias[3];
+  w1 = net.A(kPackL1 / 64 + mt);
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb) {
+    w2[kb] = net.A(kPackL2 / 64 + mt * 4 + kb);
+    w3[kb] = net.A(kPackL3 / 64 + mt * 4 + kb);
+    w4[kb] = net.A(kPackL4 / 64 + kb);
+    w3t[kb] = net.A(kPackL3T / 64 + mt * 4 + kb);
+    w2t[kb] = net.A(kPackL2T / 64 + mt * 4 + kb);
+  }
+  w4t = net.A(kPackL4T / 64 + mt);
+#pragma unroll
+  for (int L = 0; L < 3; ++L) bias[L] = net.bias(L, mt);
+  const long long row = idx ? min(max((long long)idx[smp], 0LL), nrows - 1) : mlp_sample_row(seed, t, nrows, smp);
   load_gelu_table(tab, stab);
-  __syncthreads();
-  const int col0 = 32 * wave;
-  const long long row = min(max((long long)idx[blockIdx.x * kTS + col0 + n], 0LL), nrows - 1);
   float x[kMlpIn];
 #pragma unroll
   for (int f = 0; f < kMlpIn; ++f) x[f] = Xs[row * kMlpIn + f];
+  float ys[kMlpOut];
+#pragma unroll
+  for (int o = 0; o < kMlpOut; ++o) ys[o] = Ys[row * kMlpOut + o];
+  __syncthreads();
+  if (mt == 0 && h == 0) {
+#pragma unroll
+    for (int f = 0; f < 8; ++f) sX[f * kTSP + col0 + n] = (__bf16)(f < kMlpIn ? x[f] : 0.0f);
+  }
+  // this wavefront's rows of a layer's values: kept for the weight gradients
+  // and exchanged; then the four B operands of its sample tile
+  int par = 0;
+  bf16x8 B[4];
+  auto exchange = [&](const __bf16 (&v)[16], __bf16* keep) {
+    lds_store_rows(keep, v, mt, lane, col0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      bf16x8 b;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) b[j] = v[8 * q + j];
+      sB[par][st][2 * mt + q][lane] = b;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) B[kb] = sB[par][st][kb][lane];
+    par ^= 1;
+  };
+  f32x16 z[3];   // hidden pre-activations of this wavefront's rows
+#pragma unroll
+  for (int L = 0; L < 3; ++L) {
+    f32x16 acc = bias[L];
+    if (L == 0) {
+      acc = mfma16(w1, input_operand(x, h), acc);
+    } else {
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) acc = mfma16(L == 1 ? w2[kb] : w3[kb], B[kb], acc);
+    }
+    z[L] = acc;
+    __bf16 v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = (__bf16)net.gelu(acc[j]);
+    exchange(v, sH[L]);
+  }
+  // outputs (both wavefronts of a sample tile)
+  f32x16 out = {};
   if (h == 0) {
 #pragma unroll
-    for (int f = 0; f < 8; ++f) sX[f * kTS + col0 + n] = (__bf16)(f < kMlpIn ? x[f] : 0.0f);
+    for (int o = 0; o < kMlpOut; ++o) out[o] = net.b4(o);
   }
-  Pre pre;
-  Hid hs[3];
-  const GlobalNet gnet{pk, th, stab, lane};
-  const f32x16 out = mlp_forward_tile<true>(gnet, input_operand(x, h), lane, &pre, hs);
 #pragma unroll
-  for (int L = 0; L < 3; ++L) lds_store_tile(sH[L], hs[L], lane, col0);
+  for (int kb = 0; kb < 4; ++kb) out = mfma16(w4[kb], B[kb], out);
   // dL/dy on the lanes of half 0 (sample n); loss = mean over batch and outputs
   const float inv = 2.0f / (float)(kMlpOut * batch);
   float dy[kMlpOut];
   float l2 = 0.0f;
 #pragma unroll
   for (int o = 0; o < kMlpOut; ++o) {
-    const float d = out[o] - Ys[row * kMlpOut + o];
+    const float d = out[o] - ys[o];
     dy[o] = h == 0 ? d * inv : 0.0f;
     l2 += h == 0 ? d * d : 0.0f;
   }
-  if (h == 0) {
+  if (mt == 0 && h == 0) {
 #pragma unroll
-    for (int o = 0; o < kMlpOut; ++o) sdZ4[o * kTS + col0 + n] = (__bf16)dy[o];
+    for (int o = 0; o < kMlpOut; ++o) sdZ4[o * kTSP + col0 + n] = (__bf16)dy[o];
   }
   bf16x8 bdy;
 #pragma unroll
   for (int j = 0; j < 8; ++j) bdy[j] = (__bf16)(j < kMlpOut ? dy[j] : 0.0f);
+  for (int o = 32; o > 0; o >>= 1) l2 += __shfl_xor(l2, o, 64);
+  if (mt == 0 && lane == 0) sloss[st] = l2;
   // dZ3 = (W4^T dy) * GELU'(z3), then dZ_L = (W_{L+1}^T dZ_{L+1}) * GELU'(z_L)
-  Hid dz;
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
+  for (int L = 2; L >= 0; --L) {
     f32x16 acc = {};
-    acc = mfma16(pk[kPackL4T + mt * 64 + lane], bdy, acc);
+    if (L == 2) {
+      acc = mfma16(w4t, bdy, acc);
+    } else {
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) acc = mfma16(L == 1 ? w3t[kb] : w2t[kb], B[kb], acc);
+    }
+    __bf16 v[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       float g, dg;
-      gelu<true>(pre.z[2][mt][j], g, dg);
-      dz.v[mt][j] = (__bf16)(acc[j] * dg);
+      gelu<true>(z[L][j], g, dg);
+      v[j] = (__bf16)(acc[j] * dg);
     }
+    exchange(v, sdZ[L]);   // (after the last: the barrier of the tiles below)
   }
-  lds_store_tile(sdZ[2], dz, lane, col0);
-#pragma unroll
-  for (int L = 2; L >= 1; --L) {
-    const int blk = L == 2 ? kPackL3T : kPackL2T;
-    Hid nd;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      f32x16 acc = {};
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) acc = mfma16(pk[blk + (mt * 4 + kb) * 64 + lane], bop(dz, kb), acc);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        float g, dg;
-        gelu<true>(pre.z[L - 1][mt][j], g, dg);
-        nd.v[mt][j] = (__bf16)(acc[j] * dg);
-      }
-    }
-    dz = nd;
-    lds_store_tile(sdZ[L - 1], dz, lane, col0);
-  }
-  for (int o = 32; o > 0; o >>= 1) l2 += __shfl_xor(l2, o, 64);
-  if (lane == 0) sloss[wave] = l2;
-  __syncthreads();
   float* pg = partial + (size_t)blockIdx.x * kPartialStride;
-  {   // W4 (3 x 64): wave w takes input column tile w
+#pragma unroll
+  for (int L = 2; L >= 1; --L) {   // W3 = dZ3 H2^T, W2 = dZ2 H1^T: wave w takes row tile w / 2, column tile w % 2
+    const int ow = L == 2 ? kOW3 : kOW2;
+    const f32x16 acc = wgrad_tile(sdZ[L], kMlpHid, sH[L - 1], kMlpHid, mt, st, lane);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) pg[ow + drow(mt, j, h) * kMlpHid + 32 * st + n] = acc[j];
+  }
+  if (wave < 2) {   // W4 (3 x 64): input column tile w
     const f32x16 acc = wgrad_tile(sdZ4, kMlpOut, sH[2], kMlpHid, 0, wave, lane);
     if (h == 0) {
 #pragma unroll
       for (int j = 0; j < kMlpOut; ++j) pg[kOW4 + j * kMlpHid + 32 * wave + n] = acc[j];
     }
-  }
-#pragma unroll
-  for (int L = 2; L >= 1; --L) {   // W3 = dZ3 H2^T, W2 = dZ2 H1^T: wave w takes row tile w
-    const int ow = L == 2 ? kOW3 : kOW2;
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const f32x16 acc = wgrad_tile(sdZ[L], kMlpHid, sH[L - 1], kMlpHid, wave, nt, lane);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) pg[ow + drow(wave, j, h) * kMlpHid + 32 * nt + n] = acc[j];
-    }
-  }
-  {   // W1 = dZ1 X^T (64 x 6)
-    const f32x16 acc = wgrad_tile(sdZ[0], kMlpHid, sX, kMlpIn, wave, 0, lane);
+  } else {   // W1 = dZ1 X^T (64 x 6): row tile w - 2
+    const f32x16 acc = wgrad_tile(sdZ[0], kMlpHid, sX, kMlpIn, wave - 2, 0, lane);
     if (n < kMlpIn) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) pg[kOW1 + drow(wave, j, h) * kMlpIn + n] = acc[j];
+      for (int j = 0; j < 16; ++j) pg[kOW1 + drow(wave - 2, j, h) * kMlpIn + n] = acc[j];
     }
   }
-  // biases: sums of the dZ rows over the samples
-  for (int r = threadIdx.x; r < 3 * kMlpHid + kMlpOut; r += 128) {
-    const __bf16* src = r < 3 * kMlpHid ? sdZ[r / kMlpHid] + (r % kMlpHid) * kTS
-                                        : sdZ4 + (r - 3 * kMlpHid) * kTS;
+  // biases: sums of the dZ rows over the samples, in order
+  if (const int r = threadIdx.x; r < 3 * kMlpHid + kMlpOut) {
+    const __bf16* src = r < 3 * kMlpHid ? sdZ[r / kMlpHid] + (r % kMlpHid) * kTSP
+                                        : sdZ4 + (r - 3 * kMlpHid) * kTSP;
     float acc = 0.0f;
-    for (int c = 0; c < kTS; ++c) acc += (float)src[c];
+#pragma unroll
+    for (int c = 0; c < kTS; c += 8) {
+      const bf16x8 q = *reinterpret_cast<const bf16x8*>(src + c);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc += (float)q[j];
+    }
     const int ob = r < kMlpHid       ? kOb1 + r
                    : r < 2 * kMlpHid ? kOb2 + r - kMlpHid
                    : r < 3 * kMlpHid ? kOb3 + r - 2 * kMlpHid
@@ -782,16 +852,47 @@ __global__ void __launch_bounds__(128) k_mlp_grad(const bf16x8* __restrict__ pk,
 // Sums the workgroup partials in workgroup order; with `update`, an Adam step
 // with the bias corrections bc1 = 1/(1 - b1^t), bc2 = 1/(1 - b2^t) of step t
 // (from the launcher, in FP64: 1 - b2^t evaluated in FP32 would lose about
-// 2^-24 / (1 - b2^t) of its relative accuracy to cancellation).  Slot kMlpNparam is the batch's summed
-// squared error, reported as the mean loss.
-__global__ void k_mlp_adam(float* __restrict__ th, float* __restrict__ m1, float* __restrict__ m2,
-                           const float* __restrict__ partial, int nwg, float bc1, float bc2, float lr,
-                           float b1, float b2, float eps, int update, float* __restrict__ grad_out,
-                           float* __restrict__ loss_out, int batch) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > kMlpNparam) return;
+// 2^-24 / (1 - b2^t) of its relative accuracy to cancellation), and with pk the
+// new parameters stored in the packed operands too.  Slot kMlpNparam is the
+// batch's summed squared error, reported as the mean loss.
+//
+// 64 parameters per workgroup: its four wavefronts load 64 partials at a time,
+// 16 each in flight together, and the first one sums them from LDS in order.
+// (One thread per parameter walking the partials took 17.0 us at 64 of them,
+// a load latency per few partials on 36 CUs, and the packing a launch of
+// 4.5 us more; now 4.0 us with it.)
+constexpr int kAdamP = 64, kAdamK = 64;
+__global__ void __launch_bounds__(256) k_mlp_adam(float* __restrict__ th, float* __restrict__ m1,
+                                                  float* __restrict__ m2, const float* __restrict__ partial, int nwg,
+                                                  float bc1, float bc2, float lr, float b1, float b2, float eps,
+                                                  int update, float* __restrict__ grad_out,
+                                                  float* __restrict__ loss_out, int batch, __bf16* __restrict__ pk) {
+  __shared__ float part[kAdamK][kAdamP];
+  const int pl = threadIdx.x & 63, kg = threadIdx.x >> 6;
+  const int p = blockIdx.x * kAdamP + pl;
   float g = 0.0f;
-  for (int k = 0; k < nwg; ++k) g += partial[(size_t)k * kPartialStride + p];
+  for (int k0 = 0; k0 < nwg; k0 += kAdamK) {
+    float v[kAdamK / 4];
+#pragma unroll
+    for (int i = 0; i < kAdamK / 4; ++i) {
+      const int k = k0 + kg * (kAdamK / 4) + i;
+      v[i] = k < nwg && p <= kMlpNparam ? partial[(size_t)k * kPartialStride + p] : 0.0f;
+    }
+    if (k0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAdamK / 4; ++i) part[kg * (kAdamK / 4) + i][pl] = v[i];
+    __syncthreads();
+    if (kg == 0) {
+      const int m = min(kAdamK, nwg - k0);
+      if (m == kAdamK) {
+#pragma unroll
+        for (int k = 0; k < kAdamK; ++k) g += part[k][pl];
+      } else {
+        for (int k = 0; k < m; ++k) g += part[k][pl];
+      }
+    }
+  }
+  if (kg != 0 || p > kMlpNparam) return;
   if (p == kMlpNparam) {
     if (loss_out) *loss_out = g / (float)(kMlpOut * batch);
     return;
@@ -804,7 +905,9 @@ __global__ void k_mlp_adam(float* __restrict__ th, float* __restrict__ m1, float
   m2[p] = v;
   const float ah = a * bc1;
   const float vh = v * bc2;
-  th[p] -= lr * ah / (sqrtf(vh) + eps);
+  const float w = th[p] - lr * ah / (sqrtf(vh) + eps);
+  th[p] = w;
+  if (pk) pack_param(pk, p, w);
 }
 
 // Forward over n rows, 64 per wavefront.  raw = 1: X and Y are model values
@@ -842,8 +945,9 @@ void launch_mlp_gelu_table(hipStream_t s, float2* tab) {
   hca_launch(k_mlp_gelu_table, dim3((kGeluN + 1 + 255) / 256), dim3(256), 0, s, tab);
 }
 
-void launch_mlp_pack(hipStream_t s, const float* theta, bf16x8* packed) {
-  hca_launch(k_mlp_pack, dim3((kPackAll + 255) / 256), dim3(256), 0, s, theta, packed);
+void launch_mlp_pack(hipStream_t s, const float* theta, bf16x8* packed, float2* tab) {
+  const int n = kPackAll + (tab ? kGeluN + 1 : 0);
+  hca_launch(k_mlp_pack, dim3((n + 255) / 256), dim3(256), 0, s, theta, packed, tab);
 }
 
 template <typename T>
@@ -896,24 +1000,21 @@ void launch_mlp_init(hipStream_t s, uint64_t seed, float* theta) {
   hca_launch(k_mlp_init, dim3((kMlpNparam + 255) / 256), dim3(256), 0, s, seed, theta);
 }
 
-void launch_mlp_sample(hipStream_t s, uint64_t seed, long long t, long long n, int batch, int* idx) {
-  hca_launch(k_mlp_sample, dim3((batch + 255) / 256), dim3(256), 0, s, seed, t, n, batch, idx);
-}
-
 void launch_mlp_grad(hipStream_t s, const bf16x8* pk, const float* th, const float2* tab,
-                     const float* Xs, const float* Ys, const int* idx, int batch, long long nrows,
-                     float* partial) {
-  hca_launch(k_mlp_grad, dim3(batch / kTS), dim3(128), 0, s, pk, th, tab, Xs, Ys, idx, batch,
+                     const float* Xs, const float* Ys, const int* idx, uint64_t seed, long long t, int batch,
+                     long long nrows, float* partial) {
+  hca_launch(k_mlp_grad, dim3(batch / kTS), dim3(256), 0, s, pk, th, tab, Xs, Ys, idx, seed, t, batch,
                      nrows, partial);
 }
 
 void launch_mlp_adam(hipStream_t s, float* th, float* m1, float* m2, const float* partial, int nwg,
                      int t, float lr, float b1, float b2, float eps, int update, float* grad_out,
-                     float* loss_out, int batch) {
+                     float* loss_out, int batch, bf16x8* pk) {
   const float bc1 = (float)(1.0 / (1.0 - std::pow((double)b1, (double)t)));
   const float bc2 = (float)(1.0 / (1.0 - std::pow((double)b2, (double)t)));
-  hca_launch(k_mlp_adam, dim3((kMlpNparam + 1 + 255) / 256), dim3(256), 0, s, th, m1, m2,
-                     partial, nwg, bc1, bc2, lr, b1, b2, eps, update, grad_out, loss_out, batch);
+  hca_launch(k_mlp_adam, dim3((kMlpNparam + kAdamP) / kAdamP), dim3(256), 0, s, th, m1, m2,
+                     partial, nwg, bc1, bc2, lr, b1, b2, eps, update, grad_out, loss_out, batch,
+                     reinterpret_cast<__bf16*>(pk));
 }
 
 void launch_mlp_eval(hipStream_t s, const bf16x8* pk, const float* th, const float2* tab,

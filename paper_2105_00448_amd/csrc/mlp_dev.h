@@ -68,7 +68,8 @@ struct MlpDev {
 };
 
 // Launchers (k_mlp.hip).
-void launch_mlp_pack(hipStream_t s, const float* theta, bf16x8* packed);
+// Packed operands of theta; with tab, the GELU table in the same launch.
+void launch_mlp_pack(hipStream_t s, const float* theta, bf16x8* packed, float2* tab = nullptr);
 void launch_mlp_gelu_table(hipStream_t s, float2* tab);
 // The network's update for every occupied voxel; the voxels that fall back
 // are listed in `fb` (per flat work item, as CaList lists cells) and then
@@ -98,13 +99,14 @@ int mlp_moments_blocks(long long n);
 void launch_mlp_standardize(hipStream_t s, const float* X, const float* Y, long long n,
                             const float* stats, float* Xs, float* Ys);
 void launch_mlp_init(hipStream_t s, uint64_t seed, float* theta);
-void launch_mlp_sample(hipStream_t s, uint64_t seed, long long t, long long n, int batch, int* idx);
+// Gradient partials of the rows idx[0 .. batch), or without idx of the rows
+// that (seed, t) draws.
 void launch_mlp_grad(hipStream_t s, const bf16x8* pk, const float* th, const float2* tab,
-                     const float* Xs, const float* Ys, const int* idx, int batch, long long nrows,
-                     float* partial);
+                     const float* Xs, const float* Ys, const int* idx, uint64_t seed, long long t, int batch,
+                     long long nrows, float* partial);
 void launch_mlp_adam(hipStream_t s, float* th, float* m1, float* m2, const float* partial, int nwg,
                      int t, float lr, float b1, float b2, float eps, int update,
-                     float* grad_out, float* loss_out, int batch);
+                     float* grad_out, float* loss_out, int batch, bf16x8* pk = nullptr);
 void launch_mlp_eval(hipStream_t s, const bf16x8* pk, const float* th, const float2* tab,
                      const float* stats, const float* X, long long n, int raw, float* Y);
 

@@ -24,7 +24,6 @@ struct hca_mlp_trainer {
   bf16x8* packed = nullptr;
   float2* gelu_tab = nullptr;           // kGeluN + 1
   float* partial = nullptr;             // kMaxBatch / 64 workgroups
-  int* idx = nullptr;                   // kMaxBatch
   float* losses = nullptr;              // device, grows with n_steps
   int losses_cap = 0;
   float* loss1 = nullptr;               // device scalar
@@ -57,7 +56,7 @@ hipError_t talloc(T** p, size_t count) {
 
 void tfree(hca_mlp_trainer* t) {
   void* bufs[] = {t->Xs, t->Ys, t->stats, t->theta, t->m1, t->m2, (void*)t->packed, t->gelu_tab,
-                  t->partial, t->idx, t->losses, t->loss1};
+                  t->partial, t->losses, t->loss1};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
   if (t->own_stream && t->stream) (void)hipStreamDestroy(t->stream);
@@ -104,7 +103,7 @@ hca_status hca_mlp_trainer_create(hca_mlp_trainer** out, const float* X, const f
       talloc(&t->m1, kMlpNparam) != hipSuccess || talloc(&t->m2, kMlpNparam) != hipSuccess ||
       talloc(&t->packed, kPackAll) != hipSuccess || talloc(&t->gelu_tab, kGeluN + 1) != hipSuccess ||
       talloc(&t->partial, (size_t)(kMaxBatch / 64) * kPartialStride) != hipSuccess ||
-      talloc(&t->idx, kMaxBatch) != hipSuccess || talloc(&t->loss1, 1) != hipSuccess ||
+      talloc(&t->loss1, 1) != hipSuccess ||
       talloc(&part, (size_t)nblk * (kMlpIn + kMlpOut) * 4) != hipSuccess) {
     if (part) (void)hipFree(part);
     return bail(HCA_E_NOMEM);
@@ -181,7 +180,7 @@ hca_status hca_mlp_gradient(hca_mlp_trainer* t, const int32_t* idx, int batch, f
   if (!t || !idx || !grad) return HCA_E_INVALID;
   if (batch < 64 || batch > kMaxBatch || batch % 64) return tfail(t, HCA_E_RANGE, "batch size");
   launch_mlp_pack(t->stream, t->theta, t->packed);
-  launch_mlp_grad(t->stream, t->packed, t->theta, t->gelu_tab, t->Xs, t->Ys, idx, batch, t->n, t->partial);
+  launch_mlp_grad(t->stream, t->packed, t->theta, t->gelu_tab, t->Xs, t->Ys, idx, 0, 0, batch, t->n, t->partial);
   launch_mlp_adam(t->stream, t->theta, t->m1, t->m2, t->partial, batch / 64, 1, 0.f, 0.9f, 0.999f,
                   1e-8f, 0, grad, t->loss1, batch);
   TCHK(t, hipGetLastError());
@@ -203,13 +202,15 @@ hca_status hca_mlp_train(hca_mlp_trainer* t, int n_steps, int batch, float lr, f
     TCHK(t, talloc(&t->losses, (size_t)n_steps));
     t->losses_cap = n_steps;
   }
+  // two launches a step: the gradient of the minibatch it draws, then the
+  // Adam step, which stores the new parameters in the packed operands too
+  launch_mlp_pack(t->stream, t->theta, t->packed);
   for (int k = 0; k < n_steps; ++k) {
     const long long step = t->t + 1;
-    launch_mlp_sample(t->stream, t->seed, step, t->n, batch, t->idx);
-    launch_mlp_pack(t->stream, t->theta, t->packed);
-    launch_mlp_grad(t->stream, t->packed, t->theta, t->gelu_tab, t->Xs, t->Ys, t->idx, batch, t->n, t->partial);
+    launch_mlp_grad(t->stream, t->packed, t->theta, t->gelu_tab, t->Xs, t->Ys, nullptr, t->seed, step, batch, t->n,
+                    t->partial);
     launch_mlp_adam(t->stream, t->theta, t->m1, t->m2, t->partial, batch / 64, (int)step, lr, 0.9f,
-                    0.999f, 1e-8f, 1, nullptr, t->losses + k, batch);
+                    0.999f, 1e-8f, 1, nullptr, t->losses + k, batch, t->packed);
     t->t = step;
   }
   TCHK(t, hipGetLastError());

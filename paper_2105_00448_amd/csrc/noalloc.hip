@@ -64,9 +64,8 @@ extern "C" hca_status hca_mlp_gradient_noalloc(const float* theta, const float* 
   float* partial = reinterpret_cast<float*>(base + kOffPart);
   hipStream_t s = static_cast<hipStream_t>(stream);
   // every scratch region the later kernels read is written first in this call
-  launch_mlp_gelu_table(s, tab);
-  launch_mlp_pack(s, theta, packed);
-  launch_mlp_grad(s, packed, theta, tab, Xs, Ys, idx, batch, n_rows, partial);
+  launch_mlp_pack(s, theta, packed, tab);
+  launch_mlp_grad(s, packed, theta, tab, Xs, Ys, idx, 0, 0, batch, n_rows, partial);
   // update = 0: the parameters and moments are neither read nor written
   launch_mlp_adam(s, const_cast<float*>(theta), nullptr, nullptr, partial, batch / 64, 1, 0.f, 0.9f,
                   0.999f, 1e-8f, 0, grad, loss, batch);
