@@ -301,7 +301,8 @@ void launch_guess_projection(hipStream_t s, const Work& w, const T* c, const T* 
 constexpr int kMaxLevels = 16;
 constexpr int kCoarseThreads = 1024;
 constexpr int kCoarseMaxCellsPerThread = 8;
-// LDS floats per cell of a coarse-solve level: two iterates, r, D^-1, gx, gy, gz
+// Floats of a coarse-solve level's cell that level kc is chosen by: two iterates, r, D^-1, gx, gy, gz
+// (all in LDS after level kc; two of level kc's, the others in registers)
 constexpr int kCoarseLdsPerCell = 7;
 
 // One replicate at one multigrid level.  Level k cell I covers fine cells
@@ -339,17 +340,16 @@ struct MgCoarseRep {
   int nlev;                 // LDS levels (kc .. kc+nlev-1), the last has one cell
   int kc;
   int n0[3];
-  int dims[kMaxLevels][3];
-  // LDS: the system's precomputed block (pre_len floats, as in coarse_pre),
-  // then each level's (ua, ub, r) block at pre_len + lds_off[j]
-  int lds_off[kMaxLevels];
+  int dims[3];              // of level kc
+  int rest;                 // cells of the levels after kc
+  int alike;                // all cells of level kc have the same extents, and so the couplings g
+  float g[3];
+  float a;
   long long off_kc;         // replicate offset in the level-kc arrays
-  long long pre_off;        // this system's block in MgBufs::coarse_pre (a multiple of 4)
-  int pre_lev[kMaxLevels];  // level j's [D^-1 | gx | gy | gz] within the block
-  int pre_len;              // floats in the block (a multiple of 4)
+  long long pre_off;        // this system's block in MgBufs::coarse_pre: [gz | gy | gx | D^-1] of
+                            // level kc, then of each level after it (offsets multiples of 4)
   const float* r_kc;        // this system's level-kc r and u (level arrays + off_kc)
   float* u_kc;
-  float a;
 };
 
 struct MgBufs {
@@ -358,6 +358,8 @@ struct MgBufs {
   const MgCoarseRep* coarse;
   float* coarse_pre;        // per solve: couplings and D^-1 of the coarse-solve levels
   int coarse_lds_bytes;
+  int coarse_cells;         // most cells that a system's level kc has
+  int coarse_flat;          // every lattice has one plane
   float w_a, w_b;            // Jacobi weights: pre-sweeps (w_a, w_b), post-sweeps (w_b, w_a)
   float w0[3];              // level 0: pre-sweeps (w0[0], w0[1], w0[2]), post-sweeps reversed
   int fused;                // fused smoothing passes (k_mg_prefused, k_mg_postfused) on every level
@@ -369,8 +371,8 @@ struct MgBufs {
 
 // Allow the fused passes their dynamic LDS (above 64 KiB).
 hipError_t mg_set_fused_lds();
-// Allow the coarse-solve kernels `bytes` of dynamic LDS (above 64 KiB).
-hipError_t mg_set_coarse_lds(int bytes);
+// Allow the coarse-solve kernels of level kc's most cells `bytes` of dynamic LDS (above 64 KiB).
+hipError_t mg_set_coarse_lds(int cells, int flat, int bytes);
 template <typename T>
 void launch_mg_prepare(hipStream_t s, const Work& w, const MgBufs& mg, const T* c);
 // One V-cycle on the residual sb.r, result in sb.z; finishes the flexible-CG

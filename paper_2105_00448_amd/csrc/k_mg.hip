@@ -1338,352 +1338,457 @@ __global__ void __launch_bounds__(kRzBlock) k_mg_rz32(MgLevel L0, const double* 
 
 // ---- coarse levels: one workgroup per system, in LDS --------------------------
 
+// A level of a system's coarse solve: dims (those of level kc halved j times,
+// rounded up) and the cells of the levels kc+1 .. before it, by which its
+// blocks lie in LDS and in the precomputed block.
 struct CoarseLevel {
-  Geo<false> G;
-  int n;
-  float rnx, rny;   // 1/nx, 1/ny (coordinates without integer division)
-  // LDS: two Jacobi iterates and the residual, [ua | ub | r]; D^-1 and the
-  // couplings to the +x/+y/+z neighbour (0 at the edge), [D^-1 | gx | gy | gz],
-  // the level's part of the system's precomputed block copied into LDS.
-  float *ua, *ub, *r, *dinv, *gx, *gy, *gz;
+  int nx, ny, nz, n, plane, before;
 };
 
-// Level j of a system's coarse solve (LDS pointers and geometry).
-__device__ inline CoarseLevel coarse_level(const MgCoarseRep& cr, float* lds, int j, float a) {
+__device__ inline CoarseLevel coarse_level(const MgCoarseRep& cr, int j, int before) {
   CoarseLevel L;
-  L.G.nx = cr.dims[j][0];
-  L.G.ny = cr.dims[j][1];
-  L.G.nz = cr.dims[j][2];
-  L.G.k = cr.kc + j;
-  L.G.n0x = cr.n0[0];
-  L.G.n0y = cr.n0[1];
-  L.G.n0z = cr.n0[2];
-  L.G.a = a;
-  L.n = L.G.nx * L.G.ny * L.G.nz;
-  L.rnx = 1.f / (float)L.G.nx;
-  L.rny = 1.f / (float)L.G.ny;
-  L.ua = lds + cr.pre_len + cr.lds_off[j];
-  L.ub = L.ua + L.n;
-  L.r = L.ub + L.n;
-  L.dinv = lds + cr.pre_lev[j];
-  L.gx = L.dinv + L.n;
-  L.gy = L.gx + L.n;
-  L.gz = L.gy + L.n;
+  const int up = (1 << j) - 1;
+  L.nx = (cr.dims[0] + up) >> j;
+  L.ny = (cr.dims[1] + up) >> j;
+  L.nz = (cr.dims[2] + up) >> j;
+  L.plane = L.nx * L.ny;
+  L.n = L.plane * L.nz;
+  L.before = before;
   return L;
 }
 
 // Coordinates of cell t (t < 2^13): the float quotient (t + 1/2) / nx is at
-// least 1/(2 nx) from an integer and its rounding error far below that; the
-// fix-ups only guard the argument.
+// least 1/(2 nx) from an integer and its error below 2^-21 of it, far less.
 __device__ inline void cell_xyz(const CoarseLevel& L, int t, int& x, int& y, int& z) {
-  int q = (int)(((float)t + 0.5f) * L.rnx);
-  x = t - q * L.G.nx;
-  if (x < 0) {
-    --q;
-    x += L.G.nx;
-  } else if (x >= L.G.nx) {
-    ++q;
-    x -= L.G.nx;
-  }
-  z = (int)(((float)q + 0.5f) * L.rny);
-  y = q - z * L.G.ny;
-  if (y < 0) {
-    --z;
-    y += L.G.ny;
-  } else if (y >= L.G.ny) {
-    ++z;
-    y -= L.G.ny;
-  }
+  const int q = (int)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)L.nx));
+  x = t - __mul24(q, L.nx);
+  z = (int)(((float)q + 0.5f) * __builtin_amdgcn_rcpf((float)L.ny));
+  y = q - __mul24(z, L.ny);
 }
 
-// Neighbours of cell t in LDS, branch-free: indices clamped to t where a
-// face is missing and the coupling of a missing face 0, so all reads of a
-// stencil are issued together instead of one per taken branch.  The stored
-// +x/+y/+z couplings are already 0 at the upper edges.
-struct CoarseNb {
-  int xm, xp, ym, yp, zm, zp;   // neighbour indices (t where absent)
-  float fxm, fym, fzm;          // 1 where the lower neighbour exists, else 0
+// One cell of a level as its thread holds it: D^-1, the residual and the
+// couplings to the neighbours -x, +x, -y, +y, -z, +z (0 at a missing face).
+struct CoarseCell {
+  float d, r, g[6];
 };
 
-__device__ inline CoarseNb coarse_nb(const CoarseLevel& L, int t, int x, int y, int z) {
-  const int nx = L.G.nx, plane = nx * L.G.ny;
-  CoarseNb b;
-  b.xm = x > 0 ? t - 1 : t;
-  b.xp = x + 1 < nx ? t + 1 : t;
-  b.ym = y > 0 ? t - nx : t;
-  b.yp = y + 1 < L.G.ny ? t + nx : t;
-  b.zm = z > 0 ? t - plane : t;
-  b.zp = z + 1 < L.G.nz ? t + plane : t;
-  b.fxm = x > 0 ? 1.f : 0.f;
-  b.fym = y > 0 ? 1.f : 0.f;
-  b.fzm = z > 0 ? 1.f : 0.f;
-  return b;
-}
-
-// sum_J g_IJ V(J) over the existing neighbours, in the order -x, +x, -y, +y, -z, +z
-template <typename VF>
-__device__ inline float lds_nbsum_f(const CoarseLevel& L, const CoarseNb& b, int t, VF V) {
-  const float gxm = b.fxm * L.gx[b.xm], gym = b.fym * L.gy[b.ym], gzm = b.fzm * L.gz[b.zm];
-  float s = gxm * V(b.xm);
-  s += L.gx[t] * V(b.xp);
-  s += gym * V(b.ym);
-  s += L.gy[t] * V(b.yp);
-  s += gzm * V(b.zm);
-  s += L.gz[t] * V(b.zp);
+// sum_J g_IJ v(J) over the neighbours of cell t, in the order -x, +x, -y, +y,
+// -z, +z (FLAT: a level of one plane).  No coordinates and no bounds: a missing
+// face has the coupling 0, and v lies in LDS between finite numbers, a
+// neighbour's place being at most a level's cells away.
+template <bool FLAT>
+__device__ inline float coarse_nbsum(const CoarseLevel& L, const CoarseCell& c, const float* v, int t) {
+  const float* w = v + t;
+  float s = c.g[0] * w[-1];
+  s += c.g[1] * w[1];
+  s += c.g[2] * w[-L.nx];
+  s += c.g[3] * w[L.nx];
+  if (!FLAT) {
+    s += c.g[4] * w[-L.plane];
+    s += c.g[5] * w[L.plane];
+  }
   return s;
 }
 
-__device__ inline float lds_nbsum(const CoarseLevel& L, const float* v, int t, int x, int y, int z) {
-  const CoarseNb b = coarse_nb(L, t, x, y, z);
-  return lds_nbsum_f(L, b, t, [&](int j) { return v[j]; });
-}
-
-// The cells of a level dealt to the workgroup's threads: t = thread + m * block.
-#define FOR_MY_CELLS(L, t) for (int t = (int)threadIdx.x; t < (L).n; t += kCoarseThreads)
-
-// One phase over the n cells of a level: value(t) of the cells a thread
-// holds is formed first (their LDS reads in flight together; tail slots repeat
-// cell n-1), then store(t, value) for the cells that exist; batches of four
-// cells per thread.  A phase reads no array it stores to, other than a cell's
-// own entry.
-template <int M, typename VF, typename SF>
-__device__ inline void coarse_phase_m(int base, int n, VF value, SF store) {
-  float v[M];
-#pragma unroll
-  for (int m = 0; m < M; ++m) v[m] = value(min(base + (int)threadIdx.x + m * kCoarseThreads, n - 1));
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int t = base + (int)threadIdx.x + m * kCoarseThreads;
-    if (t < n) store(t, v[m]);
+// D^-1 and the couplings of cell t from a level's block [gz | gy | gx | D^-1]
+// (couplings to +x, +y, +z, 0 at the upper edges; those of the cells before
+// t are the ones to its lower neighbours: 0 again at the lower edges, where
+// they are an upper edge's of the row, the plane or the array before).
+template <bool FLAT>
+__device__ inline void coarse_cell(const CoarseLevel& L, const float* blk, int t, CoarseCell& c) {
+  const float *gz = blk + t, *gy = gz + L.n, *gx = gy + L.n;
+  c.d = gx[L.n];
+  c.g[0] = gx[-1];
+  c.g[1] = gx[0];
+  c.g[2] = gy[-L.nx];
+  c.g[3] = gy[0];
+  if (!FLAT) {
+    const float gzm = blk[max(t - L.plane, 0)];
+    c.g[4] = t >= L.plane ? gzm : 0.f;
+    c.g[5] = gz[0];
   }
 }
 
-template <typename VF, typename SF>
-__device__ inline void coarse_phase(int n, VF value, SF store) {
-  if (n <= kCoarseThreads) {
-    if ((int)threadIdx.x < n) store((int)threadIdx.x, value((int)threadIdx.x));
-  } else if (n <= 2 * kCoarseThreads) {
-    coarse_phase_m<2>(0, n, value, store);
+// The couplings of cell (x, y, z) of a level whose cells are all alike: g along each axis.
+template <bool FLAT>
+__device__ inline void coarse_alike(const CoarseLevel& L, const float (&g)[3], int x, int y, int z, CoarseCell& c) {
+  c.g[0] = x > 0 ? g[0] : 0.f;
+  c.g[1] = x + 1 < L.nx ? g[0] : 0.f;
+  c.g[2] = y > 0 ? g[1] : 0.f;
+  c.g[3] = y + 1 < L.ny ? g[1] : 0.f;
+  if (!FLAT) {
+    c.g[4] = z > 0 ? g[2] : 0.f;
+    c.g[5] = z + 1 < L.nz ? g[2] : 0.f;
+  }
+}
+
+// u2 of the two sweeps from zero (dr: D^-1 r of the level)
+template <bool FLAT>
+__device__ inline float coarse_pre(const CoarseLevel& L, const CoarseCell& c, const float* dr, int t, float wa,
+                                   float wb) {
+  const float s = coarse_nbsum<FLAT>(L, c, dr, t);
+  const float u1 = wa * c.d * c.r;
+  return (1.f - wb) * u1 + wb * c.d * (c.r + wa * s);
+}
+
+// (r - A u) of cell t, its own u given
+template <bool FLAT>
+__device__ inline float coarse_res(const CoarseLevel& L, const CoarseCell& c, const float* v, int t, float u) {
+  return c.r - u / c.d + coarse_nbsum<FLAT>(L, c, v, t);
+}
+
+// One weighted-Jacobi sweep of cell t, its own u given
+template <bool FLAT>
+__device__ inline float coarse_sweep(const CoarseLevel& L, const CoarseCell& c, const float* v, int t, float u,
+                                     float omega) {
+  return (1.f - omega) * u + omega * c.d * (c.r + coarse_nbsum<FLAT>(L, c, v, t));
+}
+
+// Cell t of level C: the sum of its up to eight children's residuals (level
+// L), every one read (for an absent one some number nearby) and weighted 0 or
+// 1, in the order x, then y, then z.
+template <bool FLAT>
+__device__ inline float coarse_sum8(const CoarseLevel& L, const CoarseLevel& C, const float* res, int t) {
+  int X, Y, Z;
+  cell_xyz(C, t, X, Y, Z);
+  const float* f = res + 2 * (X + __mul24(L.nx, Y) + __mul24(L.plane, Z));
+  const bool x1 = 2 * X + 1 < L.nx, y1 = 2 * Y + 1 < L.ny, z1 = 2 * Z + 1 < L.nz;
+  float s = f[0];
+  s += x1 ? f[1] : 0.f;
+  s += y1 ? f[L.nx] : 0.f;
+  s += (x1 & y1) ? f[L.nx + 1] : 0.f;
+  if (!FLAT) {
+    const float* h = f + L.plane;
+    s += z1 ? h[0] : 0.f;
+    s += (x1 & z1) ? h[1] : 0.f;
+    s += (y1 & z1) ? h[L.nx] : 0.f;
+    s += (x1 & y1 & z1) ? h[L.nx + 1] : 0.f;
+  }
+  return s;
+}
+
+// Where cell (x, y, z) of level L takes its correction from in level C: the
+// cell with the larger weight and the distances to the other one of each axis (0:
+// none, weight 0 instead of 1/4).
+struct CoarseParent {
+  int at, dx, dy, dz;
+};
+
+// lin_axis's coarse cells of fine cell i, without branches: the nearer one and the distance to the other
+__device__ inline void coarse_axis(int i, int nf, int nc, int& I, int& d) {
+  I = i >> 1;
+  d = (i & 1) ? 1 : -1;
+  const int J = I + d;
+  const bool none = (J < 0) | (J >= nc) | (((nf & 1) != 0) & ((I == nc - 1) | (J == nc - 1)));
+  d = none ? 0 : d;
+}
+
+template <bool FLAT>
+__device__ inline CoarseParent coarse_parent(const CoarseLevel& L, const CoarseLevel& C, int x, int y, int z) {
+  int Ix, Iy, Iz = 0, dx, dy, dz = 0;
+  coarse_axis(x, L.nx, C.nx, Ix, dx);
+  coarse_axis(y, L.ny, C.ny, Iy, dy);
+  if (!FLAT) coarse_axis(z, L.nz, C.nz, Iz, dz);
+  return {Ix + __mul24(Iy, C.nx) + __mul24(Iz, C.plane), dx, __mul24(dy, C.nx), __mul24(dz, C.plane)};
+}
+
+// u3 = u2 + P e of a cell (e: level C's correction): x first along each
+// coarse row, then y, then z (the global levels' order).
+template <bool FLAT>
+__device__ inline float coarse_prolong(const CoarseParent& P, const float* e, float u) {
+  const float wx = P.dx ? 0.25f : 0.f, wy = P.dy ? 0.25f : 0.f, wz = P.dz ? 0.25f : 0.f;
+  const float* e0 = e + P.at;
+  const float r00 = (1.f - wx) * e0[0] + wx * e0[P.dx];
+  const float r01 = (1.f - wx) * e0[P.dy] + wx * e0[P.dy + P.dx];
+  const float p0 = (1.f - wy) * r00 + wy * r01;
+  if (FLAT) return u + p0;
+  const float* e1 = e0 + P.dz;
+  const float r10 = (1.f - wx) * e1[0] + wx * e1[P.dx];
+  const float r11 = (1.f - wx) * e1[P.dy] + wx * e1[P.dy + P.dx];
+  const float p1 = (1.f - wy) * r10 + wy * r11;
+  return u + ((1.f - wz) * p0 + wz * p1);
+}
+
+// Between two phases: of the workgroup, or of one wavefront (whose LDS
+// accesses are made in their order; only the compiler has to keep it).
+template <bool WAVE>
+__device__ inline void coarse_sync() {
+  if (WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   } else {
-    for (int b = 0; b < n; b += 4 * kCoarseThreads) coarse_phase_m<4>(b, n, value, store);
+    __syncthreads();
   }
-}
-
-// One weighted-Jacobi sweep, src -> dst (different buffers, so no barrier
-// between reading and writing).
-__device__ inline void lds_sweep(const CoarseLevel& L, const float* src, float* dst, float omega) {
-  coarse_phase(
-      L.n,
-      [&](int t) {
-        int x, y, z;
-        cell_xyz(L, t, x, y, z);
-        return (1.f - omega) * src[t] + omega * L.dinv[t] * (L.r[t] + lds_nbsum(L, src, t, x, y, z));
-      },
-      [&](int t, float v) { dst[t] = v; });
 }
 
 // Once per solve, one workgroup per system: coarse reaction terms of the
-// one-workgroup levels (summed from level kc, kept in the LDS ua slots), then
-// each level's couplings and D^-1 into the system's precomputed block.
+// one-workgroup levels (summed from level kc, in LDS), then each level's
+// couplings and D^-1 into the system's precomputed block.  Each face's coupling
+// (a division) is formed once and shared through LDS.
 __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse_prep(const MgCoarseRep* coarse,
                                                                    const float* const* lev_c,
                                                                    float* __restrict__ pre) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   const int rep = blockIdx.x;
   const MgCoarseRep& cr = coarse[rep];
-  const float a = cr.a;
   const int J = cr.nlev;
+  const int n0 = cr.dims[0] * cr.dims[1] * cr.dims[2];
+  // LDS: the couplings [gz | gy | gx] of the level at work (3 n0), then the
+  // reaction terms of level kc and of the others
+  float* sc = lds + 3 * n0;
   {
-    const CoarseLevel L = coarse_level(cr, lds, 0, a);
     const float* gc = lev_c[cr.kc] + cr.off_kc;
-    for (int t = threadIdx.x; t < L.n; t += kCoarseThreads) L.ua[t] = gc[t];
+    for (int t = threadIdx.x; t < n0; t += kCoarseThreads) sc[t] = gc[t];
   }
-  __syncthreads();
-  for (int j = 1; j < J; ++j) {
-    const CoarseLevel F = coarse_level(cr, lds, j - 1, a);
-    const CoarseLevel C = coarse_level(cr, lds, j, a);
-    for (int t = threadIdx.x; t < C.n; t += kCoarseThreads) {
-      int X, Y, Z;
-      cell_xyz(C, t, X, Y, Z);
-      float s = 0.f;
-      for (int dz = 0; dz < 2 && 2 * Z + dz < F.G.nz; ++dz)
-        for (int dy = 0; dy < 2 && 2 * Y + dy < F.G.ny; ++dy)
-          for (int dx = 0; dx < 2 && 2 * X + dx < F.G.nx; ++dx)
-            s += F.ua[(2 * X + dx) + F.G.nx * ((2 * Y + dy) + F.G.ny * (2 * Z + dz))];
-      C.ua[t] = s;
-    }
-    __syncthreads();
-  }
-  for (int j = 0; j < J; ++j) {
-    const CoarseLevel L = coarse_level(cr, lds, j, a);
-    float* g = pre + cr.pre_off + cr.pre_lev[j];
+  for (int j = 0, before = 0; j < J; ++j) {
+    const CoarseLevel L = coarse_level(cr, j, before);
+    const float* c = sc + (j ? n0 + before : 0);
+    float* g = pre + cr.pre_off + 4 * (j ? n0 + before : 0);
+    Geo<false> G;
+    G.nx = L.nx;
+    G.ny = L.ny;
+    G.nz = L.nz;
+    G.k = cr.kc + j;
+    G.n0x = cr.n0[0];
+    G.n0y = cr.n0[1];
+    G.n0z = cr.n0[2];
+    G.a = cr.a;
+    float *lz = lds, *ly = lds + L.n, *lx = ly + L.n;
     for (int t = threadIdx.x; t < L.n; t += kCoarseThreads) {
       int x, y, z;
       cell_xyz(L, t, x, y, z);
-      g[t] = 1.f / (L.ua[t] + L.G.gsum(x, y, z));
-      g[L.n + t] = x + 1 < L.G.nx ? L.G.gx(x, y, z) : 0.f;
-      g[2 * L.n + t] = y + 1 < L.G.ny ? L.G.gy(x, y, z) : 0.f;
-      g[3 * L.n + t] = z + 1 < L.G.nz ? L.G.gz(x, y, z) : 0.f;
+      g[t] = lz[t] = z + 1 < L.nz ? G.gz(x, y, z) : 0.f;
+      g[L.n + t] = ly[t] = y + 1 < L.ny ? G.gy(x, y, z) : 0.f;
+      g[2 * L.n + t] = lx[t] = x + 1 < L.nx ? G.gx(x, y, z) : 0.f;
     }
+    __syncthreads();
+    for (int t = threadIdx.x; t < L.n; t += kCoarseThreads) {
+      // the order of Geo::gsum; a missing face adds 0
+      float s = t >= 1 ? lx[t - 1] : 0.f;
+      s += lx[t];
+      s += t >= L.nx ? ly[t - L.nx] : 0.f;
+      s += ly[t];
+      s += t >= L.plane ? lz[t - L.plane] : 0.f;
+      s += lz[t];
+      g[3 * L.n + t] = 1.f / (c[t] + s);
+    }
+    before = j ? before + L.n : 0;
+    if (j + 1 < J) {
+      const CoarseLevel C = coarse_level(cr, j + 1, before);
+      for (int t = threadIdx.x; t < C.n; t += kCoarseThreads)
+        sc[n0 + before + t] = coarse_sum8<false>(L, C, c, t);
+      __syncthreads();
+    }
+  }
+}
+
+// LDS of a coarse solve: the blocks [gz | gy | gx | D^-1] of the levels after
+// kc (`rest` cells); level kc's [ub] and [ua], each between two guards of
+// zeros; [ua | ub | r] of the others, zeros at first.
+struct CoarseLds {
+  float *blocks, *levels;
+  __device__ inline float* blk(const CoarseLevel& L) const { return blocks + 4 * L.before; }
+  __device__ inline float* ua(const CoarseLevel& L) const { return levels + 3 * L.before; }
+};
+
+// The levels from L (its index j) down while one has more than `stop` cells,
+// each with at most K cells a thread; on entry level L's residual (r) and
+// D^-1 r (ub) are in LDS, on return those of the level that L has become.
+template <bool FLAT, bool WAVE, int K>
+__device__ inline void coarse_down(const MgCoarseRep& cr, const CoarseLds& M, CoarseLevel& L, int& j, int stop,
+                                   float wa, float wb) {
+  constexpr int T = WAVE ? 64 : kCoarseThreads;
+  while (L.n > stop) {
+    const CoarseLevel C = coarse_level(cr, j + 1, L.before + L.n);
+    float *ua = M.ua(L), *ub = ua + L.n, *r = ub + L.n;
+    CoarseCell c[K];
+    float u[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int t = (int)threadIdx.x + k * T;
+      if (t >= L.n) break;
+      coarse_cell<FLAT>(L, M.blk(L), t, c[k]);
+      c[k].r = r[t];
+      u[k] = coarse_pre<FLAT>(L, c[k], ub, t, wa, wb);
+      ua[t] = u[k];
+    }
+    coarse_sync<WAVE>();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int t = (int)threadIdx.x + k * T;
+      if (t >= L.n) break;
+      ub[t] = coarse_res<FLAT>(L, c[k], ua, t, u[k]);
+    }
+    coarse_sync<WAVE>();
+    for (int t = threadIdx.x; t < C.n; t += T) {
+      const float s = coarse_sum8<FLAT>(L, C, ub, t);
+      M.ua(C)[2 * C.n + t] = s;
+      M.ua(C)[C.n + t] = M.blk(C)[3 * C.n + t] * s;
+    }
+    coarse_sync<WAVE>();
+    L = C;
+    ++j;
+  }
+}
+
+// From level j's corrected u (C's ua) up to level `to`'s.
+template <bool FLAT, bool WAVE, int K>
+__device__ inline void coarse_up(const MgCoarseRep& cr, const CoarseLds& M, CoarseLevel& C, int& j, int to,
+                                 float wa, float wb) {
+  constexpr int T = WAVE ? 64 : kCoarseThreads;
+  while (j > to) {
+    --j;
+    CoarseLevel L = coarse_level(cr, j, 0);
+    L.before = C.before - L.n;
+    float *ua = M.ua(L), *ub = ua + L.n, *r = ub + L.n;
+    CoarseCell c[K];
+    float u[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int t = (int)threadIdx.x + k * T;
+      if (t >= L.n) break;
+      coarse_cell<FLAT>(L, M.blk(L), t, c[k]);
+      c[k].r = r[t];
+      int x, y, z;
+      cell_xyz(L, t, x, y, z);
+      u[k] = coarse_prolong<FLAT>(coarse_parent<FLAT>(L, C, x, y, z), M.ua(C), ua[t]);
+      ua[t] = u[k];
+    }
+    coarse_sync<WAVE>();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int t = (int)threadIdx.x + k * T;
+      if (t >= L.n) break;
+      u[k] = coarse_sweep<FLAT>(L, c[k], ua, t, u[k], wb);
+      ub[t] = u[k];
+    }
+    coarse_sync<WAVE>();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int t = (int)threadIdx.x + k * T;
+      if (t >= L.n) break;
+      ua[t] = coarse_sweep<FLAT>(L, c[k], ub, t, u[k], wa);
+    }
+    coarse_sync<WAVE>();
+    C = L;
   }
 }
 
 // The V-cycle of levels kc.. of one system in LDS (one workgroup per system),
 // the same cycle as the multi-workgroup levels: two sweeps, restriction by
-// aggregate sums, ..., the one-cell level solved exactly, cell-centred linear
-// prolongation, two sweeps; the correction of level kc is written to that
-// level's global u.  Every level's final iterate is left in its ua.
-__global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const MgCoarseRep* coarse,
+// aggregate sums, ..., the one-cell level solved exactly (no faces: u = D^-1 r),
+// cell-centred linear prolongation, two sweeps; the correction of level kc is
+// written to that level's global u.
+//
+// A serial chain of phases on one CU: its time is LDS accesses, latencies and
+// barriers, not bandwidth.  So level kc's cells (M a thread) keep D^-1, r, u and
+// their couplings in registers from the first phase to the last and share
+// only what neighbours read; every cell's residual is formed once, by its own
+// thread, and then summed; neighbours are read without coordinates or
+// bounds, between zeros; and levels of at most 64 cells are the first
+// wavefront's alone, without barriers.  Measured, the mean of a solve's calls:
+// 50 x 50 cells 10.0 us and 16^3 cells 10.9 us, against 22 and 19 us where every
+// phase took each cell's coordinates, couplings and D^-1 from LDS again.
+template <int M, bool FLAT>
+__global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const MgCoarseRep* __restrict__ coarse,
                                                               float wa, float wb,
-                                                              const float* const* lev_r,
-                                                              float* const* lev_u,
                                                               const float* __restrict__ pre,
-                                                              const SolveScal* ss) {
+                                                              const SolveScal* __restrict__ ss) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  __shared__ MgCoarseRep s_cr;
   const int rep = blockIdx.x;
-  // the system's descriptor into LDS (every later phase reads it there
-  // instead of from global memory)
-  {
-    static_assert(sizeof(MgCoarseRep) % 4 == 0 && sizeof(MgCoarseRep) / 4 <= kCoarseThreads, "descriptor copy");
-    constexpr int nw = (int)(sizeof(MgCoarseRep) / 4);
-    const int* src = reinterpret_cast<const int*>(coarse + rep);
-    const int v = (int)threadIdx.x < nw ? src[threadIdx.x] : 0;
-    if (ss[rep].done) return;
-    if ((int)threadIdx.x < nw) reinterpret_cast<int*>(&s_cr)[threadIdx.x] = v;
-  }
-  __syncthreads();
-  const MgCoarseRep& cr = s_cr;
-  const float a = cr.a;
-  const int J = cr.nlev;
-  // r of level kc, and the precomputed block (D^-1 and the couplings of every
-  // level), into LDS; each pass issues all of its global loads before its
-  // first LDS store (one memory latency per pass, not one per element)
-  {
-    const CoarseLevel L = coarse_level(cr, lds, 0, a);
-    const float* gr = cr.r_kc;
-    float rv[kCoarseMaxCellsPerThread];
-#pragma unroll
-    for (int m = 0; m < kCoarseMaxCellsPerThread; ++m) {
-      const int t = (int)threadIdx.x + m * kCoarseThreads;
-      rv[m] = gr[min(t, L.n - 1)];
-    }
-    const float4* src = reinterpret_cast<const float4*>(pre + cr.pre_off);
-    float4* dst = reinterpret_cast<float4*>(lds);
-    const int n4 = cr.pre_len >> 2;
-    constexpr int kBatch = 6;
-    for (int b = 0; b < n4; b += kBatch * kCoarseThreads) {
-      float4 v[kBatch];
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        const int i = b + (int)threadIdx.x + k * kCoarseThreads;
-        v[k] = src[min(i, n4 - 1)];
-      }
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        const int i = b + (int)threadIdx.x + k * kCoarseThreads;
-        if (i < n4) dst[i] = v[k];
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < kCoarseMaxCellsPerThread; ++m) {
-      const int t = (int)threadIdx.x + m * kCoarseThreads;
-      if (t < L.n) L.r[t] = rv[m];
-    }
-  }
-  __syncthreads();
-  // down: u2 of the two sweeps from zero (u1 = w D^-1 r, formed on the fly at
-  // the neighbours), then the aggregate sums of r - A u2
-  for (int j = 0; j + 1 < J; ++j) {
-    const CoarseLevel L = coarse_level(cr, lds, j, a);
-    coarse_phase(
-        L.n,
-        [&](int t) {
-          int x, y, z;
-          cell_xyz(L, t, x, y, z);
-          const CoarseNb nb = coarse_nb(L, t, x, y, z);
-          const float s = lds_nbsum_f(L, nb, t, [&](int i) { return L.dinv[i] * L.r[i]; });
-          const float d = L.dinv[t], rr = L.r[t];
-          const float u1 = wa * d * rr;
-          return (1.f - wb) * u1 + wb * d * (rr + wa * s);
-        },
-        [&](int t, float v) { L.ua[t] = v; });
-    __syncthreads();
-    const CoarseLevel C = coarse_level(cr, lds, j + 1, a);
-    FOR_MY_CELLS(C, t) {
-      int X, Y, Z;
-      cell_xyz(C, t, X, Y, Z);
-      // the up to eight children, every one evaluated (absent ones at a
-      // clamped index) and weighted 0 or 1, in the order x, then y, then z
-      float s = 0.f;
-#pragma unroll
-      for (int dz = 0; dz < 2; ++dz)
-#pragma unroll
-        for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-          for (int dx = 0; dx < 2; ++dx) {
-            const bool in = 2 * X + dx < L.G.nx && 2 * Y + dy < L.G.ny && 2 * Z + dz < L.G.nz;
-            const int x = in ? 2 * X + dx : 2 * X, y = in ? 2 * Y + dy : 2 * Y, z = in ? 2 * Z + dz : 2 * Z;
-            const int f = x + L.G.nx * (y + L.G.ny * z);
-            const float res = L.r[f] - L.ua[f] / L.dinv[f] + lds_nbsum(L, L.ua, f, x, y, z);
-            s += in ? res : 0.f;
-          }
-      C.r[t] = s;
-    }
-    __syncthreads();
-  }
-  // coarsest: one cell and no faces, so u = r / c exactly; larger: sweeps
-  {
-    const CoarseLevel L = coarse_level(cr, lds, J - 1, a);
-    FOR_MY_CELLS(L, t) L.ua[t] = L.dinv[t] * L.r[t];
-    __syncthreads();
-    if (L.n > 1) {
-      for (int it = 0; it < 15; ++it) {
-        lds_sweep(L, L.ua, L.ub, wa);
-        __syncthreads();
-        lds_sweep(L, L.ub, L.ua, wb);
-        __syncthreads();
-      }
-    }
-  }
-  // up: u3 = u2 + P e, two sweeps (the last of level kc straight to global)
-  for (int j = J - 2; j >= 0; --j) {
-    const CoarseLevel L = coarse_level(cr, lds, j, a);
-    const CoarseLevel C = coarse_level(cr, lds, j + 1, a);
-    coarse_phase(L.n, [&](int t) {
-      int x, y, z;
-      cell_xyz(L, t, x, y, z);
-      int Ix, Jx, Iy, Jy, Iz, Jz;
-      float wx, wy, wz;
-      lin_axis(x, L.G.nx, C.G.nx, Ix, Jx, wx);
-      lin_axis(y, L.G.ny, C.G.ny, Iy, Jy, wy);
-      lin_axis(z, L.G.nz, C.G.nz, Iz, Jz, wz);
-      const int sy = C.G.nx, sz = C.G.nx * C.G.ny;
-      const float* e = C.ua;
-      // x first along each coarse row, then y, then z (the global levels' order)
-      const float r00 = (1.f - wx) * e[Iz * sz + Iy * sy + Ix] + wx * e[Iz * sz + Iy * sy + Jx];
-      const float r01 = (1.f - wx) * e[Iz * sz + Jy * sy + Ix] + wx * e[Iz * sz + Jy * sy + Jx];
-      const float r10 = (1.f - wx) * e[Jz * sz + Iy * sy + Ix] + wx * e[Jz * sz + Iy * sy + Jx];
-      const float r11 = (1.f - wx) * e[Jz * sz + Jy * sy + Ix] + wx * e[Jz * sz + Jy * sy + Jx];
-      const float p0 = (1.f - wy) * r00 + wy * r01;
-      const float p1 = (1.f - wy) * r10 + wy * r11;
-      return L.ua[t] + ((1.f - wz) * p0 + wz * p1);
-    }, [&](int t, float v) { L.ua[t] = v; });
-    __syncthreads();
-    lds_sweep(L, L.ua, L.ub, wb);
-    __syncthreads();
-    if (j > 0) {
-      lds_sweep(L, L.ub, L.ua, wa);
-      __syncthreads();
-    } else {
-      lds_sweep(L, L.ub, cr.u_kc, wa);
-    }
-  }
+  const MgCoarseRep cr = coarse[rep];
+  const int done = ss[rep].done;
+  asm volatile("" ::"s"(cr.r_kc), "s"(cr.pre_off), "s"(cr.rest));   // with `done`, not after it
+  if (done) return;
+  const int J = cr.nlev, tid = (int)threadIdx.x;
+  const CoarseLevel L0 = coarse_level(cr, 0, 0);
+  const float* blk = pre + cr.pre_off;
+  const float* gr = cr.r_kc;
+  float* gu = cr.u_kc;
   if (J == 1) {   // level kc is the one-cell level itself
-    const CoarseLevel L = coarse_level(cr, lds, 0, a);
-    float* gu = cr.u_kc;
-    FOR_MY_CELLS(L, t) gu[t] = L.ua[t];
+    if (tid == 0) gu[0] = blk[3] * gr[0];
+    return;
   }
+  CoarseLevel L = coarse_level(cr, 1, 0);
+  const int rest = cr.rest, guard = FLAT ? L0.nx : L0.plane;
+  float *ub = lds + 4 * rest + guard, *ua = ub + L0.n + guard;
+  const CoarseLds S{lds, ua + L0.n + guard};
+  CoarseCell c[M];
+  CoarseParent P[M];
+  float u[M];
+  // Slots beyond the level's cells repeat its last one, stores included.  The
+  // thread's number is hidden from the compiler in each phase, which otherwise
+  // keeps every index of every cell in registers from the first to the last.
+#define FOR_MY_CELLS(BODY)                                    \
+  {                                                           \
+    int t0 = tid;                                             \
+    asm volatile("" : "+v"(t0));                              \
+    _Pragma("unroll") for (int m = 0; m < M; ++m) {           \
+      const int t = min(t0 + m * kCoarseThreads, L0.n - 1);   \
+      BODY;                                                   \
+    }                                                         \
+  }
+  FOR_MY_CELLS(c[m].r = gr[t])
+  if (cr.alike) {
+    FOR_MY_CELLS(c[m].d = blk[3 * L0.n + t])
+  } else {
+    FOR_MY_CELLS(coarse_cell<FLAT>(L0, blk, t, c[m]))
+  }
+  {
+    const float4* src = reinterpret_cast<const float4*>(blk + 4 * L0.n);
+    float4* dst = reinterpret_cast<float4*>(lds);
+    for (int i = tid; i < rest; i += kCoarseThreads) dst[i] = src[i];
+  }
+  for (int i = tid; i < guard; i += kCoarseThreads) ub[i - guard] = ub[L0.n + i] = ua[L0.n + i] = 0.f;
+  for (int i = tid; i < 3 * rest; i += kCoarseThreads) S.levels[i] = 0.f;
+  // (the loads under way) what else a cell needs from its coordinates
+  FOR_MY_CELLS({
+    int x; int y; int z;
+    cell_xyz(L0, t, x, y, z);
+    if (cr.alike) coarse_alike<FLAT>(L0, cr.g, x, y, z, c[m]);
+    P[m] = coarse_parent<FLAT>(L0, L, x, y, z);
+    asm volatile("" : "+v"(P[m].at), "+v"(P[m].dx), "+v"(P[m].dy), "+v"(P[m].dz));
+  })
+  FOR_MY_CELLS(ub[t] = c[m].d * c[m].r)
+  __syncthreads();
+  FOR_MY_CELLS(u[m] = coarse_pre<FLAT>(L0, c[m], ub, t, wa, wb))
+  FOR_MY_CELLS(ua[t] = u[m])
+  __syncthreads();
+  float v[M];
+  FOR_MY_CELLS(v[m] = coarse_res<FLAT>(L0, c[m], ua, t, u[m]))
+  FOR_MY_CELLS(ub[t] = v[m])
+  __syncthreads();
+  for (int t = tid; t < L.n; t += kCoarseThreads) {
+    const float s = coarse_sum8<FLAT>(L0, L, ub, t);
+    S.ua(L)[2 * L.n + t] = s;
+    S.ua(L)[L.n + t] = S.blk(L)[3 * L.n + t] * s;
+  }
+  __syncthreads();
+  int j = 1;
+  const bool two = L.n > kCoarseThreads;   // at most twice as many: more do not fit LDS
+  if (two) coarse_down<FLAT, false, 2>(cr, S, L, j, kCoarseThreads, wa, wb);
+  const int j2 = j;
+  coarse_down<FLAT, false, 1>(cr, S, L, j, 64, wa, wb);
+  const int jw = j;
+  if (tid < 64) {
+    CoarseLevel W = L;
+    coarse_down<FLAT, true, 1>(cr, S, W, j, 1, wa, wb);
+    if (tid == 0) S.ua(W)[0] = S.ua(W)[1];   // u = D^-1 r
+    coarse_sync<true>();
+    coarse_up<FLAT, true, 1>(cr, S, W, j, jw, wa, wb);
+  }
+  __syncthreads();
+  j = jw;
+  coarse_up<FLAT, false, 1>(cr, S, L, j, j2, wa, wb);
+  if (two) coarse_up<FLAT, false, 2>(cr, S, L, j, 1, wa, wb);
+  FOR_MY_CELLS(ua[t] = u[m] = coarse_prolong<FLAT>(P[m], S.ua(L), u[m]))
+  __syncthreads();
+  FOR_MY_CELLS(u[m] = coarse_sweep<FLAT>(L0, c[m], ua, t, u[m], wb))
+  FOR_MY_CELLS(ub[t] = u[m])
+  __syncthreads();
+  FOR_MY_CELLS(u[m] = coarse_sweep<FLAT>(L0, c[m], ub, t, u[m], wa))
+  FOR_MY_CELLS(gu[t] = u[m])
+#undef FOR_MY_CELLS
 }
 
 // ---- launchers -------------------------------------------------------------
@@ -1709,8 +1814,26 @@ hipError_t mg_set_fused_lds() {
   return e;
 }
 
-hipError_t mg_set_coarse_lds(int bytes) {
-  hipError_t e = hipFuncSetAttribute((const void*)k_mg_coarse, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+// The coarse solve for level kc of up to `cells` cells: the fewest cells a
+// thread that take them (the slots of a thread are worked on together, those
+// beyond a system's cells for nothing).  More than 5814 cells do not fit a
+// level's 28 bytes a cell in 160 KiB.  flat: every system has one plane.
+typedef void (*CoarseKernel)(const MgCoarseRep*, float, float, const float*, const SolveScal*);
+template <bool FLAT>
+static CoarseKernel coarse_kernel_of(int cells) {
+  if (cells <= kCoarseThreads) return k_mg_coarse<1, FLAT>;
+  if (cells <= 2 * kCoarseThreads) return k_mg_coarse<2, FLAT>;
+  if (cells <= 3 * kCoarseThreads) return k_mg_coarse<3, FLAT>;
+  if (cells <= 4 * kCoarseThreads) return k_mg_coarse<4, FLAT>;
+  return k_mg_coarse<6, FLAT>;
+}
+static CoarseKernel coarse_kernel(int cells, int flat) {
+  return flat ? coarse_kernel_of<true>(cells) : coarse_kernel_of<false>(cells);
+}
+
+hipError_t mg_set_coarse_lds(int cells, int flat, int bytes) {
+  hipError_t e =
+      hipFuncSetAttribute((const void*)coarse_kernel(cells, flat), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute((const void*)k_mg_coarse_prep, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
@@ -1794,8 +1917,8 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
     H(MG_DOWN, 0);
   }
   H(MG_COARSE, 1);
-  hca_launch(k_mg_coarse, dim3(w.nreps), dim3(kCoarseThreads), mg.coarse_lds_bytes, s, mg.coarse, wa, wb,
-             (const float* const*)mg.lev_r, (float* const*)mg.lev_u, (const float*)mg.coarse_pre, ss);
+  hca_launch(coarse_kernel(mg.coarse_cells, mg.coarse_flat), dim3(w.nreps), dim3(kCoarseThreads), mg.coarse_lds_bytes, s,
+             (const MgCoarseRep*)mg.coarse, wa, wb, (const float*)mg.coarse_pre, ss);
   H(MG_COARSE, 0);
   if (mg.nlev_glob > 1) {
     H(MG_UP, 1);

@@ -1730,6 +1730,7 @@ hca_status build_mg(Ctx* c) {
   // coarse-solve descriptors
   std::vector<MgCoarseRep> cr(S);
   size_t lds_max = 0;
+  int ncells_max = 0, flat = 1;
   long long pre_total = 0;
   for (int s = 0; s < S; ++s) {
     const int r = s % R;
@@ -1738,29 +1739,42 @@ hca_status build_mg(Ctx* c) {
     d.kc = kcr[r];
     d.nlev = (int)dims[r].size() - kcr[r];
     d.a = (float)sd[s].a;
-    for (int i = 0; i < 3; ++i) d.n0[i] = dims[r][0][i];
-    int o = 0, g = 0;
-    for (int j = 0; j < d.nlev; ++j) {
-      for (int i = 0; i < 3; ++i) d.dims[j][i] = dims[r][kcr[r] + j][i];
-      d.lds_off[j] = o;
-      d.pre_lev[j] = g;
-      o += (kCoarseLdsPerCell - 4) * d.dims[j][0] * d.dims[j][1] * d.dims[j][2];
-      g += 4 * d.dims[j][0] * d.dims[j][1] * d.dims[j][2];
+    // extents of level kc's cells along each axis (alike where the lattice's
+    // edge is a whole number of them), and the couplings between such cells
+    int e[3];
+    d.alike = 1;
+    for (int i = 0; i < 3; ++i) {
+      d.n0[i] = dims[r][0][i];
+      d.dims[i] = dims[r][kcr[r]][i];
+      e[i] = std::min(1 << d.kc, d.n0[i]);
+      if (d.n0[i] % e[i]) d.alike = 0;
     }
-    d.pre_len = g;
-    lds_max = std::max(lds_max, (size_t)(o + g) * sizeof(float));
+    for (int i = 0; i < 3; ++i)
+      d.g[i] = 2.f * d.a * (float)(e[(i + 1) % 3] * e[(i + 2) % 3]) / (float)(e[i] + e[i]);
+    const int n = d.dims[0] * d.dims[1] * d.dims[2];
+    for (int j = 1; j < d.nlev; ++j) d.rest += (int)cells(dims[r][kcr[r] + j]);
+    ncells_max = std::max(ncells_max, n);
+    if (d.dims[2] > 1) flat = 0;
+    // k_mg_coarse: two iterates of level kc between three guards of a plane, and
+    // all of the others; k_mg_coarse_prep: c and the couplings of level kc, c of
+    // the others, and as far as the places of an absent child reach beyond
+    const int plane = d.dims[0] * d.dims[1];
+    lds_max = std::max(lds_max, sizeof(float) * (size_t)std::max(2 * n + 3 * plane + 7 * d.rest,
+                                                                 4 * n + d.rest + plane + d.dims[0] + 1));
     d.off_kc = mreps[kcr[r]][s].off;
     d.r_kc = pr[kcr[r]] + d.off_kc;
     d.u_kc = pu[kcr[r]] + d.off_kc;
     d.pre_off = pre_total;
-    pre_total += g;
+    pre_total += 4 * (long long)(n + d.rest);
   }
   MgCoarseRep* dcr = nullptr;
   hca_status st = mg_upload(c, &dcr, cr);
   if (st != HCA_OK) return st;
   mg.coarse = dcr;
   mg.coarse_lds_bytes = (int)lds_max;
-  if (lds_max > 65536) HIPCHK(c, mg_set_coarse_lds((int)lds_max));
+  mg.coarse_cells = ncells_max;
+  mg.coarse_flat = flat;
+  if (lds_max > 65536) HIPCHK(c, mg_set_coarse_lds(ncells_max, flat, (int)lds_max));
   if (c->prm.mg_fuse) HIPCHK(c, mg_set_fused_lds());
   if ((st = mg_alloc(c, &mg.coarse_pre, (size_t)pre_total)) != HCA_OK) return st;
   if (c->ncol && c->prm.mg_fuse && (st = mg_alloc(c, &mg.colsum, (size_t)c->ncol)) != HCA_OK) return st;
@@ -1771,6 +1785,8 @@ hca_status build_mg(Ctx* c) {
   c->mg1.coarse = mg.coarse;
   c->mg1.coarse_pre = mg.coarse_pre;
   c->mg1.coarse_lds_bytes = mg.coarse_lds_bytes;
+  c->mg1.coarse_cells = mg.coarse_cells;
+  c->mg1.coarse_flat = mg.coarse_flat;
   c->mg1.lev_c = mg.lev_c;
   c->mg1.lev_r = mg.lev_r;
   c->mg1.lev_u = mg.lev_u;
