@@ -41,7 +41,7 @@ inline void hca_launch(F kernel, dim3 grid, dim3 block, unsigned shmem, hipStrea
 constexpr int kBlock = 256;        // threads per workgroup (all kernels but the two below)
 constexpr int kF3Block = 768;      // most threads of the multigrid's fused smoothing passes
 constexpr int kRzBlock = 512;      // precision 32: columns of an r.z partial
-constexpr int kF3Group = 8;        // planes per r.z partial of level 0's post-smoothing
+constexpr int kF3Group = 8;        // most planes per r.z partial of level 0's post-smoothing
 constexpr int kStripPad = 4;       // values that a strip load may reach past its array's ends
 constexpr int kFlatChunk = 1024;   // voxels per flat work item (4 per thread)
 constexpr int kMaxFlatBlocksPerRep = 2048;
@@ -317,6 +317,7 @@ struct MgRep {
   int rtile_b0, rtile_nb;   // tiles of the cells this level receives by restriction
   int tx;
   int fe, frpw, fty;        // fused tiles: strips per row (halo strips included), rows per wavefront, output rows
+  int fgroup;               // level 0: planes per r.z partial (4 or 8)
   float a;                  // face coupling D/h^2 of the system's field
 };
 

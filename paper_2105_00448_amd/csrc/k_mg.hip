@@ -875,15 +875,21 @@ struct F3Geo<false> {
   }
 };
 
-// The marching of both passes over a tile [z0, z1): stage 0's planes in groups
-// of four, each plane's step specialised for the plane number mod 4.  From
-// the four planes below the tile (the lattice's first plane where there are
-// none: the planes below it are 0) to the S above it.  A stage's first planes
-// are computed from zeros instead of the planes that were left out; no plane
-// of the tile depends on them.
+// The first plane a tile [z0, z1) marches from: S below it (0 at least), where
+// S = 2 (z0 is even); S = 3's r.z groups want a multiple of four.
+template <int S>
+__device__ inline int f3_first_plane(int z0) {
+  return S == 2 ? max(z0 - 2, 0) : max(z0 - 4, 0) & ~3;
+}
+
+// The marching of both passes over a tile: stage 0's planes in groups
+// of four, each plane's step specialised for its number in the group.  From
+// f3_first_plane (the planes below the lattice are 0) to the S above the tile.
+// A stage's first planes are computed from zeros instead of the planes that
+// were left out; no plane of the tile depends on them.
 template <int S, typename STEP>
 __device__ inline void f3_march(int z0, int z1, bool active, STEP step) {
-  const int zf = max(z0 - 4, 0) & ~3;
+  const int zf = f3_first_plane<S>(z0);
   if (active) {
     for (int z = zf; z < z1 + S; z += 4) {
       step(z, std::integral_constant<int, 0>());
@@ -945,7 +951,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_prefused(MgLevel Lk, MgLevel
   // the extended tile's first cell in the plane that is loaded next (uniform,
   // and kept opaque to the compiler, which would otherwise carry one pointer
   // per array and unrolled plane), and the strip's byte offsets from it
-  long long at = m.off + t.x0 - 4 + (long long)m.nx * (t.y0 - S) + plane * (max(t.z0 - 4, 0) & ~3);
+  long long at = m.off + t.x0 - 4 + (long long)m.nx * (t.y0 - S) + plane * f3_first_plane<S>(t.z0);
   const unsigned vo = f.nv > 0 ? 4u * f.vo : kNoLane;
   const unsigned io = f.inner ? 4u * f.vo : kNoLane;
   const int sce = P32 && S == 3 ? ilogb(ss[t.rep].sc) : 0;
@@ -955,7 +961,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_prefused(MgLevel Lk, MgLevel
   const bool ragged = __ballot(f.nv > 0 && f.nv < 4) != 0;   // a strip of the wavefront straddles the lattice's end
   const bool lead = f.inner && ((f.y & 1) == 0), odd = f.inner && ((f.y & 1) != 0);
   float h[S][2][4];        // a stage's values at the two newest planes, by plane parity
-  float rh[4][4], dh[4][4];   // r, D^-1 by plane mod 4
+  float rh[4][4], dh[4][4];   // r, D^-1 by step mod 4
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -965,8 +971,9 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_prefused(MgLevel Lk, MgLevel
   }
   // operands of the next two planes, by plane parity
   f4 nr[2], nd[2];
+  const int zlim = min(nz, z1 + S);   // the tile depends on the planes below
   auto fetch = [&](int z, int q) {   // plane z, at `at`, into slot q
-    const bool in = z < nz;
+    const bool in = z < zlim;
     nr[q] = strip_load(strip_buf(r + at, in), vo);
     nd[q] = strip_load(strip_buf(Lk.dinv + at, in), vo);
   };
@@ -988,7 +995,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_prefused(MgLevel Lk, MgLevel
     }
   };
   {
-    const int zf = max(z0 - 4, 0) & ~3;
+    const int zf = f3_first_plane<S>(z0);
     fetch(zf, 0);
     at += plane;
     fetch(zf + 1, 1);
@@ -1092,7 +1099,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
   // the extended tile's first cell in the plane that is loaded next (uniform,
   // and kept opaque to the compiler, which would otherwise carry one pointer
   // per array and unrolled plane), and the strip's byte offsets from it
-  long long at = m.off + t.x0 - 4 + (long long)m.nx * (t.y0 - S) + plane * (max(t.z0 - 4, 0) & ~3);
+  long long at = m.off + t.x0 - 4 + (long long)m.nx * (t.y0 - S) + plane * f3_first_plane<S>(t.z0);
   const unsigned vo = f.nv > 0 ? 4u * f.vo : kNoLane;
   const unsigned io = f.inner ? 4u * f.vo : kNoLane;
   const int sce = P32 && S == 3 ? ilogb(sb.ss[t.rep].sc) : 0;
@@ -1149,7 +1156,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
     sE[q] = o;
   };
   float h[S][2][4];
-  f4 rh[4], dh[4];   // by plane mod 4; a plane's are loaded when the plane four below is done with
+  f4 rh[4], dh[4];   // by step mod 4; a plane's are loaded when the plane four below is done with
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -1159,10 +1166,11 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
   // cells for r.z, one plane ahead
   f4 nu[2];
   StripVal<ST> rq;
-  auto fetch_u = [&](int z, int q) { nu[q] = strip_load(strip_buf(Lk.u + at, z < nz), vo); };   // plane z is at `at`
+  const int zlim = min(nz, z1 + S);   // the tile depends on the planes below
+  auto fetch_u = [&](int z, int q) { nu[q] = strip_load(strip_buf(Lk.u + at, z < zlim), vo); };   // plane z is at `at`
   auto fetch_rd = [&](int z, int q) {   // plane z is one below `at`
-    rh[q] = strip_load(strip_buf(r + (at - plane), z < nz), vo);
-    dh[q] = strip_load(strip_buf(Lk.dinv + (at - plane), z < nz), vo);
+    rh[q] = strip_load(strip_buf(r + (at - plane), z < zlim), vo);
+    dh[q] = strip_load(strip_buf(Lk.dinv + (at - plane), z < zlim), vo);
   };
 #pragma unroll
   for (int k = 0; k < 4; ++k) rh[k] = dh[k] = 0.f;
@@ -1170,7 +1178,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
   if constexpr (ZOUT) rq.load(strip_buf(sb.r + at, false), ir);
   double rz = 0.0;
   double rzc[4] = {0.0, 0.0, 0.0, 0.0};   // precision 32: per column
-  const int zf = max(z0 - 4, 0) & ~3;
+  const int zf = f3_first_plane<S>(z0);
   const bool zrag = (nz & 1) != 0;
   // E of zf's own coarse plane and of the one below
   if (zf > 0) {
@@ -1190,14 +1198,15 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
   fetch_rd(zf, 0);
   fetch_u(zf + 1, 1);
   __syncthreads();
-  // r.z of the group of planes that ends with z: one partial per kF3Group
+  const int gmask = m.fgroup - 1;
+  // r.z of the group of planes that ends with z: one partial per gmask + 1
   // planes of a tile column, whatever the tile's depth, so that the sum does
   // not depend on how the batch's lattices are cut in z
   auto put_rz = [&](int z) {
     if (threadIdx.x == 0) {
       double tsum = 0.0;
       for (int k = 0; k < kF3Block / 64; ++k) tsum += sRz[k];
-      store_partials(sb.partial + (size_t)(t.part + (z - z0) / kF3Group) * 3, tsum * sb.ss[t.rep].isc, 0.0, 0.0);
+      store_partials(sb.partial + (size_t)(t.part + (z - z0) / (gmask + 1)) * 3, tsum * sb.ss[t.rep].isc, 0.0, 0.0);
     }
   };
   auto step = [&](int z, auto K) {
@@ -1273,12 +1282,12 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
           }
           if constexpr (ZOUT && !P32) {
             // zs is the last plane of a group in one step of four at most
-            if (s == S && ((k - S) & 3) == 3 && zs % kF3Group == kF3Group - 1 && zs >= z0 && zs < z1) {
+            if (s == S && ((k - S) & 3) == 3 && (zs & gmask) == gmask && zs >= z0 && zs < z1) {
               for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
               if ((threadIdx.x & 63) == 0) sRz[threadIdx.x >> 6] = rz;
               rz = 0.0;
             }
-            if (s == S && ((k - S) & 3) == 0 && zs % kF3Group == 0 && zs > z0 && zs < z1) put_rz(zs - 1);
+            if (s == S && ((k - S) & 3) == 0 && (zs & gmask) == 0 && zs > z0 && zs < z1) put_rz(zs - 1);
           }
         }
 #pragma unroll
@@ -1301,7 +1310,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
     }
   }
   if constexpr (ZOUT && !P32) {
-    if (z1 % kF3Group != 0) {   // the lattice's last, shorter group
+    if ((z1 & gmask) != 0) {   // the lattice's last, shorter group
       for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
       if ((threadIdx.x & 63) == 0) sRz[threadIdx.x >> 6] = rz;
       __syncthreads();

@@ -995,31 +995,43 @@ FusedShape fused_shape(int nx, int ny, int nz, int S) {
 
 // Planes that a fused tile of depth d marches through above the lattice's
 // bottom (k_mg.hip, f3_march).
-int fused_steps(int d, int S, bool bottom) { return (d + S + (bottom ? 0 : 4) + 3) & ~3; }
+int fused_steps(int d, int S, bool bottom) { return (d + S + (bottom ? 0 : S == 2 ? 2 : 4) + 3) & ~3; }
+
+// Planes per r.z partial of a lattice, and so the least depth of level 0's
+// tiles over it; a function of the lattice alone, like the order of the sums.
+// Lattices of up to 64^3 voxels leave the chip idle and take as long as their
+// tiles are deep: pre + post of level 0 at depths 8 / 4, three systems of 32^3
+// iterating, 27 / 21 us.
+int fused_group(int nx, int ny, int nz) { return (long long)nx * ny * nz <= 1LL << 18 ? 4 : kF3Group; }
 
 // Depth of a level's fused tiles, for the whole batch (HCA_FUSED_DEPTH
-// overrides; a multiple of kF3Group: the r.z partials, and so every result,
-// do not depend on it): the fewest microseconds by a model of the pass, the
-// wavefront steps of the batch dealt over 1024 SIMDs at g_fused_work each,
-// plus the longest tile's steps at g_fused_step each (the latency that a small
-// batch is bound by).  Measured, pre + post of level 0, all systems iterating,
-// at depths 8 / 16 / 24 / 32 / 48 / 64: one 128^3 lattice 91 / 72 / 86 / 99 /
-// 132 / 165 us (16 taken), 181 x 150 x 133 158 / 153 / 168 / 143 / 186 / 222 us
-// (16), the 64-replicate ensemble 1171 / 982 / 942 / 936 / 1322 / 1310 us (32).
+// overrides; a multiple of every lattice's group on level 0 and of 4 on the
+// others: the r.z partials, and so every result, do not depend on it): the
+// fewest microseconds by a model of the pass, the wavefront steps of the batch
+// dealt over 1024 SIMDs at `work` each, plus the longest tile's steps at
+// `step` each (the latency that a small batch is bound by).  Measured, pre +
+// post of level 0, all systems iterating, at depths 8 / 16 / 24 / 32 / 48 / 64:
+// one 128^3 lattice 91 / 72 / 86 / 99 / 132 / 165 us (16 taken), 181 x 150 x 133
+// 158 / 153 / 168 / 143 / 186 / 222 us (16), the 64-replicate ensemble 1171 / 982 /
+// 942 / 936 / 1322 / 1310 us (32).  Level 1 at depths 4 / 8 / 16 / 24: three systems of
+// 64^3 cells 21 / 27 / 38 / 49 us (4 taken), 59 x 52 x 46, five systems, 24 / 26 / 37 / 47 (4), the
+// ensemble 114 / 91 / 88 / 100 (8); level 2 of the ensemble 25 / 29 / 42 / 46 (4).
 int g_fused_depth = 0;
 // Precision 32: coarser levels smooth in fused passes from this many cells over
 // all systems (HCA_FUSE_MIN_CELLS).
 long long g_fuse_min_cells = 2LL << 20;
-double g_fused_work = 0.22, g_fused_step = 0.35;
 struct FusedLat {
   FusedShape f;
-  int nz;
+  int nz, least;   // least: of the tiles' depth
 };
 int fused_depth(const std::vector<FusedLat>& lats, int S) {
   if (g_fused_depth) return g_fused_depth;
-  int best = kF3Group;
+  const double work_us = S == 3 ? 0.22 : 0.25, step_us = S == 3 ? 0.35 : 0.45;
+  int least = 4, best = kF3Group;
+  for (const FusedLat& l : lats) least = std::max(least, l.least);
   double best_us = -1.0;
-  for (int d : {8, 16, 24, 32, 48, 64}) {
+  for (int d : {4, 8, 16, 24, 32, 48, 64}) {
+    if (d < least) continue;
     double work = 0.0;
     int longest = 0;
     for (const FusedLat& l : lats) {
@@ -1032,7 +1044,7 @@ int fused_depth(const std::vector<FusedLat>& lats, int S) {
       }
       work += steps * l.f.ntx * l.f.nty * l.f.waves;
     }
-    const double us = work * g_fused_work / 1024.0 + longest * g_fused_step;
+    const double us = work * work_us / 1024.0 + longest * step_us;
     if (best_us < 0.0 || us < best_us) {
       best_us = us;
       best = d;
@@ -1339,7 +1351,7 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
     std::vector<FusedLat> lats;
     for (int r = 0; r < R; ++r) {
       const RepHost& H = c->reps[r];
-      lats.insert(lats.end(), c->dp.nf, FusedLat{fused_shape(H.nx, H.ny, H.nz, 3), H.nz});
+      lats.insert(lats.end(), c->dp.nf, FusedLat{fused_shape(H.nx, H.ny, H.nz, 3), H.nz, fused_group(H.nx, H.ny, H.nz)});
     }
     const int fdepth = fused_depth(lats, 3);
     c->sys_n.clear();
@@ -1351,13 +1363,13 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
         const FusedShape& fs = lats[(size_t)r * c->dp.nf].f;
         const size_t first = ftiles.size();
         if (kPrecision == 64) {
-          const int groups = (H.nz + kF3Group - 1) / kF3Group;
+          const int group = lats[(size_t)r * c->dp.nf].least, groups = (H.nz + group - 1) / group;
           d.fpart_b0 = npart;
           d.fpart_nb = fs.ntx * fs.nty * groups;
           add_tiles(ftiles, f * R + r, H.nx, H.ny, H.nz, fs.tx, fdepth, fs.fty);
           for (size_t k = first; k < ftiles.size(); ++k) {
             Tile& t = ftiles[k];
-            t.part = npart + (t.y0 / fs.fty * fs.ntx + t.x0 / fs.tx) * groups + t.z0 / kF3Group;
+            t.part = npart + (t.y0 / fs.fty * fs.ntx + t.x0 / fs.tx) * groups + t.z0 / group;
           }
         } else {
           const int depth = rz32_depth(H);
@@ -1602,7 +1614,7 @@ hca_status build_mg(Ctx* c) {
     for (int s = 0; k >= 1 && s < S; ++s) {
       const int r = s % R;
       if (k < kcr[r])
-        lats.push_back(FusedLat{fused_shape(dims[r][k][0], dims[r][k][1], dims[r][k][2], 2), dims[r][k][2]});
+        lats.push_back(FusedLat{fused_shape(dims[r][k][0], dims[r][k][1], dims[r][k][2], 2), dims[r][k][2], 4});
     }
     const int fdepth = fused_depth(lats, 2);
     int fthreads = k == 0 ? c->fthreads : 64;
@@ -1640,6 +1652,7 @@ hca_status build_mg(Ctx* c) {
         m.fe = fs.fe;
         m.frpw = fs.frpw;
         m.fty = fs.fty;
+        m.fgroup = fused_group(m.nx, m.ny, m.nz);
         if (k == 0) {
           m.tx = sd[s].tx;
           m.off = sd[s].off;

@@ -58,3 +58,18 @@ def test_tile_depth_does_not_change_a_bit(monkeypatch):
         for a, b in zip(out[0], other):
             for k in a:
                 assert np.array_equal(a[k], b[k]), k
+
+
+def test_shallow_tiles_do_not_change_a_bit(monkeypatch):
+    """Lattices of up to 64^3 voxels: partials of four planes, tiles of four or
+    more on every level, alone or beside a larger lattice (partials of eight)."""
+    small = [replicate(s, 60 + i) for i, s in enumerate([(37, 30, 61), (16, 64, 64), (64, 64, 64), (3, 9, 20)])]
+    alone = [fields([r], mg_coarse_max=512)[0][0] for r in small]
+    batch = fields(small, mg_coarse_max=512)[0]
+    mixed = fields(small + [replicate((65, 64, 64), 70)], mg_coarse_max=512)[0]
+    monkeypatch.setenv("HCA_FUSED_DEPTH", "16")
+    deep = fields(small, mg_coarse_max=512)[0]
+    for i in range(len(small)):
+        for other in (batch[i], mixed[i], deep[i]):
+            for k in alone[i]:
+                assert np.array_equal(alone[i][k], other[k]), (i, k)
