@@ -127,6 +127,7 @@ struct SolveScal {
   double rzo;       // r_new . z_old (flexible CG)
   double rzn;       // r_new . z_new
   double pq;        // p.Ap
+  double qz;        // Ap.z (precision 64, multigrid)
   double alpha, beta;
   double rr0;       // ||r_0||^2 of this solve
   // The multigrid works in FP32 on r sc (r32 = r sc) and returns z sc: sc is a
@@ -242,6 +243,21 @@ void launch_init_cells(hipStream_t s, const Work& w, const DevParams& p, const u
 void launch_convert(hipStream_t s, const float* src, double* dst, long long n);
 void launch_convert(hipStream_t s, const double* src, float* dst, long long n);
 
+// The z of a solve's first iterations, kept (precision 64, multigrid): with
+// x = x_0 + sum_k alpha_k p_k and p_k = z_k + beta_k p_(k-1), the first n terms are
+// sum_j G_j z_j, G_j = alpha_j + beta_(j+1) G_(j+1), made once at the solve's end
+// from 4 bytes per iteration and voxel, where x += alpha p took 16 in every
+// apply.  Iterations beyond the first n keep that form, and their z the one
+// buffer sb.z32.  The z of iterations 0 and 1 lie in the memory of b, which
+// nothing reads once the start residual is formed.
+constexpr int kZRing = 4;
+struct CgRing {
+  int n;                 // iterations whose z is kept: 0, 2 or kZRing
+  float *z01, *z23;      // z of iterations 0, 1 and 2, 3, `stride` apart
+  long long stride;
+  double* hist;          // per system and kept iteration: alpha, beta, 1 / (the scale of z)
+};
+
 // solver (k_solver.hip)
 template <typename T>
 struct SolverBufsT {
@@ -255,7 +271,15 @@ struct SolverBufsT {
   unsigned* counter;          // per replicate
   SolveScal* ss;              // per replicate
   int* ndone;                 // replicates finished
+  CgRing ring;
 };
+
+// Where z of iteration `it` lies (the kept ones in their own buffers).
+template <typename T>
+__host__ __device__ inline float* cg_z(const SolverBufsT<T>& sb, int it) {
+  if (it >= sb.ring.n) return sb.z32;
+  return (it < 2 ? sb.ring.z01 : sb.ring.z23) + (it & 1) * sb.ring.stride;
+}
 // Systems whose field (s / nrep) is not in field_mask are marked finished.
 template <typename T>
 void launch_cg_start(hipStream_t s, const Work& w, double rtol, int maxit, const T* c, const T* b,
@@ -273,8 +297,9 @@ template <typename T>
 void launch_cg_r32(hipStream_t s, const Work& w, const SolverBufsT<T>& sb);
 // One iteration is launch_cg_apply (with the iteration's parity: the
 // direction p alternates between p0 and p1) then launch_cg_update.  The apply
-// also makes the previous iteration's x += alpha p (x: the solved field), so
-// a solve ends with launch_cg_finish for the last one.
+// also makes the previous iteration's x += alpha p (x: the solved field) where
+// that one's z is not kept, so a solve ends with launch_cg_finish for the kept
+// ones and the last.
 template <typename T>
 void launch_cg_apply(hipStream_t s, const Work& w, const T* c, T* x, const SolverBufsT<T>& sb, int parity);
 // The apply kernel alone (no reduce), for the tile autotuner.
@@ -390,7 +415,8 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
 // The last CG iteration's x += alpha p of a solve of every field (the systems
 // f * nrep + r of SolverBufsT, f < nf), left to the first kernel that reads
 // the fields after the solve: the ODE phase, which streams every voxel once
-// anyway and is bound by its arithmetic.  Kernels take it by a pointer to
+// anyway and is bound by its arithmetic (precision 32 alone; the FP64 kernels
+// leave it out).  Kernels take it by a pointer to
 // device memory (null: nothing left to make), read per run of voxels, so its
 // fields hold no registers over the kernel.
 template <typename T>

@@ -655,6 +655,7 @@ __global__ void __launch_bounds__(kBlock) k_mg_post2(MgLevel Lk, float omega, co
     double rz = 0.0;
     // level 0 reads the FP64 residual (for r.z): the cycle works on r sc
     const double sc = L0 ? sb.ss[t.rep].sc : 1.0, isc = L0 ? sb.ss[t.rep].isc : 1.0;
+    float* const zo = cg_z(sb, sb.ss[t.rep].it);
     {
       const OpU<RT> op{in, Lk.dinv, r};
       mg_plane(G, t, m.tx, m.off, lds, op,
@@ -662,7 +663,7 @@ __global__ void __launch_bounds__(kBlock) k_mg_post2(MgLevel Lk, float omega, co
                  const float rs = L0 ? (float)((double)c.r * sc) : (float)c.r;
                  const float u5 = (1.f - omega) * u4 + omega * c.dinv * (rs + s);
                  if (L0) {
-                   sb.z32[i] = u5;
+                   zo[i] = u5;
                    rz += (double)c.r * ((double)u5 * isc);
                  } else {
                    Lk.u[i] = u5;
@@ -1088,6 +1089,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
                                                                   // (by plane parity; its owner's alone)
   const Tile t = Lk.ftiles[blockIdx.x];
   if (t.rep < 0 || sb.ss[t.rep].done) return;
+  float* const zo = ZOUT ? cg_z(sb, sb.ss[t.rep].it) : out;
   const MgRep m = Lk.reps[t.rep];
   const MgRep mc = Lc.reps[t.rep];
   const F3Own f = f3_own(t, m, S);
@@ -1260,7 +1262,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
                                  F3_NB(i, u, lo, hi, ym, yp, h[s - 1][wb], nv), u[i]);
           if (s == S) {
             const bool mine = zs >= z0 && zs < z1;
-            strip_store(strip_buf((ZOUT ? sb.z32 : out) + (at - (S + 2) * plane), mine), io, v, f.nv, ragged);
+            strip_store(strip_buf(zo + (at - (S + 2) * plane), mine), io, v, f.nv, ragged);
             if constexpr (ZOUT) {
               // (lanes and planes that are not the tile's have r = 0 here)
               if (ragged) {

@@ -12,7 +12,7 @@ namespace hca {
 // fin: a deferred solve end, made per run before its listing (K aliases
 // fin.x, so K is not restrict-qualified).
 template <typename T>
-__global__ void __launch_bounds__(kBlock) k_ode(Work w, DevParams p, const uint8_t* __restrict__ L,
+__global__ void __launch_bounds__(kBlock, 4) k_ode(Work w, DevParams p, const uint8_t* __restrict__ L,
                                                 const T* K,
                                                 double* __restrict__ P,
                                                 double* __restrict__ Vc,

@@ -24,6 +24,8 @@
 // one iteration late, by the next apply, which reads the previous p anyway
 // (x moves once per iteration instead of x and p in the update); the last
 // iteration's update is made by a finishing pass after the solve.
+#include <type_traits>
+
 #include "dev_util.h"
 
 namespace hca {
@@ -72,9 +74,9 @@ constexpr int kPlaneMax = 400;
 // deeper rings hold more registers (fewer resident waves) and measured slower.
 constexpr int kStencilPrefetch = 1;
 
-// Marches the tile over [z0, z1) and calls f(i, deg, u_i, (A u)_i) for every
-// voxel of the tile inside the lattice, where u = op.value(op.load(j)) is the
-// operand (possibly formed on the fly from several arrays) and
+// Marches the tile over [z0, z1) and calls f(i, deg, u_i, (A u)_i, raw_i) for
+// every voxel of the tile inside the lattice, where u = op.value(op.load(j)) is the
+// operand (possibly formed on the fly from several arrays; raw_i its own) and
 // (A u)_i = (c_i + a deg) u_i - a sum_nb u_j.  Values the op needs at the
 // voxel itself only (op.load_ctr, prefetched with the plane like c) are
 // handed, with the voxel's raw operand, to op.at_center(i, raw_i, extra_i)
@@ -154,9 +156,11 @@ __device__ inline void plane_stencil(const TileCoord& tc, const T* __restrict__ 
   for (int d = 0; d < PD; ++d) ring[d] = Slot{op.zero(), op.zero(), 0.0, op.ctr_zero()};
   __syncthreads();   // the previous tile's readers are done with both buffers
   double um, cc;
+  Raw rc;   // of the voxel at hand
   {
     Slot s0{op.zero(), op.zero(), 0.0, op.ctr_zero()};
     load_slot(s0, z0);
+    rc = s0.ri;
     if (tc.valid) op.at_center(i, s0.ri, s0.e);
     um = (tc.valid && z0 > 0) ? (double)(T)op.value(op.load(i - plane)) : 0.0;
 #pragma unroll
@@ -174,9 +178,11 @@ __device__ inline void plane_stencil(const TileCoord& tc, const T* __restrict__ 
       if (z < z1) {   // uniform over the workgroup
         const bool zl = z > 0, zr = z + 1 < tc.nz;
         double cn = 0.0;
+        Raw rn = op.zero();
         if (zr) {   // plane z+1 into LDS; its slot then takes plane z+1+PD
           store_slot(ring[d], nxt);
           cn = ring[d].c;
+          rn = ring[d].ri;
           if (tc.valid && z + 1 < z1) op.at_center(i + plane, ring[d].ri, ring[d].e);
           const int zq = z + 1 + PD;
           if (zq <= z1 && zq < tc.nz) load_slot(ring[d], zq);
@@ -192,11 +198,12 @@ __device__ inline void plane_stencil(const TileCoord& tc, const T* __restrict__ 
         if (tc.valid) {
           const int deg = deg_xy + (int)zl + (int)zr;
           const double Au = (cc + a * deg) * uc - a * s;
-          f(i, deg, uc, Au);
+          f(i, deg, uc, Au, rc);
         }
         um = uc;
         uc = up;
         cc = cn;
+        rc = rn;
         T* t = cur;
         cur = nxt;
         nxt = t;
@@ -224,10 +231,13 @@ struct OpX {
   __device__ inline void at_center(long long, const Raw&, const Ctr&) const {}
 };
 
-// The voxel's own x comes with it (extra) when the previous iteration's
-// x += alpha p_old is due (every iteration but a solve's first; alpha the
-// previous iteration's), made as the voxel's plane enters LDS.
-template <bool JAC, typename T>
+// The forms of the apply's operand, one per kind of iteration so that no load
+// hangs on a condition of its own: a solve's first (p = z); one with no x to
+// update (the last iteration's z is kept, CgRing); one with: the voxel's own x
+// comes with it (extra) and the previous iteration's x += alpha p_old is made as
+// the voxel's plane enters LDS.
+enum ApplyForm { AP_FIRST, AP_KEPT, AP_X };
+template <bool JAC, typename T, ApplyForm FORM>
 struct OpP {
   struct Raw {
     double z, p;
@@ -242,12 +252,14 @@ struct OpP {
   double beta;
   double isc;   // multigrid: z = z32 / sc
   double alpha;
-  bool first;
   __device__ inline Raw zero() const { return Raw{0.0, 0.0}; }
   __device__ inline Ctr ctr_zero() const { return Ctr{0.0}; }
-  __device__ inline Ctr load_ctr(long long j) const { return Ctr{first ? 0.0 : (double)x[j]}; }
+  __device__ inline Ctr load_ctr(long long j) const {
+    if constexpr (FORM == AP_X) return Ctr{x[j]};
+    return Ctr{0.0};
+  }
   __device__ inline void at_center(long long i, const Raw& r, const Ctr& e) const {
-    if (!first) x[i] = (T)(e.x + alpha * r.p);
+    if constexpr (FORM == AP_X) x[i] = (T)(e.x + alpha * r.p);
   }
   __device__ inline Raw load(long long j) const {
     Raw r;
@@ -255,10 +267,11 @@ struct OpP {
       r.z = z[j];
     else
       r.z = (double)z32[j] * isc;
-    r.p = first ? 0.0 : pold[j];
+    r.p = 0.0;
+    if constexpr (FORM != AP_FIRST) r.p = pold[j];
     return r;
   }
-  __device__ inline double value(const Raw& r) const { return first ? r.z : r.z + beta * r.p; }
+  __device__ inline double value(const Raw& r) const { return FORM == AP_FIRST ? r.z : r.z + beta * r.p; }
 };
 
 // r = b - A x; Jacobi mode also Dinv = 1/diag(A), z = Dinv r.
@@ -277,7 +290,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_start(Work w, const T* __restrict
     double bb = 0.0, rr = 0.0, rz = 0.0;
     {
       plane_stencil<kStencilPrefetch>(tc, c, lds, OpX<T>{x},
-                     [&](long long i, int deg, double, double Ax) {
+                     [&](long long i, int deg, double, double Ax, const auto&) {
                        const double bi = b[i];
                        const double r = (double)(T)(bi - Ax);
                        sb.r[i] = (T)r;
@@ -299,8 +312,17 @@ __global__ void __launch_bounds__(kBlock) k_cg_start(Work w, const T* __restrict
   }
 }
 
+// Precision 64 with the multigrid: r_new.z_old from the apply's q.z.
+template <bool JAC, typename T>
+constexpr bool kSumQz = !JAC && sizeof(T) == 8;
+
 // p_new = z + beta p_old (p_new = z on the first iteration), q = A p_new;
-// and the previous iteration's x += alpha p_old (not on the first).
+// and the previous iteration's x += alpha p_old where its z is not kept.
+// Bound by HBM: read z, p_old, c, write p_new, q, 36 B a voxel in precision 64
+// with z kept and 52 with x read and written (three systems of 128^3, the
+// mean of a solve's calls: 42.8 us against 53.5).
+// Precision 64 with the multigrid also sums q.z, which saves the update a read of
+// z: r_new.z_old = r.z - alpha q.z.
 template <bool JAC, typename T>
 __global__ void __launch_bounds__(kBlock) k_cg_apply(Work w, const T* __restrict__ c,
                                                      const T* __restrict__ z,
@@ -316,26 +338,33 @@ __global__ void __launch_bounds__(kBlock) k_cg_apply(Work w, const T* __restrict
     const TileCoord tc = tile_coord(w, ti);
     const SolveScal* ssr = sb.ss + tc.rep;
     if (ssr->done) continue;
-    const double beta = ssr->beta;
-    const bool first = ssr->first != 0;
-    double pq = 0.0;
-    {
+    const int iter = ssr->it;
+    double pq = 0.0, qz = 0.0;
+    auto run = [&](auto form) {
       // ss.alpha is still the previous iteration's (this apply's reduce sets the next)
-      const OpP<JAC, T> op{z, sb.z32, pold, x, beta, ssr->isc, ssr->alpha, first};
-      plane_stencil<kStencilPrefetch>(tc, c, lds, op, [&](long long i, int, double pc, double Ap) {
+      const OpP<JAC, T, decltype(form)::value> op{z, cg_z(sb, iter), pold, x, ssr->beta, ssr->isc, ssr->alpha};
+      plane_stencil<kStencilPrefetch>(tc, c, lds, op, [&](long long i, int, double pc, double Ap, const auto& raw) {
         const T qi = (T)Ap;
         pnew[i] = (T)pc;
         q[i] = qi;
         pq += pc * (double)qi;
+        if constexpr (kSumQz<JAC, T>) qz += raw.z * (double)qi;
       });
-    }
+    };
+    if (ssr->first)
+      run(std::integral_constant<ApplyForm, AP_FIRST>());
+    else if (iter > sb.ring.n)
+      run(std::integral_constant<ApplyForm, AP_X>());
+    else if constexpr (kSumQz<JAC, T>)   // z is kept in no other
+      run(std::integral_constant<ApplyForm, AP_KEPT>());
     pq = block_sum(pq, lds4);
-    store_partials(sb.partial + (size_t)ti * 3, pq, 0.0, 0.0);
+    if constexpr (kSumQz<JAC, T>) qz = block_sum(qz, lds4);
+    store_partials(sb.partial + (size_t)ti * 3, pq, qz, 0.0);
   }
 }
 
-// r -= alpha q; partials of r.r, r.z_old and (Jacobi) r.z'.  (x += alpha p
-// is made by the next apply, or by k_cg_finish after the last iteration.)
+// r -= alpha q; partials of r.r, (but kSumQz) r.z_old and (Jacobi) r.z'.
+// (x += alpha p is made by the next apply, or at the solve's end.)
 template <bool JAC, typename T>
 __global__ void __launch_bounds__(kBlock) k_cg_update(Work w, const T* __restrict__ q, SolverBufsT<T> sb) {
   __shared__ double lds4[4];
@@ -349,6 +378,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Work w, const T* __restric
     const long long off = w.reps[fb.rep].off;
     const double alpha = ssr->alpha;
     const double sc = ssr->sc, isc_prev = ssr->isc_prev;
+    const float* z32 = cg_z(sb, ssr->it);
     double rr = 0.0, rzo = 0.0, rzn = 0.0;
     // kUpd voxels per thread per trip, every load issued before any use, so
     // enough bytes are in flight per CU to stream at HBM rate on long items
@@ -362,7 +392,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Work w, const T* __restric
         if (i < end) {
           rv[u] = sb.r[i];
           qv[u] = q[i];
-          zo[u] = jac ? (double)sb.z[i] : (double)sb.z32[i] * isc_prev;
+          if constexpr (!kSumQz<JAC, T>) zo[u] = jac ? (double)sb.z[i] : (double)z32[i] * isc_prev;
           dv[u] = jac ? (double)sb.dinv[i] : 0.0;
         }
       }
@@ -374,7 +404,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Work w, const T* __restric
         sb.r[i] = (T)r;
         if (!jac && sb.r32) sb.r32[i] = (float)(r * sc);   // the multigrid's scaled copy
         rr += r * r;
-        rzo += r * zo[u];
+        if constexpr (!kSumQz<JAC, T>) rzo += r * zo[u];
         if (jac) {
           const double znew = (double)(T)(r * dv[u]);
           sb.z[i] = (T)znew;
@@ -383,28 +413,23 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(Work w, const T* __restric
       }
     }
     rr = block_sum(rr, lds4);
-    rzo = block_sum(rzo, lds4);
-    rzn = block_sum(rzn, lds4);
+    if constexpr (!kSumQz<JAC, T>) {
+      rzo = block_sum(rzo, lds4);
+      rzn = block_sum(rzn, lds4);
+    }
     store_partials(sb.partial + (size_t)it * 3, rr, rzo, rzn);
   }
 }
 
-// The last iteration's x += alpha p of every system that iterated (the
-// earlier iterations' were made by the applies that followed them).
+// The end of every system's solve that iterated (cg_finish_span).
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_cg_finish(Work w, T* __restrict__ x, SolverBufsT<T> sb) {
   int b0, b1;
   work_range(w.nflat, b0, b1);
   for (int it = b0; it < b1; ++it) {
     const FlatBlk fb = w.flat[it];
-    const SolveScal* ssr = sb.ss + fb.rep;
-    const int n = ssr->it;
-    if (n == 0) continue;
-    const T* __restrict__ p = ((n - 1) & 1) ? sb.p0 : sb.p1;   // the direction of iteration n - 1
-    const double alpha = ssr->alpha;
-    const long long off = w.reps[fb.rep].off;
-    for (long long i = off + fb.begin + threadIdx.x; i < off + fb.end; i += kBlock)
-      x[i] = (T)fma(alpha, (double)p[i], (double)x[i]);
+    cg_finish_span(sb.ring, (const T*)sb.p0, (const T*)sb.p1, sb.ss, fb.rep, x, w.reps[fb.rep].off + fb.begin,
+                   (int)(fb.end - fb.begin));
   }
 }
 
@@ -776,8 +801,10 @@ __global__ void __launch_bounds__(kBlock) k_cg_reduce(Work w, SolverBufsT<T> sb,
   const int b0 = KIND == RED_RZF ? rp.fpart_b0 : tiles ? rp.tile_b0 : rp.flat_b0;
   const int nb = KIND == RED_RZF ? rp.fpart_nb : tiles ? rp.tile_nb : rp.flat_nb;
   const double t0 = sum_partials(sb.partial, b0, nb, 0, lds4);
-  const double t1 = (KIND == RED_START || KIND == RED_UPDATE) ? sum_partials(sb.partial, b0, nb, 1, lds4) : 0.0;
-  const double t2 = (KIND == RED_START || KIND == RED_UPDATE) ? sum_partials(sb.partial, b0, nb, 2, lds4) : 0.0;
+  const bool qz = !sb.jacobi && sizeof(T) == 8;   // kSumQz
+  const bool two = KIND == RED_START || (KIND == RED_APPLY ? qz : KIND == RED_UPDATE && !qz);
+  const double t1 = two ? sum_partials(sb.partial, b0, nb, 1, lds4) : 0.0;
+  const double t2 = KIND == RED_START || (KIND == RED_UPDATE && !qz) ? sum_partials(sb.partial, b0, nb, 2, lds4) : 0.0;
   if (threadIdx.x != 0) return;
   if (KIND == RED_START) {
     s.bb = t0;
@@ -805,14 +832,21 @@ __global__ void __launch_bounds__(kBlock) k_cg_reduce(Work w, SolverBufsT<T> sb,
     if (s.done) atomicAdd(sb.ndone, 1);
   } else if (KIND == RED_APPLY) {
     s.pq = t0;
+    s.qz = t1;
     s.alpha = s.rz / t0;
+    if (s.it < sb.ring.n) {   // beta and isc are the ones z and p of this iteration were formed with
+      double* h = sb.ring.hist + 3 * ((size_t)rep * kZRing + s.it);
+      h[0] = s.alpha;
+      h[1] = s.beta;
+      h[2] = s.isc;
+    }
     // the scale of the r32 the next update writes (from the current ||r||)
     s.isc_prev = s.isc;
     s.sc = residual_scale(s.rr, rp.n);
     s.isc = 1.0 / s.sc;
   } else if (KIND == RED_UPDATE) {
     s.rr = t0;
-    s.rzo = t1;
+    s.rzo = qz ? s.rz - s.alpha * s.qz : t1;
     s.it += 1;
     s.first = 0;
     if (sb.jacobi) {

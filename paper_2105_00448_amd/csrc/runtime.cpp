@@ -87,7 +87,7 @@ const double kBytesPerVoxel[KC_COUNT] = {
     9.0 + 9 * kE,   // setup_step: read L, w, K, G1, G2; write c, b of three systems
     5 * kE,         // cg_start: read x, c, b; write r, (Jacobi: dinv, z)
     4.0 + 6 * kE,   // cg_apply, multigrid: read z (4), p_old, c, x; write p_new, q, x (the
-                    // previous iteration's x += alpha p; a solve's first apply: 4 + 4 e)
+                    // previous iteration's x += alpha p; 4 + 4 e where there is none to make)
     6 * kE,         // cg_update, Jacobi: read r, q, z, dinv; write r, z
     49.0 + kE,      // ode: read L, K, P, Vc, phi; write P, Vc, phi
     11.0,           // ca_propose: scan (read L, phi; write code, win); the list's decisions
@@ -107,7 +107,7 @@ const double kBytesPerVoxel[KC_COUNT] = {
     16.0,           // mg sweep L0: read u (4), r (4), dinv (4); write u' (4)
     12.5,           // mg prefused L0: read r (4), dinv (4); write u3 (4), r1 (1/8 of 4)
     kE == 8 ? 24.5 : 16.5,   // mg postfused L0: read u3 (4), e (1/8), r (4), dinv (4), r (FP64); write z (4)
-    3 * kE,         // cg_finish: read x, p; write x (once per solve)
+    3 * kE,         // cg_finish: read x, p; write x (once per solve; with kept z: finish_bytes)
     11 * kE};       // guess fit, per voxel of one fitted field: read x1, x2, x3, c, b (the products);
                     // read x1, x2, x3; write x0, x1, x2 (the shifted history; x0 and x1 alone
                     // when the history buffers rotate)
@@ -115,12 +115,12 @@ constexpr double kBytesSetupVegf = 8.0 + 3 * kE;   // setup_step with vegf: + re
 constexpr double kBytesSetupDrug3 = 3 * kE;        // setup_step with drug3: + read G3; write c, b
 constexpr double kBytesStatsField = kE;            // stats: per extra field scanned (V, G3)
 // cg_update, multigrid: the compulsory r, q read and r written (the CG's own
-// traffic; x += alpha p moved to the next apply); the kernel also reads the
-// FP32 z and writes the FP32 copy of r for the multigrid (8 B more per voxel,
-// not counted here)
+// traffic); the kernel also writes the FP32 copy of r for the multigrid
+// (precision 64) or reads the FP32 z (precision 32): 4 B more per voxel, not
+// counted here
 constexpr double kBytesUpdateMg = 3 * kE;
 constexpr double kBytesApplyJacobi = 7 * kE;       // cg_apply, Jacobi: z is a stored field value
-constexpr double kBytesApplyX = 2 * kE;            // cg_apply's x read and write (not on a solve's first)
+constexpr double kBytesApplyX = 2 * kE;            // cg_apply's x read and write (iterations after CgRing's)
 
 constexpr int kTagState = -2;   // launches over every voxel of every replicate
 constexpr int kTagAll = -1;     // solver launches over every system
@@ -564,6 +564,21 @@ bool capture_iterations(Ctx* c, const Work& W, const MgBufs& mg, double rtol, in
 // no-op iteration pair of launches).
 int g_solve_lead = 0;
 
+// Bytes of the solves' ends of the first nsys systems (c->h_ss their last
+// scalars) and the voxels of those that iterated: x read and written, the kept
+// z (CgRing) and, where there were more iterations, p read.
+double finish_bytes(const Ctx* c, int nsys, double& vox) {
+  double bytes = 0.0;
+  vox = 0.0;
+  for (int s = 0; s < nsys; ++s) {
+    const int it = c->h_ss[s].it, kept = std::min(it, c->sb.ring.n);
+    if (it == 0) continue;
+    vox += (double)c->sys_n[s];
+    bytes += (double)c->sys_n[s] * (2 * kE + 4.0 * kept + (it > kept ? kE : 0.0));
+  }
+  return bytes;
+}
+
 // Flexible CG on the systems of W (all systems: sys_all, oxygen only: sys1) for
 // (diag(c) - a Lap) x = b, x = the field array F.  Systems of fields outside
 // `fmask` are marked finished at the start.  Iterations are launched in
@@ -574,7 +589,10 @@ int g_solve_lead = 0;
 // (sys1, mg1: the same arrays, fewer workgroups) and its captured graph.
 // defer_finish (a solve of every field that the ODE phase follows): when every
 // system converged, the last iteration's x += alpha p is left to the ODE
-// kernel (c->fin_pending), which reads every voxel of the fields anyway.
+// kernel (c->fin_pending), which reads every voxel of the fields anyway; not
+// in precision 64: the kept z cost the ODE kernel's wavefronts more than a pass of
+// their own (128^3: 216 us against 151 + 51, the 64-replicate ensemble 1600
+// against 899 + 574, the network at 384^3 4740 against 3314 + 1313).
 // prep_o2_only: the other fields' multigrid data are current (c->fixed_ops);
 // only the oxygen systems' are rebuilt from this step's c.
 hca_status solve(Ctx* c, const Work& W_all, const MgBufs& mg_all, unsigned fmask, double rtol,
@@ -600,8 +618,8 @@ hca_status solve(Ctx* c, const Work& W_all, const MgBufs& mg_all, unsigned fmask
   int real = 0;
   auto iteration = [&](int it) {
     {
-      // a solve's first apply has no earlier x += alpha p to make
-      ProfScope ps(c, KC_CG_APPLY, it, true, it == 0 ? -kBytesApplyX : 0.0);
+      // no earlier x += alpha p to make: a solve's first apply, and those after kept z
+      ProfScope ps(c, KC_CG_APPLY, it, true, it <= c->sb.ring.n ? -kBytesApplyX : 0.0);
       launch_cg_apply(c->stream, *Wp, c->c, c->F, c->sb, it & 1);
     }
     {
@@ -652,10 +670,12 @@ hca_status solve(Ctx* c, const Work& W_all, const MgBufs& mg_all, unsigned fmask
   }
   bool allconv = true;
   for (int s = 0; s < nsys; ++s) allconv = allconv && c->h_ss[s].conv;
-  if (defer_finish && allconv) {
+  if (defer_finish && allconv && kPrecision == 32) {
     c->fin_pending = true;
-  } else {   // the last iteration's x += alpha p (systems that iterated)
-    ProfScope ps(c, KC_CG_FINISH, 0);
+  } else {   // the solves' ends (systems that iterated)
+    double vox = 0.0;
+    const double bytes = finish_bytes(c, nsys, vox);
+    ProfScope ps(c, KC_CG_FINISH, 0, true, vox > 0.0 ? bytes / vox - kBytesPerVoxel[KC_CG_FINISH] : 0.0);
     launch_cg_finish(c->stream, W_all, c->F, c->sb);
   }
   prof_flush(c, c->h_ss, nsys);
@@ -673,15 +693,13 @@ hca_status solve(Ctx* c, const Work& W_all, const MgBufs& mg_all, unsigned fmask
 }
 
 // The deferred solve end for the ODE phase (null: none) and its bytes per
-// voxel (x, p read and x written for each system that iterated).
+// voxel.
 const CgFinish<Real>* take_finish(Ctx* c, double& bpv) {
   bpv = 0.0;
   if (!c->fin_pending) return nullptr;
   c->fin_pending = false;
   double vox = 0.0;
-  for (int s = 0; s < c->dp.nf * c->nreps; ++s)
-    if (c->h_ss[s].it > 0) vox += (double)c->sys_n[s];
-  bpv = kBytesPerVoxel[KC_CG_FINISH] * vox / (double)c->ntot;
+  bpv = finish_bytes(c, c->dp.nf * c->nreps, vox) / (double)c->ntot;
   return c->d_fin;
 }
 
@@ -1202,6 +1220,7 @@ hca_status plan_tiles(Ctx* c) {
   Real* tx = (Real*)scratch(sizeof(Real) * n);   // the apply's x (a zero alpha leaves it as it is)
   SolverBufs tsb{};
   tsb.z32 = (float*)scratch(4 * n);   // multigrid layout (jacobi = 0)
+  tsb.ring.n = kPrecision == 64 ? 0 : -1;   // x not updated, as where z is kept, or updated
   tsb.p0 = (Real*)scratch(sizeof(Real) * n);
   tsb.p1 = (Real*)scratch(sizeof(Real) * n);
   tsb.q = (Real*)scratch(sizeof(Real) * n);
@@ -1447,8 +1466,9 @@ hca_status alloc_all(Ctx* c) {
   for (double** p : f1)
     if ((st = big(p, n)) != HCA_OK) return st;
   Real** f3[] = {&c->F, &c->c, &c->b, &c->sb.r, &c->sb.p0, &c->sb.p1, &c->sb.q};
+  const size_t zstride = (n3 + 31) & ~(size_t)31;   // of the z that lie in b (CgRing): two within n3 + 32 values
   for (Real** p : f3)   // (strip loads of the multigrid read up to kStripPad values past a row)
-    if ((st = big(p, n3 + kStripPad)) != HCA_OK) return st;
+    if ((st = big(p, n3 + (p == &c->b ? 32 : kStripPad))) != HCA_OK) return st;
   if (c->use_mg) {
     for (float** p : {&c->sb.z32, &c->sb.r32}) {   // (strip loads: as above)
       if (p == &c->sb.r32 && sizeof(Real) == 4 && c->prm.mg_fuse) continue;   // the fused passes scale r themselves
@@ -1490,6 +1510,25 @@ hca_status alloc_all(Ctx* c) {
     if ((st = big(&c->Fprev2, n3)) != HCA_OK) return st;
     HIPCHK(c, dalloc(&c->d_gpart, (size_t)kGuessPartsPerTile * std::max(1, c->sys_all.ntiles)));
     HIPCHK(c, dalloc(&c->d_galpha, 4 * (size_t)nsys));
+  }
+  // Precision 64 keeps the z of a solve's first iterations (CgRing): two in b,
+  // and two in memory of their own where that is there in plenty (HCA_CG_KEEP:
+  // at most so many).
+  if (c->use_mg && kPrecision == 64) {
+    int keep = kZRing;
+    if (const char* e = getenv("HCA_CG_KEEP")) keep = std::max(0, std::min(kZRing, atoi(e))) & ~1;
+    CgRing& g = c->sb.ring;
+    g.n = std::min(keep, 2);
+    g.stride = (long long)zstride;
+    g.z01 = (float*)c->b;
+    HIPCHK(c, dalloc(&g.hist, (size_t)nsys * 3 * kZRing));
+    size_t mfree = 0, mall = 0;
+    if (keep > 2 && hipMemGetInfo(&mfree, &mall) == hipSuccess && 2 * zstride * sizeof(float) <= mfree / 8) {
+      if (dalloc(&g.z23, 2 * zstride) == hipSuccess)
+        g.n = keep;
+      else
+        (void)hipGetLastError();
+    }
   }
   {
     const CgFinish<Real> fin{c->F, c->sb.p0, c->sb.p1, c->sb.ss, c->ntot, c->dp.nf, c->nreps};
@@ -1836,7 +1875,7 @@ hca_status steady_oxygen(Ctx* c) {
 
 void free_all(Ctx* c) {
   void* bufs[] = {c->L, c->code, c->win, (void*)c->ca_list.cells, (void*)c->ca_list.item_n, c->w, c->P, c->Vc, c->phi, c->F, c->c, c->b,
-                  c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
+                  c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.ring.z23, (void*)c->sb.ring.hist, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
                   c->sb.counter, c->sb.ss, c->sb.ndone, c->dose_t, c->dose_a, c->g0, c->b_o2lin, c->Fprev, c->Fprev2, c->d_gpart, c->d_galpha, (void*)c->d_fin, c->d_step,
                   c->d_reps, c->d_flat, c->d_tiles, c->d_sys, c->d_sflat, c->d_stiles, c->d_ftiles, c->d_ftiles1, c->d_rztiles, c->d_cnt, (void*)c->d_cpart,
                   c->d_bad, c->d_theta, (void*)c->d_pack, (void*)c->d_gelu, c->before,

@@ -45,7 +45,7 @@ def kernels(e):
     p32 = "false" if e == 8 else "true"   # the fused passes' precision flag
     return {
         f"k_cg_update<false, {fp}>": ("k_cg_update", 3 * e),
-        f"k_cg_apply<false, {fp}>": ("k_cg_apply", 4 + 6 * e),
+        f"k_cg_apply<false, {fp}>": ("k_cg_apply", 4 + (4 if e == 8 else 6) * e),
         f"k_cg_finish<{fp}>": ("k_cg_finish", 3 * e),
         "k_mg_pre<true, float>": ("k_mg_pre_L0", 12.0),
         "k_mg_sweep<true, float>": ("k_mg_sweep_L0", 16.0),
