@@ -268,9 +268,7 @@ struct SolverBufsT {
   T* dinv;                    // 1/diag(A), written by the start kernel (Jacobi)
   int jacobi;                 // 1: Jacobi preconditioner inside the update kernel
   double* partial;            // per work item
-  unsigned* counter;          // per replicate
   SolveScal* ss;              // per replicate
-  int* ndone;                 // replicates finished
   CgRing ring;
 };
 

@@ -1285,7 +1285,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
           if constexpr (ZOUT && !P32) {
             // zs is the last plane of a group in one step of four at most
             if (s == S && ((k - S) & 3) == 3 && (zs & gmask) == gmask && zs >= z0 && zs < z1) {
-              for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
+              rz = wave_sum(rz);
               if ((threadIdx.x & 63) == 0) sRz[threadIdx.x >> 6] = rz;
               rz = 0.0;
             }
@@ -1313,7 +1313,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
   }
   if constexpr (ZOUT && !P32) {
     if ((z1 & gmask) != 0) {   // the lattice's last, shorter group
-      for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
+      rz = wave_sum(rz);
       if ((threadIdx.x & 63) == 0) sRz[threadIdx.x >> 6] = rz;
       __syncthreads();
     }
@@ -1335,7 +1335,7 @@ __global__ void __launch_bounds__(kRzBlock) k_mg_rz32(MgLevel L0, const double* 
   const MgRep m = L0.reps[t.rep];
   const int x = t.x0 + (int)threadIdx.x % m.tx, y = t.y0 + (int)threadIdx.x / m.tx;
   double rz = x < m.nx && y < m.ny ? colsum[t.part + x + (long long)m.nx * y] : 0.0;
-  for (int o = 32; o > 0; o >>= 1) rz += __shfl_xor(rz, o, 64);
+  rz = wave_sum(rz);
   if ((threadIdx.x & 63) == 0) sum[threadIdx.x >> 6] = rz;
   __syncthreads();
   if (threadIdx.x == 0) {

@@ -280,7 +280,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_start(Work w, const T* __restrict
                                                      const T* __restrict__ b,
                                                      const T* __restrict__ x,
                                                      SolverBufsT<T> sb) {
-  __shared__ double lds4[4];
+  __shared__ double lds4[4][3];
   __shared__ T lds[2][kPlaneMax];
   int t0, t1;
   tile_range(w.ntiles, t0, t1);
@@ -305,10 +305,9 @@ __global__ void __launch_bounds__(kBlock) k_cg_start(Work w, const T* __restrict
                        }
                      });
     }
-    bb = block_sum(bb, lds4);
-    rr = block_sum(rr, lds4);
-    rz = block_sum(rz, lds4);
-    store_partials(sb.partial + (size_t)ti * 3, bb, rr, rz);
+    double sums[3] = {bb, rr, rz};
+    block_sums(sums, lds4);
+    store_partials(sb.partial + (size_t)ti * 3, sums[0], sums[1], sums[2]);
   }
 }
 
@@ -330,7 +329,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_apply(Work w, const T* __restrict
                                                      T* __restrict__ pnew,
                                                      T* __restrict__ q, T* __restrict__ x,
                                                      SolverBufsT<T> sb) {
-  __shared__ double lds4[4];
+  __shared__ double lds4[4][2];
   __shared__ T lds[2][kPlaneMax];
   int t0, t1;
   tile_range(w.ntiles, t0, t1);
@@ -357,9 +356,9 @@ __global__ void __launch_bounds__(kBlock) k_cg_apply(Work w, const T* __restrict
       run(std::integral_constant<ApplyForm, AP_X>());
     else if constexpr (kSumQz<JAC, T>)   // z is kept in no other
       run(std::integral_constant<ApplyForm, AP_KEPT>());
-    pq = block_sum(pq, lds4);
-    if constexpr (kSumQz<JAC, T>) qz = block_sum(qz, lds4);
-    store_partials(sb.partial + (size_t)ti * 3, pq, qz, 0.0);
+    double sums[2] = {pq, qz};
+    block_sums(sums, lds4);
+    store_partials(sb.partial + (size_t)ti * 3, sums[0], sums[1], 0.0);
   }
 }
 
@@ -587,7 +586,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
                                                        const T* __restrict__ x1, const T* __restrict__ x2,
                                                        const T* __restrict__ x3, double* __restrict__ part,
                                                        unsigned fmask, int nrep) {
-  __shared__ double lds4[4];
+  __shared__ double lds4[4][kGuessPartsPerTile];
   __shared__ T lds[2][4][kPlaneMax];
   int t0, t1;
   tile_range(w.ntiles, t0, t1);
@@ -610,8 +609,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
       d[10] += bi * g;
       d[11] += g * g;
     });
-#pragma unroll
-    for (int q = 0; q < kGuessPartsPerTile; ++q) d[q] = block_sum(d[q], lds4);
+    block_sums(d, lds4);
     if (threadIdx.x == 0) {
       double* o = part + (size_t)ti * kGuessPartsPerTile;
 #pragma unroll
@@ -622,39 +620,56 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
 
 // Least squares in the first n of the basis images (n = 1, 2, 3): the normal
 // equations G c = r scaled to a unit diagonal and solved by Cholesky; false
-// if a pivot is not well above 0 (the vectors nearly dependent).
+// if a pivot is not well above 0 (the vectors nearly dependent).  Unrolled, with
+// its contractions written out (the compiler's choice would differ with the
+// unrolling, and in precision 32 a last bit here can flip one of the guess's).
 __device__ inline bool ls_fit(const double (&G)[3][3], const double (&r)[3], int n, double (&cf)[3]) {
+#pragma clang fp contract(off)
   double D[3], S[3][3], y[3];
+#pragma unroll
   for (int p = 0; p < n; ++p) {
     if (!(G[p][p] > 0.0)) return false;
     D[p] = 1.0 / sqrt(G[p][p]);
   }
+#pragma unroll
   for (int p = 0; p < n; ++p)
+#pragma unroll
     for (int q = 0; q < n; ++q) S[p][q] = G[p][q] * D[p] * D[q];
   double Lm[3][3] = {};
+#pragma unroll
   for (int p = 0; p < n; ++p) {   // S = L L^T
     double dd = S[p][p];
-    for (int k = 0; k < p; ++k) dd -= Lm[p][k] * Lm[p][k];
+#pragma unroll
+    for (int k = 0; k < p; ++k) dd = fma(-Lm[p][k], Lm[p][k], dd);
     if (!(dd > 1e-12)) return false;
     Lm[p][p] = sqrt(dd);
+#pragma unroll
     for (int q = p + 1; q < n; ++q) {
       double v = S[q][p];
-      for (int k = 0; k < p; ++k) v -= Lm[q][k] * Lm[p][k];
+#pragma unroll
+      for (int k = 0; k < p; ++k) v = fma(-Lm[q][k], Lm[p][k], v);
       Lm[q][p] = v / Lm[p][p];
     }
   }
+#pragma unroll
   for (int p = 0; p < n; ++p) {   // L y = D r
     double v = r[p] * D[p];
-    for (int k = 0; k < p; ++k) v -= Lm[p][k] * y[k];
+#pragma unroll
+    for (int k = 0; k < p; ++k) v = fma(-Lm[p][k], y[k], v);
     y[p] = v / Lm[p][p];
   }
+#pragma unroll
   for (int p = n - 1; p >= 0; --p) {   // L^T z = y, c = D z
     double v = y[p];
-    for (int k = p + 1; k < n; ++k) v -= Lm[k][p] * cf[k];
+#pragma unroll
+    for (int k = p + 1; k < n; ++k) v = fma(-Lm[k][p], cf[k], v);
     cf[p] = v / Lm[p][p];
   }
+#pragma unroll
   for (int p = 0; p < n; ++p) cf[p] *= D[p];
+#pragma unroll
   for (int p = n; p < 3; ++p) cf[p] = 0.0;
+#pragma unroll
   for (int p = 0; p < n; ++p)
     if (!isfinite(cf[p])) return false;
   return true;
@@ -666,18 +681,18 @@ __device__ inline bool ls_fit(const double (&G)[3][3], const double (&r)[3], int
 __global__ void __launch_bounds__(kBlock) k_guess_reduce(Work w, const double* __restrict__ part,
                                                          double* __restrict__ alpha, unsigned fmask,
                                                          int nrep) {
-  __shared__ double lds4[4];
+  __shared__ double lds4[4][kGuessPartsPerTile];
   const int rep = blockIdx.x;
   if (!((fmask >> (rep / nrep)) & 1u)) return;
   const RepDev rp = w.reps[rep];
-  double t[kGuessPartsPerTile];
+  double t[kGuessPartsPerTile] = {};
+#pragma unroll 2
+  for (int j = threadIdx.x; j < rp.tile_nb; j += kBlock) {
+    const double* o = part + (size_t)(rp.tile_b0 + j) * kGuessPartsPerTile;
 #pragma unroll
-  for (int k = 0; k < kGuessPartsPerTile; ++k) {
-    double s = 0.0;
-    for (int j = threadIdx.x; j < rp.tile_nb; j += kBlock)
-      s += part[(size_t)(rp.tile_b0 + j) * kGuessPartsPerTile + k];
-    t[k] = block_sum(s, lds4);
+    for (int k = 0; k < kGuessPartsPerTile; ++k) t[k] += o[k];
   }
+  block_sums(t, lds4);
   if (threadIdx.x != 0) return;
   const double G[3][3] = {{t[0], t[1], t[2]}, {t[1], t[3], t[4]}, {t[2], t[4], t[5]}};
   const double r[3] = {t[6], t[7], t[8]};
@@ -692,6 +707,7 @@ __global__ void __launch_bounds__(kBlock) k_guess_reduce(Work w, const double* _
   };
   double best[3] = {1.0, 0.0, 0.0};   // x1 alone (also when x1 = 0)
   double rbest = resid(best);
+#pragma unroll   // arrays in registers instead of scratch memory: 13 -> 4.8 us
   for (int n = 1; n <= 3; ++n) {
     double cf[3];
     if (ls_fit(G, r, n, cf)) {
@@ -770,41 +786,54 @@ __global__ void __launch_bounds__(kBlock) k_cg_r32(Work w, SolverBufsT<T> sb) {
   }
 }
 
-// Fixed-order sum of component k of the partials [b0, b0 + nb).
-__device__ inline double sum_partials(const double* partial, int b0, int nb, int k, double* lds4) {
-  double s = 0.0;
-  for (int j = threadIdx.x; j < nb; j += kBlock) s += partial[(size_t)(b0 + j) * 3 + k];
-  return block_sum(s, lds4);
+// Fixed-order sums of the first N components of the partials [b0, b0 + nb).
+template <int N>
+__device__ inline void sum_partials(const double* __restrict__ partial, int b0, int nb, double (&s)[N],
+                                    double (&lds)[4][N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) s[k] = 0.0;
+#pragma unroll 8
+  for (int j = threadIdx.x; j < nb; j += kBlock) {
+    const double* o = partial + (size_t)(b0 + j) * 3;
+#pragma unroll
+    for (int k = 0; k < N; ++k) s[k] += o[k];
+  }
+  block_sums(s, lds);
 }
 
 // One workgroup per replicate: finish the reduction of the preceding kernel
-// and advance the replicate's CG scalars.
+// and advance the replicate's CG scalars.  All latency: the scalars and the
+// partials' place are loaded side by side before the sums, and every component
+// in one pass over the partials (128^3, the mean of a solve's calls: p.q 4.9 -> 4.6
+// us, r.r 5.2 -> 4.6).
 template <int KIND, typename T>
 __global__ void __launch_bounds__(kBlock) k_cg_reduce(Work w, SolverBufsT<T> sb, double rtol, int maxit,
                                                       unsigned fmask, int nrep) {
-  __shared__ double lds4[4];
+  // components: b.b, r.r, r.z; p.q, q.z; r.r (r.z_old, r.z'); r.z'
+  constexpr bool qz = sizeof(T) == 8;   // with the multigrid (kSumQz)
+  constexpr int N = KIND == RED_START || KIND == RED_UPDATE ? 3 : KIND == RED_APPLY && qz ? 2 : 1;
+  __shared__ double lds[4][N];
   const int rep = blockIdx.x;
   SolveScal& s = sb.ss[rep];
-  if (KIND != RED_START && s.done) return;
+  const RepDev rp = w.reps[rep];
+  const int done = s.done, it = s.it, first = s.first;
+  const double rz = s.rz, rr = s.rr, bb = s.bb, isc = s.isc, beta = s.beta, alpha = s.alpha, sqz = s.qz, rzo = s.rzo;
+  if (KIND != RED_START && done) return;
   if (KIND == RED_START && !((fmask >> (rep / nrep)) & 1u)) {   // field not requested
     if (threadIdx.x == 0) {
       s.it = 0;
       s.rr = s.bb = 0.0;
       s.conv = 1;
       s.done = 1;
-      atomicAdd(sb.ndone, 1);
     }
     return;
   }
-  const RepDev rp = w.reps[rep];
   const bool tiles = KIND != RED_UPDATE;
   const int b0 = KIND == RED_RZF ? rp.fpart_b0 : tiles ? rp.tile_b0 : rp.flat_b0;
   const int nb = KIND == RED_RZF ? rp.fpart_nb : tiles ? rp.tile_nb : rp.flat_nb;
-  const double t0 = sum_partials(sb.partial, b0, nb, 0, lds4);
-  const bool qz = !sb.jacobi && sizeof(T) == 8;   // kSumQz
-  const bool two = KIND == RED_START || (KIND == RED_APPLY ? qz : KIND == RED_UPDATE && !qz);
-  const double t1 = two ? sum_partials(sb.partial, b0, nb, 1, lds4) : 0.0;
-  const double t2 = KIND == RED_START || (KIND == RED_UPDATE && !qz) ? sum_partials(sb.partial, b0, nb, 2, lds4) : 0.0;
+  double t[N];
+  sum_partials(sb.partial, b0, nb, t, lds);
+  const double t0 = t[0], t1 = N > 1 ? t[N > 1 ? 1 : 0] : 0.0, t2 = N > 2 ? t[N > 2 ? 2 : 0] : 0.0;
   if (threadIdx.x != 0) return;
   if (KIND == RED_START) {
     s.bb = t0;
@@ -818,9 +847,9 @@ __global__ void __launch_bounds__(kBlock) k_cg_reduce(Work w, SolverBufsT<T> sb,
     s.pq = 0.0;
     s.it = 0;
     s.first = 1;
-    s.sc = residual_scale(t1, rp.n);
-    s.isc = 1.0 / s.sc;
-    s.isc_prev = s.isc;
+    const double sc = residual_scale(t1, rp.n);
+    s.sc = sc;
+    s.isc = s.isc_prev = 1.0 / sc;
     // A right-hand side with ||b||^2 < 1e-280 (a drug field hundreds of steps
     // after its last dose) counts as solved by the initial guess: its squared
     // norms would leave FP64's normal range, and no result depends on a field
@@ -829,45 +858,41 @@ __global__ void __launch_bounds__(kBlock) k_cg_reduce(Work w, SolverBufsT<T> sb,
     const bool bad = !isfinite(t1) || !isfinite(t0);   // give up at once
     s.conv = conv ? 1 : 0;
     s.done = (conv || bad) ? 1 : 0;
-    if (s.done) atomicAdd(sb.ndone, 1);
   } else if (KIND == RED_APPLY) {
+    const double a = rz / t0;
     s.pq = t0;
     s.qz = t1;
-    s.alpha = s.rz / t0;
-    if (s.it < sb.ring.n) {   // beta and isc are the ones z and p of this iteration were formed with
-      double* h = sb.ring.hist + 3 * ((size_t)rep * kZRing + s.it);
-      h[0] = s.alpha;
-      h[1] = s.beta;
-      h[2] = s.isc;
+    s.alpha = a;
+    if (it < sb.ring.n) {   // beta and isc are the ones z and p of this iteration were formed with
+      double* h = sb.ring.hist + 3 * ((size_t)rep * kZRing + it);
+      h[0] = a;
+      h[1] = beta;
+      h[2] = isc;
     }
     // the scale of the r32 the next update writes (from the current ||r||)
-    s.isc_prev = s.isc;
-    s.sc = residual_scale(s.rr, rp.n);
-    s.isc = 1.0 / s.sc;
+    const double sc = residual_scale(rr, rp.n);
+    s.isc_prev = isc;
+    s.sc = sc;
+    s.isc = 1.0 / sc;
   } else if (KIND == RED_UPDATE) {
     s.rr = t0;
-    s.rzo = qz ? s.rz - s.alpha * s.qz : t1;
-    s.it += 1;
+    s.rzo = qz && !sb.jacobi ? rz - alpha * sqz : t1;
+    s.it = it + 1;
     s.first = 0;
     if (sb.jacobi) {
       s.rzn = t2;
-      s.beta = (t2 - t1) / s.rz;
+      s.beta = (t2 - t1) / rz;
       s.rz = t2;
     }
-    const bool conv = t0 <= rtol * rtol * s.bb;
+    const bool conv = t0 <= rtol * rtol * bb;
     s.conv = conv ? 1 : 0;
-    if (conv || s.it >= maxit || !isfinite(t0)) {
-      s.done = 1;
-      atomicAdd(sb.ndone, 1);
-    }
+    if (conv || it + 1 >= maxit || !isfinite(t0)) s.done = 1;
   } else {   // RED_RZ, RED_RZF: r.z' of the preconditioner, beta of the flexible CG
     s.rzn = t0;
-    s.beta = s.first ? 0.0 : (t0 - s.rzo) / s.rz;
+    s.beta = first ? 0.0 : (t0 - rzo) / rz;
     s.rz = t0;
   }
 }
-
-__global__ void k_zero_int(int* p) { *p = 0; }
 
 template <typename T>
 void launch_cg_reduce(hipStream_t s, const Work& w, const SolverBufsT<T>& sb, int kind, double rtol,
@@ -902,7 +927,6 @@ void launch_cg_start(hipStream_t s, const Work& w, double rtol, int maxit, const
                      const T* x, const SolverBufsT<T>& sb, unsigned field_mask, int nrep) {
   hca_launch(k_cg_start<T>, dim3(grid_tiles(w.ntiles, w.max_blocks)), dim3(kBlock), 0, s, w, c, b, x,
              sb);
-  hca_launch(k_zero_int, dim3(1), dim3(1), 0, s, sb.ndone);   // before the start reduce counts
   launch_cg_reduce(s, w, sb, RED_START, rtol, maxit, field_mask, nrep);
   if (sb.r32) launch_cg_r32(s, w, sb);
 }

@@ -1496,11 +1496,8 @@ hca_status alloc_all(Ctx* c) {
   if (!c->use_mg && (st = big(&c->sb.dinv, n3)) != HCA_OK) return st;
   const size_t nwork = (size_t)std::max({c->sys_all.ntiles, c->sys_all.nflat, c->nfparts});
   HIPCHK(c, dalloc(&c->sb.partial, 3 * nwork));
-  HIPCHK(c, dalloc(&c->sb.counter, nsys));
-  HIPCHK(c, hipMemset(c->sb.counter, 0, sizeof(unsigned) * nsys));
   HIPCHK(c, dalloc(&c->sb.ss, nsys));
   HIPCHK(c, hipMemset(c->sb.ss, 0, sizeof(SolveScal) * nsys));
-  HIPCHK(c, dalloc(&c->sb.ndone, 1));
   HIPCHK(c, dalloc(&c->dose_t, (size_t)c->nreps * 3 * HCA_MAX_DOSES));
   HIPCHK(c, dalloc(&c->dose_a, (size_t)c->nreps * 3 * HCA_MAX_DOSES));
   HIPCHK(c, dalloc(&c->g0, (size_t)c->nreps * 6));   // levels at both ends of a field substep
@@ -1876,7 +1873,7 @@ hca_status steady_oxygen(Ctx* c) {
 void free_all(Ctx* c) {
   void* bufs[] = {c->L, c->code, c->win, (void*)c->ca_list.cells, (void*)c->ca_list.item_n, c->w, c->P, c->Vc, c->phi, c->F, c->c, c->b,
                   c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.ring.z23, (void*)c->sb.ring.hist, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
-                  c->sb.counter, c->sb.ss, c->sb.ndone, c->dose_t, c->dose_a, c->g0, c->b_o2lin, c->Fprev, c->Fprev2, c->d_gpart, c->d_galpha, (void*)c->d_fin, c->d_step,
+                  c->sb.ss, c->dose_t, c->dose_a, c->g0, c->b_o2lin, c->Fprev, c->Fprev2, c->d_gpart, c->d_galpha, (void*)c->d_fin, c->d_step,
                   c->d_reps, c->d_flat, c->d_tiles, c->d_sys, c->d_sflat, c->d_stiles, c->d_ftiles, c->d_ftiles1, c->d_rztiles, c->d_cnt, (void*)c->d_cpart,
                   c->d_bad, c->d_theta, (void*)c->d_pack, (void*)c->d_gelu, c->before,
                   c->item_cnt, c->item_off};
