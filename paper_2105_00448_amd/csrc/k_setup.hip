@@ -257,27 +257,56 @@ __global__ void __launch_bounds__(kBlock) k_rhs_lap(Work w, DevParams p, long lo
                                                     const T* __restrict__ F, T* __restrict__ b) {
   const double sK = (1.0 - p.theta) * p.aK, sG = (1.0 - p.theta) * p.aG,
                sV = (1.0 - p.theta) * p.aV;
-  for_each_voxel(w, [&](int, const RepDev& rp, long long g) {
-    const long long i = g - rp.off;
-    const int x = (int)(i % rp.nx);
-    const long long q = i / rp.nx;
-    const int y = (int)(q % rp.ny);
-    const int z = (int)(q / rp.ny);
-    const long long sy = rp.nx, sz = (long long)rp.nx * rp.ny;
-    for (int f = 0; f < p.nf; ++f) {
-      const T* u = F + (long long)f * ntot;
-      const double uc = u[g];
-      double lap = 0.0;
-      if (x > 0) lap += (double)u[g - 1] - uc;
-      if (x + 1 < rp.nx) lap += (double)u[g + 1] - uc;
-      if (y > 0) lap += (double)u[g - sy] - uc;
-      if (y + 1 < rp.ny) lap += (double)u[g + sy] - uc;
-      if (z > 0) lap += (double)u[g - sz] - uc;
-      if (z + 1 < rp.nz) lap += (double)u[g + sz] - uc;
-      const long long j = g + (long long)f * ntot;
-      b[j] = (T)((double)b[j] + (f == 0 ? sK : (p.vegf && f == p.fV) ? sV : sG) * lap);
+  // Four voxels per thread, a field's loads of all four in flight together; a
+  // missing neighbour is the voxel itself (its difference 0).  Indices fit 32
+  // bits: 2^32 voxels of nine FP64 arrays would not fit the device.  (A voxel
+  // and a field at a time, with a branch per neighbour: 13.5 us for a 100 x 100
+  // slice's three fields, against 6.8.)
+  constexpr int kV = 4;
+  int b0, b1;
+  work_range(w.nflat, b0, b1);
+  for (int it = b0; it < b1; ++it) {
+    const FlatBlk fb = w.flat[it];
+    const RepDev rp = w.reps[fb.rep];
+    const unsigned nx = (unsigned)rp.nx, ny = (unsigned)rp.ny, nz = (unsigned)rp.nz;
+    const int sy = rp.nx, sz = rp.nx * rp.ny;
+    for (long long i0 = fb.begin + threadIdx.x; i0 < fb.end; i0 += kV * kBlock) {
+      long long g[kV];
+      int d[kV][6];
+#pragma unroll
+      for (int v = 0; v < kV; ++v) {
+        const unsigned i = (unsigned)min(i0 + (long long)v * kBlock, fb.end - 1);
+        const unsigned q = i / nx, x = i - q * nx, z = q / ny, y = q - z * ny;
+        g[v] = rp.off + i;
+        d[v][0] = x > 0 ? -1 : 0;
+        d[v][1] = x + 1 < nx ? 1 : 0;
+        d[v][2] = y > 0 ? -sy : 0;
+        d[v][3] = y + 1 < ny ? sy : 0;
+        d[v][4] = z > 0 ? -sz : 0;
+        d[v][5] = z + 1 < nz ? sz : 0;
+      }
+      for (int f = 0; f < p.nf; ++f) {
+        const double scale = f == 0 ? sK : (p.vegf && f == p.fV) ? sV : sG;
+        const long long fo = (long long)f * ntot;
+        double uc[kV], bv[kV], un[kV][6];
+#pragma unroll
+        for (int v = 0; v < kV; ++v) {
+          const T* u = F + fo + g[v];
+          uc[v] = u[0];
+          bv[v] = b[fo + g[v]];
+#pragma unroll
+          for (int k = 0; k < 6; ++k) un[v][k] = u[d[v][k]];
+        }
+#pragma unroll
+        for (int v = 0; v < kV; ++v) {
+          double lap = 0.0;
+#pragma unroll
+          for (int k = 0; k < 6; ++k) lap += un[v][k] - uc[v];
+          if (i0 + (long long)v * kBlock < fb.end) b[fo + g[v]] = (T)(bv[v] + scale * lap);
+        }
+      }
     }
-  });
+  }
 }
 
 // Extrapolation in time of the solved fields as the solver's initial guess,

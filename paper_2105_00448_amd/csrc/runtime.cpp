@@ -1805,11 +1805,11 @@ hca_status build_mg(Ctx* c) {
     ncells_max = std::max(ncells_max, n);
     if (d.dims[2] > 1) flat = 0;
     // k_mg_coarse: two iterates of level kc between three guards of a plane, and
-    // all of the others; k_mg_coarse_prep: c and the couplings of level kc, c of
-    // the others, and as far as the places of an absent child reach beyond
+    // all of the others; k_mg_coarse_prep: c and the couplings of every level,
+    // and as far as the places of an absent child reach beyond
     const int plane = d.dims[0] * d.dims[1];
     lds_max = std::max(lds_max, sizeof(float) * (size_t)std::max(2 * n + 3 * plane + 7 * d.rest,
-                                                                 4 * n + d.rest + plane + d.dims[0] + 1));
+                                                                 4 * (n + d.rest) + plane + d.dims[0] + 1));
     d.off_kc = mreps[kcr[r]][s].off;
     d.r_kc = pr[kcr[r]] + d.off_kc;
     d.u_kc = pu[kcr[r]] + d.off_kc;
