@@ -1134,7 +1134,8 @@ void add_tiles(std::vector<Tile>& v, int rep, int nx, int ny, int nz, int tx, in
 // Deep tiles keep the z-halo re-reads of the plane-marching stencils small;
 // batches and large lattices supply the parallelism.
 double g_tile_target = 1024.0;
-int g_tile_depth = 16;
+constexpr int kTileDepth = 16;
+int g_tile_depth = kTileDepth;
 // Tiles per system the coarser multigrid levels aim at (HCA_MG_TILE_TARGET).
 double g_mg_tile_target = 512.0;
 
@@ -1195,6 +1196,15 @@ hca_status plan_tiles(Ctx* c) {
     }
   };
   apply_plan(g_tile_depth, 0);
+  // A small lattice's tiles march as long as they are deep and leave the chip
+  // idle: shallower ones in precision 64 (precision 32 keeps the order of its
+  // sums), by the lattice's size alone, as they fix the order of the dot products.
+  // Apply / start residual / guess products at 32^3, depths 16, 8, 4: 14.5 / 13.8 / 25.1,
+  // 9.5 / 8.7 / 15.9, 7.2 / - / - us.  The lines lie where a batch of 64 such lattices
+  // loses nothing to speak of: 1.1 M voxels 32.0 / 22.3 / 75.2, 28.4 / 18.1 / 72.1, 27.7 / 17.4 / 81.7;
+  // 26 M 420 / 343 / 656, 431 / 342 / 752, 499 / 370 / 956.
+  if (kPrecision == 64 && g_tile_depth == kTileDepth)
+    for (RepHost& R : c->reps) R.tz = even_depth(R.n <= 1 << 14 ? 4 : R.n <= 1 << 16 ? 8 : kTileDepth, R.nz);
   if (!c->prm.autotune) return HCA_OK;
   const long long n = c->ntot;
   std::vector<void*> mem;
