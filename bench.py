@@ -719,10 +719,10 @@ def roofline_of(kt_dom, dom, workload, elem=8):
          "mean_launch_us": mean_s * 1e6, "launches": kt_dom["launches"],
          "bytes_per_launch": kt_dom["bytes_per_launch"]}
     if kname == "k_cg_update":
-        # the kernel moves 8 B per voxel more than the CG's compulsory 3 stored
-        # values r, q read and r written (the multigrid's FP32 z read and, in
-        # precision 64, its r copy written; x += alpha p is made by the next apply)
-        r["frac_incl_fp32_copies"] = r["frac"] * (3 * elem + elem) / (3 * elem)
+        # the kernel moves 4 B per voxel more than the CG's compulsory 3 stored
+        # values r, q read and r written (the multigrid's FP32 copy of r written in
+        # precision 64, its FP32 z read in precision 32)
+        r["frac_incl_fp32_copies"] = r["frac"] * (3 * elem + 4) / (3 * elem)
     return r
 
 
