@@ -174,7 +174,7 @@ __device__ inline void cg_finish_span(const CgRing& ring, const T* p0, const T* 
       float zv[kZRing][kPer];
 #pragma unroll
       for (int j = 0; j < kZRing; ++j) {
-        const float* z = (j < 2 ? ring.z01 : ring.z23) + (j & 1) * ring.stride + off;
+        const float* z = ring.z(j) + off;
 #pragma unroll
         for (int k = 0; k < kPer; ++k) zv[j][k] = j < kept && l0 + k * kBlock < len ? z[l0 + k * kBlock] : 0.f;
       }

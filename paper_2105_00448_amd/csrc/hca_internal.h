@@ -249,13 +249,17 @@ void launch_convert(hipStream_t s, const double* src, float* dst, long long n);
 // from 4 bytes per iteration and voxel, where x += alpha p took 16 in every
 // apply.  Iterations beyond the first n keep that form, and their z the one
 // buffer sb.z32.  The z of iterations 0 and 1 lie in the memory of b, which
-// nothing reads once the start residual is formed.
-constexpr int kZRing = 4;
+// nothing reads once the start residual is formed; iteration 2's in memory of its
+// own, which the fused smoothing passes leave over (one kernel per sweep takes
+// it for a second iterate of level 0, and two are kept).  n follows from the
+// parameters alone: it fixes the order of x's sums, and so its bits.
+constexpr int kZRing = 3;
 struct CgRing {
-  int n;                 // iterations whose z is kept: 0, 2 or kZRing
-  float *z01, *z23;      // z of iterations 0, 1 and 2, 3, `stride` apart
+  int n;                 // iterations whose z is kept: at most kZRing
+  float *z01, *z2;       // z of iterations 0 and 1, `stride` apart, and of iteration 2
   long long stride;
   double* hist;          // per system and kept iteration: alpha, beta, 1 / (the scale of z)
+  __host__ __device__ inline float* z(int it) const { return it < 2 ? z01 + it * stride : z2; }
 };
 
 // solver (k_solver.hip)
@@ -275,8 +279,7 @@ struct SolverBufsT {
 // Where z of iteration `it` lies (the kept ones in their own buffers).
 template <typename T>
 __host__ __device__ inline float* cg_z(const SolverBufsT<T>& sb, int it) {
-  if (it >= sb.ring.n) return sb.z32;
-  return (it < 2 ? sb.ring.z01 : sb.ring.z23) + (it & 1) * sb.ring.stride;
+  return it >= sb.ring.n ? sb.z32 : sb.ring.z(it);
 }
 // Systems whose field (s / nrep) is not in field_mask are marked finished.
 template <typename T>

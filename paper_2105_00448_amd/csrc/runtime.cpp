@@ -1518,23 +1518,20 @@ hca_status alloc_all(Ctx* c) {
     HIPCHK(c, dalloc(&c->d_gpart, (size_t)kGuessPartsPerTile * std::max(1, c->sys_all.ntiles)));
     HIPCHK(c, dalloc(&c->d_galpha, 4 * (size_t)nsys));
   }
-  // Precision 64 keeps the z of a solve's first iterations (CgRing): two in b,
-  // and two in memory of their own where that is there in plenty (HCA_CG_KEEP:
-  // at most so many).
+  // Precision 64 keeps the z of a solve's first iterations (CgRing): two in b
+  // and, with the fused smoothing passes, one in memory of its own
+  // (HCA_CG_KEEP: at most so many).
   if (c->use_mg && kPrecision == 64) {
-    int keep = kZRing;
-    if (const char* e = getenv("HCA_CG_KEEP")) keep = std::max(0, std::min(kZRing, atoi(e))) & ~1;
     CgRing& g = c->sb.ring;
-    g.n = std::min(keep, 2);
+    g.n = c->prm.mg_fuse ? kZRing : 2;
+    if (const char* e = getenv("HCA_CG_KEEP")) g.n = std::max(0, std::min(g.n, atoi(e)));
     g.stride = (long long)zstride;
     g.z01 = (float*)c->b;
     HIPCHK(c, dalloc(&g.hist, (size_t)nsys * 3 * kZRing));
-    size_t mfree = 0, mall = 0;
-    if (keep > 2 && hipMemGetInfo(&mfree, &mall) == hipSuccess && 2 * zstride * sizeof(float) <= mfree / 8) {
-      if (dalloc(&g.z23, 2 * zstride) == hipSuccess)
-        g.n = keep;
-      else
-        (void)hipGetLastError();
+    if (g.n > 2) {
+      hipError_t e = dalloc(&g.z2, n3);
+      if (e == hipErrorOutOfMemory) return fail(c, HCA_E_NOMEM, "device memory exhausted");
+      HIPCHK(c, e);
     }
   }
   {
@@ -1882,7 +1879,7 @@ hca_status steady_oxygen(Ctx* c) {
 
 void free_all(Ctx* c) {
   void* bufs[] = {c->L, c->code, c->win, (void*)c->ca_list.cells, (void*)c->ca_list.item_n, c->w, c->P, c->Vc, c->phi, c->F, c->c, c->b,
-                  c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.ring.z23, (void*)c->sb.ring.hist, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
+                  c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.ring.z2, (void*)c->sb.ring.hist, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
                   c->sb.ss, c->dose_t, c->dose_a, c->g0, c->b_o2lin, c->Fprev, c->Fprev2, c->d_gpart, c->d_galpha, (void*)c->d_fin, c->d_step,
                   c->d_reps, c->d_flat, c->d_tiles, c->d_sys, c->d_sflat, c->d_stiles, c->d_ftiles, c->d_ftiles1, c->d_rztiles, c->d_cnt, (void*)c->d_cpart,
                   c->d_bad, c->d_theta, (void*)c->d_pack, (void*)c->d_gelu, c->before,
