@@ -141,9 +141,44 @@ struct ProfEntry {
 
 }  // namespace
 
+// Tuning knobs of a context, from the environment at its creation.
+constexpr int kTileDepth = 16;
+struct Tuning {
+  // Iterations of a solve's first batch before the first convergence poll: the
+  // previous solve's count plus this (then polls every two):
+  // measured on the 128^3 workload, leads -1, 0, 1, 2, 3 give 2.364, 2.321,
+  // 2.357, 2.394, 2.425 ms per step (a poll costs about as much as one extra
+  // no-op iteration pair of launches).
+  int solve_lead = 0;                     // HCA_SOLVE_LEAD
+  // Planes of a stencil tile (at most nz): -1 kTileDepth and fewer on small
+  // lattices (plan_tiles), 0 as many as give tile_target tiles per lattice.  Deep tiles keep
+  // the z-halo re-reads of the plane-marching stencils small; batches and large
+  // lattices supply the parallelism.
+  int tile_depth = -1;                    // HCA_TILE_DEPTH
+  double tile_target = 1024.0;            // HCA_TILE_TARGET
+  double mg_tile_target = 512.0;          // HCA_MG_TILE_TARGET: tiles per system the coarser multigrid levels aim at
+  int fused_depth = 0;                    // HCA_FUSED_DEPTH: planes of the fused passes' tiles; 0: by fused_depth
+  // Precision 32: coarser levels smooth in fused passes from this many cells over all systems.
+  long long fuse_min_cells = 2LL << 20;   // HCA_FUSE_MIN_CELLS
+};
+Tuning tuning_from_env() {
+  Tuning t;
+  if (const char* e = getenv("HCA_SOLVE_LEAD")) t.solve_lead = std::max(-8, std::min(8, atoi(e)));
+  if (const char* e = getenv("HCA_TILE_DEPTH")) t.tile_depth = std::max(0, atoi(e));
+  if (const char* e = getenv("HCA_TILE_TARGET"))
+    if (const double v = atof(e); v >= 1.0) t.tile_target = v;
+  if (const char* e = getenv("HCA_MG_TILE_TARGET"))
+    if (const double v = atof(e); v >= 1.0) t.mg_tile_target = v;
+  if (const char* e = getenv("HCA_FUSED_DEPTH"))
+    t.fused_depth = std::max(0, std::min(1024, atoi(e))) / kF3Group * kF3Group;
+  if (const char* e = getenv("HCA_FUSE_MIN_CELLS")) t.fuse_min_cells = std::max(1LL, atoll(e));
+  return t;
+}
+
 struct Ctx : ::hca_ctx {
   Ctx() { precision = kPrecision; }
   hca_params prm;
+  Tuning tune;
   DevParams dp;
   int nreps = 0;
   std::vector<RepHost> reps;
@@ -557,13 +592,6 @@ bool capture_iterations(Ctx* c, const Work& W, const MgBufs& mg, double rtol, in
   return true;
 }
 
-// Iterations of a solve's first batch before the first convergence poll: the
-// previous solve's count plus this (HCA_SOLVE_LEAD; then polls every two):
-// measured on the 128^3 workload, leads -1, 0, 1, 2, 3 give 2.364, 2.321,
-// 2.357, 2.394, 2.425 ms per step (a poll costs about as much as one extra
-// no-op iteration pair of launches).
-int g_solve_lead = 0;
-
 // Bytes of the solves' ends of the first nsys systems (c->h_ss their last
 // scalars) and the voxels of those that iterated: x read and written, the kept
 // z (CgRing) and, where there were more iterations, p read.
@@ -614,7 +642,7 @@ hca_status solve(Ctx* c, const Work& W_all, const MgBufs& mg_all, unsigned fmask
   }
   if (c->use_mg) run_vcycle(c, W, mg, 0);   // z of the start residual
   int launched = 0;
-  int batch = std::max(1, c->last_it[kind] + g_solve_lead);
+  int batch = std::max(1, c->last_it[kind] + c->tune.solve_lead);
   int real = 0;
   auto iteration = [&](int it) {
     {
@@ -1034,16 +1062,12 @@ int fused_group(int nx, int ny, int nz) { return (long long)nx * ny * nz <= 1LL 
 // 942 / 936 / 1322 / 1310 us (32).  Level 1 at depths 4 / 8 / 16 / 24: three systems of
 // 64^3 cells 21 / 27 / 38 / 49 us (4 taken), 59 x 52 x 46, five systems, 24 / 26 / 37 / 47 (4), the
 // ensemble 114 / 91 / 88 / 100 (8); level 2 of the ensemble 25 / 29 / 42 / 46 (4).
-int g_fused_depth = 0;
-// Precision 32: coarser levels smooth in fused passes from this many cells over
-// all systems (HCA_FUSE_MIN_CELLS).
-long long g_fuse_min_cells = 2LL << 20;
 struct FusedLat {
   FusedShape f;
   int nz, least;   // least: of the tiles' depth
 };
-int fused_depth(const std::vector<FusedLat>& lats, int S) {
-  if (g_fused_depth) return g_fused_depth;
+int fused_depth(const Tuning& tune, const std::vector<FusedLat>& lats, int S) {
+  if (tune.fused_depth) return tune.fused_depth;
   const double work_us = S == 3 ? 0.22 : 0.25, step_us = S == 3 ? 0.35 : 0.45;
   int least = 4, best = kF3Group;
   for (const FusedLat& l : lats) least = std::max(least, l.least);
@@ -1129,16 +1153,6 @@ void add_tiles(std::vector<Tile>& v, int rep, int nx, int ny, int nz, int tx, in
       }
 }
 
-// Stencil tiles are g_tile_depth planes deep (at most nz; tuning knob
-// HCA_TILE_DEPTH, 0 = instead aim at HCA_TILE_TARGET tiles per lattice).
-// Deep tiles keep the z-halo re-reads of the plane-marching stencils small;
-// batches and large lattices supply the parallelism.
-double g_tile_target = 1024.0;
-constexpr int kTileDepth = 16;
-int g_tile_depth = kTileDepth;
-// Tiles per system the coarser multigrid levels aim at (HCA_MG_TILE_TARGET).
-double g_mg_tile_target = 512.0;
-
 template <typename T>
 hca_status upload(Ctx* c, T** p, const std::vector<T>& v) {
   HIPCHK(c, dalloc(p, v.size()));
@@ -1178,8 +1192,8 @@ RepDev lattice_entry(const RepHost& R, long long off, int idx, std::vector<FlatB
 
 // ---- tile autotuner ---------------------------------------------------------------
 
-// Stencil tile shape of every lattice: tx from nx (pick_tx), g_tile_depth
-// planes deep; with params.autotune, the depth (2 ... 32 planes) and the width
+// Stencil tile shape of every lattice: tx from nx (pick_tx), kTileDepth planes
+// deep or fewer (Tuning); with params.autotune, the depth (2 ... 32 planes) and the width
 // policy (pick_tx, or 16 x 16) are instead the fastest of 10 candidates, timed on the CG apply kernel (the dominant
 // stencil) over the whole batch at once on scratch arrays of the batch's
 // shape (one warm-up launch, then the best of three), so the choice accounts
@@ -1192,10 +1206,11 @@ hca_status plan_tiles(Ctx* c) {
   auto apply_plan = [&](int depth, int policy) {
     for (RepHost& R : c->reps) {
       R.tx = policy == 1 ? 16 : pick_tx(R.nx);
-      R.tz = even_depth(depth > 0 ? depth : pick_tz(R.nx, R.ny, R.nz, R.tx, g_tile_target), R.nz);
+      R.tz = even_depth(depth > 0 ? depth : pick_tz(R.nx, R.ny, R.nz, R.tx, c->tune.tile_target), R.nz);
     }
   };
-  apply_plan(g_tile_depth, 0);
+  const int depth0 = c->tune.tile_depth >= 0 ? c->tune.tile_depth : kTileDepth;
+  apply_plan(depth0, 0);
   // A small lattice's tiles march as long as they are deep and leave the chip
   // idle: shallower ones in precision 64 (precision 32 keeps the order of its
   // sums), by the lattice's size alone, as they fix the order of the dot products.
@@ -1203,7 +1218,7 @@ hca_status plan_tiles(Ctx* c) {
   // 9.5 / 8.7 / 15.9, 7.2 / - / - us.  The lines lie where a batch of 64 such lattices
   // loses nothing to speak of: 1.1 M voxels 32.0 / 22.3 / 75.2, 28.4 / 18.1 / 72.1, 27.7 / 17.4 / 81.7;
   // 26 M 420 / 343 / 656, 431 / 342 / 752, 499 / 370 / 956.
-  if (kPrecision == 64 && g_tile_depth == kTileDepth)
+  if (kPrecision == 64 && c->tune.tile_depth < 0)
     for (RepHost& R : c->reps) R.tz = even_depth(R.n <= 1 << 14 ? 4 : R.n <= 1 << 16 ? 8 : kTileDepth, R.nz);
   if (!c->prm.autotune) return HCA_OK;
   const long long n = c->ntot;
@@ -1255,7 +1270,7 @@ hca_status plan_tiles(Ctx* c) {
   check(hipMemsetAsync(tsb.z32, 0, 4 * n, c->stream));
   check(hipMemsetAsync(tsb.ss, 0, sizeof(SolveScal) * R, c->stream));
   float tbest = 1e30f;
-  int best_depth = g_tile_depth;
+  int best_depth = depth0;
   int best_policy = 0;
   for (int policy = 0; policy < 2 && st == HCA_OK; ++policy)
     for (int depth : {2, 4, 8, 16, 32}) {
@@ -1325,21 +1340,7 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
   }
   if (const char* e = getenv("HCA_XCD_REMAP")) g_xcd_remap = atoi(e) != 0;
   if (const char* e = getenv("HCA_TILE_REMAP")) g_tile_remap = atoi(e) != 0;
-  if (const char* e = getenv("HCA_TILE_DEPTH")) g_tile_depth = std::max(0, atoi(e));
-  if (const char* e = getenv("HCA_SOLVE_LEAD")) g_solve_lead = std::max(-8, std::min(8, atoi(e)));
-  {
-    const char* e = getenv("HCA_FUSE_MIN_CELLS");
-    g_fuse_min_cells = e ? std::max(1LL, atoll(e)) : (2LL << 20);
-  }
-  if (const char* e = getenv("HCA_FUSED_DEPTH")) g_fused_depth = std::max(0, std::min(1024, atoi(e))) / kF3Group * kF3Group;
-  if (const char* e = getenv("HCA_MG_TILE_TARGET")) {
-    const double v = atof(e);
-    if (v >= 1.0) g_mg_tile_target = v;
-  }
-  if (const char* e = getenv("HCA_TILE_TARGET")) {
-    const double v = atof(e);
-    if (v >= 1.0) g_tile_target = v;
-  }
+  c->tune = tuning_from_env();
   c->work.max_blocks = max_blocks;
   {
     hca_status st = plan_tiles(c);
@@ -1382,7 +1383,7 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
       const RepHost& H = c->reps[r];
       lats.insert(lats.end(), c->dp.nf, FusedLat{fused_shape(H.nx, H.ny, H.nz, 3), H.nz, fused_group(H.nx, H.ny, H.nz)});
     }
-    const int fdepth = fused_depth(lats, 3);
+    const int fdepth = fused_depth(c->tune, lats, 3);
     c->sys_n.clear();
     for (int f = 0; f < c->dp.nf; ++f) {
       for (int r = 0; r < R; ++r) {
@@ -1659,7 +1660,7 @@ hca_status build_mg(Ctx* c) {
       if (k < kcr[r])
         lats.push_back(FusedLat{fused_shape(dims[r][k][0], dims[r][k][1], dims[r][k][2], 2), dims[r][k][2], 4});
     }
-    const int fdepth = fused_depth(lats, 2);
+    const int fdepth = fused_depth(c->tune, lats, 2);
     int fthreads = k == 0 ? c->fthreads : 64;
     for (const FusedLat& l : lats) fthreads = std::max(fthreads, 64 * l.f.waves);
     // Every level smooths in fused passes in precision 64.  In precision 32,
@@ -1674,7 +1675,7 @@ hca_status build_mg(Ctx* c) {
         for (int i = 0; i < 3; ++i) fuse_k = fuse_k && k < kcr[r] && dims[r][0][i] % (1 << k) == 0;
         if (fuse_k) cells_k += (long long)dims[r][k][0] * dims[r][k][1] * dims[r][k][2];
       }
-      fuse_k = fuse_k && cells_k * (S / R) >= g_fuse_min_cells;
+      fuse_k = fuse_k && cells_k * (S / R) >= c->tune.fuse_min_cells;
     }
     for (int s = 0; s < S; ++s) {
       const int r = s % R;
@@ -1705,7 +1706,7 @@ hca_status build_mg(Ctx* c) {
           m.tx = pick_tx(m.nx);
           m.off = off;
           off += (long long)m.nx * m.ny * m.nz;
-          const int tz = even_depth(pick_tz(m.nx, m.ny, m.nz, m.tx, g_mg_tile_target), m.nz);
+          const int tz = even_depth(pick_tz(m.nx, m.ny, m.nz, m.tx, c->tune.mg_tile_target), m.nz);
           if (m.active) {
             m.tile_b0 = (int)tiles.size();
             add_tiles(tiles, s, m.nx, m.ny, m.nz, m.tx, tz);
