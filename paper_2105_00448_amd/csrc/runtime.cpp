@@ -157,7 +157,11 @@ struct Tuning {
   int tile_depth = -1;                    // HCA_TILE_DEPTH
   double tile_target = 1024.0;            // HCA_TILE_TARGET
   double mg_tile_target = 512.0;          // HCA_MG_TILE_TARGET: tiles per system the coarser multigrid levels aim at
-  int fused_depth = 0;                    // HCA_FUSED_DEPTH: planes of the fused passes' tiles; 0: by fused_depth
+  // Planes of the fused passes' tiles: fused_depth; or, 0, as many as give fused_target
+  // tiles per lattice, between fused_min and 64; or, those 0 too, by the model.
+  int fused_depth = 0;                    // HCA_FUSED_DEPTH
+  double fused_target = 0.0;              // HCA_FUSED_TARGET (256 where the other is set)
+  int fused_min = 0;                      // HCA_FUSED_MIN (16 where the other is set)
   // Precision 32: coarser levels smooth in fused passes from this many cells over all systems.
   long long fuse_min_cells = 2LL << 20;   // HCA_FUSE_MIN_CELLS
 };
@@ -171,6 +175,9 @@ Tuning tuning_from_env() {
     if (const double v = atof(e); v >= 1.0) t.mg_tile_target = v;
   if (const char* e = getenv("HCA_FUSED_DEPTH"))
     t.fused_depth = std::max(0, std::min(1024, atoi(e))) / kF3Group * kF3Group;
+  if (const char* e = getenv("HCA_FUSED_TARGET"))
+    if (const double v = atof(e); v >= 1.0) t.fused_target = v;
+  if (const char* e = getenv("HCA_FUSED_MIN")) t.fused_min = std::max(2, std::min(64, atoi(e)));
   if (const char* e = getenv("HCA_FUSE_MIN_CELLS")) t.fuse_min_cells = std::max(1LL, atoll(e));
   return t;
 }
@@ -1062,6 +1069,10 @@ int fused_group(int nx, int ny, int nz) { return (long long)nx * ny * nz <= 1LL 
 // 942 / 936 / 1322 / 1310 us (32).  Level 1 at depths 4 / 8 / 16 / 24: three systems of
 // 64^3 cells 21 / 27 / 38 / 49 us (4 taken), 59 x 52 x 46, five systems, 24 / 26 / 37 / 47 (4), the
 // ensemble 114 / 91 / 88 / 100 (8); level 2 of the ensemble 25 / 29 / 42 / 46 (4).
+int aimed_depth(const Tuning& tune, int nz, double nxy) {   // nxy: tiles per plane
+  const double target = tune.fused_target > 0.0 ? tune.fused_target : 256.0;
+  return std::max(tune.fused_min ? tune.fused_min : 16, std::min(64, (int)std::floor(nz * nxy / target)));
+}
 struct FusedLat {
   FusedShape f;
   int nz, least;   // least: of the tiles' depth
@@ -1071,6 +1082,11 @@ int fused_depth(const Tuning& tune, const std::vector<FusedLat>& lats, int S) {
   const double work_us = S == 3 ? 0.22 : 0.25, step_us = S == 3 ? 0.35 : 0.45;
   int least = 4, best = kF3Group;
   for (const FusedLat& l : lats) least = std::max(least, l.least);
+  if (tune.fused_target > 0.0 || tune.fused_min) {
+    int d = least;
+    for (const FusedLat& l : lats) d = std::max(d, aimed_depth(tune, l.nz, (double)l.f.ntx * l.f.nty));
+    return (d + kF3Group - 1) / kF3Group * kF3Group;
+  }
   double best_us = -1.0;
   for (int d : {4, 8, 16, 24, 32, 48, 64}) {
     if (d < least) continue;
@@ -1098,10 +1114,10 @@ int fused_depth(const Tuning& tune, const std::vector<FusedLat>& lats, int S) {
 // Precision 32: the planes of an r.z column sum, which fix the depth of level
 // 0's fused tiles there (a function of the lattice alone, like the order of
 // the sums; k_mg.hip, k_mg_rz32).
-int rz32_depth(const RepHost& H) {
+int rz32_depth(const Tuning& tune, const RepHost& H) {
   const int ty = kRzBlock / H.tx;
   const double nxy = (double)((H.nx + H.tx - 1) / H.tx) * (double)((H.ny + ty - 1) / ty);
-  return even_depth(std::max(16, std::min(64, (int)std::floor(H.nz * nxy / 256.0))), H.nz);
+  return even_depth(aimed_depth(tune, H.nz, nxy), H.nz);
 }
 
 // Tiles in launch order: workgroup b runs on XCD b mod 8.  Each system's tiles
@@ -1402,7 +1418,7 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
             t.part = npart + (t.y0 / fs.fty * fs.ntx + t.x0 / fs.tx) * groups + t.z0 / group;
           }
         } else {
-          const int depth = rz32_depth(H);
+          const int depth = rz32_depth(c->tune, H);
           const long long plane = (long long)H.nx * H.ny;
           const size_t rz0 = rztiles.size();
           add_tiles(ftiles, f * R + r, H.nx, H.ny, H.nz, fs.tx, depth, fs.fty);

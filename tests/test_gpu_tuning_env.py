@@ -34,16 +34,19 @@ def test_tile_depth_holds_while_it_is_set(shape, depth, precision, monkeypatch):
         assert tz() == default
 
 
+def fused_us(rep, **over):
+    """Microseconds of level 0's pre- and post-smoothing."""
+    with hca.Simulation([rep], hca.default_params(profile=1, **over)) as sim:
+        sim.step(1)
+        sim.reset_kernel_times()
+        sim.step(2)
+        kt = sim.kernel_times()
+        return sum(kt[k]["ms"] / kt[k]["launches"] * 1e3 for k in ("k_mg_prefused<L0>", "k_mg_postfused<L0>"))
+
+
 def test_fused_depth_holds_while_it_is_set(monkeypatch):
     rep = replicate((128, 128, 128))
-
-    def us():
-        with hca.Simulation([rep], hca.default_params(profile=1)) as sim:
-            sim.step(1)
-            sim.reset_kernel_times()
-            sim.step(2)
-            kt = sim.kernel_times()
-            return sum(kt[k]["ms"] / kt[k]["launches"] * 1e3 for k in ("k_mg_prefused<L0>", "k_mg_postfused<L0>"))
+    us = lambda: fused_us(rep)
     us()
     before = us()
     monkeypatch.setenv("HCA_FUSED_DEPTH", "1024")
@@ -51,5 +54,22 @@ def test_fused_depth_holds_while_it_is_set(monkeypatch):
     monkeypatch.delenv("HCA_FUSED_DEPTH")
     after = us()
     print(f"\n[fused depth] default {before:.1f} us, one slab {forced:.1f}, default again {after:.1f}", flush=True)
+    assert forced >= 1.5 * before
+    assert after <= 1.25 * before
+
+
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("knob,value", [("HCA_FUSED_MIN", "64"), ("HCA_FUSED_TARGET", "1")])
+def test_fused_tiles_aimed_at(knob, value, precision, monkeypatch):
+    """Both give tiles of 64 planes (16 by default): half the chip and more idle."""
+    rep = replicate((128, 128, 128))
+    fused_us(rep, precision=precision)
+    before = fused_us(rep, precision=precision)
+    monkeypatch.setenv(knob, value)
+    forced = fused_us(rep, precision=precision)
+    monkeypatch.delenv(knob)
+    after = fused_us(rep, precision=precision)
+    print(f"\n[{knob}] precision {precision}: default {before:.1f} us, 64 planes {forced:.1f}, default again {after:.1f}",
+          flush=True)
     assert forced >= 1.5 * before
     assert after <= 1.25 * before
