@@ -116,7 +116,7 @@ struct Tile {
   short x0, y0;
   short z0, z1;
   int part;                   // level 0's fused tiles: the first of the tile's r.z partials (precision 32: the
-                              // column sum of (x, y) = (0, 0) over the tile's planes)
+                              // tile's slab of planes, each a plane of column sums)
 };
 
 // Per-replicate scalars of one conjugate-gradient solve.
@@ -344,6 +344,7 @@ struct MgRep {
   int tx;
   int fe, frpw, fty;        // fused tiles: strips per row (halo strips included), rows per wavefront, output rows
   int fgroup;               // level 0: planes per r.z partial (4 or 8)
+  long long col_off;        // level 0, precision 32: the system's first r.z column sum
   float a;                  // face coupling D/h^2 of the system's field
 };
 

@@ -1308,7 +1308,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_postfused(MgLevel Lk, MgLeve
   f3_march<S>(z0, z1, wact, step);
   if constexpr (ZOUT && P32) {
     if (f.inner) {
-      double* o = colsum + t.part + f.x + (long long)m.nx * f.y;
+      double* o = colsum + m.col_off + t.part * plane + f.x + (long long)m.nx * f.y;
       const double isc = sb.ss[t.rep].isc;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -1338,7 +1338,7 @@ __global__ void __launch_bounds__(kRzBlock) k_mg_rz32(MgLevel L0, const double* 
   if (ss[t.rep].done) return;
   const MgRep m = L0.reps[t.rep];
   const int x = t.x0 + (int)threadIdx.x % m.tx, y = t.y0 + (int)threadIdx.x / m.tx;
-  double rz = x < m.nx && y < m.ny ? colsum[t.part + x + (long long)m.nx * y] : 0.0;
+  double rz = x < m.nx && y < m.ny ? colsum[m.col_off + x + (long long)m.nx * (y + (long long)m.ny * t.part)] : 0.0;
   rz = wave_sum(rz);
   if ((threadIdx.x & 63) == 0) sum[threadIdx.x >> 6] = rz;
   __syncthreads();

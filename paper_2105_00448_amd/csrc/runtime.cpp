@@ -236,6 +236,7 @@ struct Ctx : ::hca_ctx {
   int nfparts = 0;                 // r.z partials of level 0's fused smoothing
   Work sys_all{}, sys1{};
   std::vector<long long> sys_n;
+  std::vector<long long> sys_col;   // precision 32: each system's first r.z column sum
   Counters* d_cnt = nullptr;
   unsigned long long* d_cpart = nullptr;   // per flat item x kCounterSlots
   unsigned long long* d_bad = nullptr;
@@ -1401,6 +1402,7 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
     }
     const int fdepth = fused_depth(c->tune, lats, 3);
     c->sys_n.clear();
+    c->sys_col.clear();
     for (int f = 0; f < c->dp.nf; ++f) {
       for (int r = 0; r < R; ++r) {
         RepDev d = lattice_entry(c->reps[r], (long long)f * c->ntot + c->reps[r].off, f * R + r,
@@ -1421,10 +1423,11 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
           const int depth = rz32_depth(c->tune, H);
           const long long plane = (long long)H.nx * H.ny;
           const size_t rz0 = rztiles.size();
+          c->sys_col.push_back(ncol);
           add_tiles(ftiles, f * R + r, H.nx, H.ny, H.nz, fs.tx, depth, fs.fty);
           add_tiles(rztiles, f * R + r, H.nx, H.ny, H.nz, H.tx, depth, kRzBlock / H.tx);
-          for (size_t k = first; k < ftiles.size(); ++k) ftiles[k].part = (int)(ncol + ftiles[k].z0 / depth * plane);
-          for (size_t k = rz0; k < rztiles.size(); ++k) rztiles[k].part = (int)(ncol + rztiles[k].z0 / depth * plane);
+          for (size_t k = first; k < ftiles.size(); ++k) ftiles[k].part = ftiles[k].z0 / depth;
+          for (size_t k = rz0; k < rztiles.size(); ++k) rztiles[k].part = rztiles[k].z0 / depth;
           ncol += (H.nz + depth - 1) / depth * plane;
           d.fpart_b0 = npart;
           d.fpart_nb = (int)(rztiles.size() - rz0);
@@ -1442,7 +1445,6 @@ hca_status build_tables(Ctx* c, const hca_replicate* in) {
         nrz1 = (int)rztiles.size();
       }
     }
-    if (ncol > 0x7fffffffLL) return fail(c, HCA_E_NOMEM, "too many r.z column sums");
     const std::vector<Tile> dealt = deal_tiles(ftiles);
     const std::vector<Tile> dealt1 = deal_tiles(std::vector<Tile>(ftiles.begin(), ftiles.begin() + nf1));
     hca_status st;
@@ -1716,6 +1718,7 @@ hca_status build_mg(Ctx* c) {
         if (k == 0) {
           m.tx = sd[s].tx;
           m.off = sd[s].off;
+          if (sizeof(Real) == 4) m.col_off = c->sys_col[s];
           m.tile_b0 = sd[s].tile_b0;
           m.tile_nb = sd[s].tile_nb;
         } else {
