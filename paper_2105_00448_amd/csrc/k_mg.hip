@@ -937,6 +937,7 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_prefused(MgLevel Lk, MgLevel
                                                              const float* __restrict__ r, const SolveScal* ss) {
   extern __shared__ __attribute__((aligned(16))) float4 lds_f3[];
   constexpr int kSt = F3Lds<S>::kStride;
+  constexpr bool kDiv = S == 2 && !P32;   // the residual's u / D^-1 rounded as one kernel per sweep rounds it
   float4* const sV = lds_f3;   // [strip][stage][parity]
   const int nstrips = f3_strips((int)blockDim.x);
   float2* const sQ = reinterpret_cast<float2*>(lds_f3 + nstrips * kSt);   // [strip][parity]: residual sums over x
@@ -1046,7 +1047,15 @@ __global__ void __launch_bounds__(kF3Block, 3) k_mg_prefused(MgLevel Lk, MgLevel
             float res[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              const float c = fmaf(-u[i], __builtin_amdgcn_rcpf(dh[kk[s]][i]), rh[kk[s]][i]);
+              const float d = dh[kk[s]][i];
+              const float rcp = __builtin_amdgcn_rcpf(d);
+              float c;
+              if (kDiv) {
+                const float q = u[i] * rcp;
+                c = rh[kk[s]][i] - fmaf(fmaf(-q, d, u[i]), rcp, q);
+              } else {
+                c = fmaf(-u[i], rcp, rh[kk[s]][i]);
+              }
               res[i] = fmaf(geo.a, F3_NB(i, u, lo, hi, ym, yp, h[s - 1][wb], nv), c);
             }
             if (ragged) {
