@@ -326,7 +326,7 @@ void launch_guess_projection(hipStream_t s, const Work& w, const T* c, const T* 
 // ---- geometric multigrid (k_mg.hip) ---------------------------------------
 constexpr int kMaxLevels = 16;
 constexpr int kCoarseThreads = 1024;
-constexpr int kCoarseMaxCellsPerThread = 8;
+constexpr int kCoarseMaxCellsPerThread = 6;   // of level kc, the most that a k_mg_coarse instance takes
 // Floats of a coarse-solve level's cell that level kc is chosen by: two iterates, r, D^-1, gx, gy, gz
 // (all in LDS after level kc; two of level kc's, the others in registers)
 constexpr int kCoarseLdsPerCell = 7;

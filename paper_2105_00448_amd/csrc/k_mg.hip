@@ -1863,8 +1863,9 @@ hipError_t mg_set_fused_lds() {
 
 // The coarse solve for level kc of up to `cells` cells: the fewest cells a
 // thread that take them (the slots of a thread are worked on together, those
-// beyond a system's cells for nothing).  More than 5814 cells do not fit a
-// level's 28 bytes a cell in 160 KiB.  flat: every system has one plane.
+// beyond a system's cells for nothing).  Level kc is chosen with no more than the last
+// one's; today's bound is lower, 5814 cells by a level's 28 bytes a cell in 160 KiB.
+// flat: every system has one plane.
 typedef void (*CoarseKernel)(const MgCoarseRep*, float, float, const float*, const SolveScal*);
 template <bool FLAT>
 static CoarseKernel coarse_kernel_of(int cells) {
@@ -1872,7 +1873,7 @@ static CoarseKernel coarse_kernel_of(int cells) {
   if (cells <= 2 * kCoarseThreads) return k_mg_coarse<2, FLAT>;
   if (cells <= 3 * kCoarseThreads) return k_mg_coarse<3, FLAT>;
   if (cells <= 4 * kCoarseThreads) return k_mg_coarse<4, FLAT>;
-  return k_mg_coarse<6, FLAT>;
+  return k_mg_coarse<kCoarseMaxCellsPerThread, FLAT>;
 }
 static CoarseKernel coarse_kernel(int cells, int flat) {
   return flat ? coarse_kernel_of<true>(cells) : coarse_kernel_of<false>(cells);
