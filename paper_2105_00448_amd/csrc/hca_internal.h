@@ -392,9 +392,7 @@ struct MgBufs {
   float w0[3];              // level 0: pre-sweeps (w0[0], w0[1], w0[2]), post-sweeps reversed
   int fused;                // fused smoothing passes (k_mg_prefused, k_mg_postfused) on every level
   double* colsum;           // precision 32: r.z of each column over a fused tile's planes
-  float** lev_c;            // device arrays of the per-level pointers
-  float** lev_r;
-  float** lev_u;
+  float** lev_c;            // device array of the levels' c
 };
 
 // Allow the fused passes their dynamic LDS (above 64 KiB).

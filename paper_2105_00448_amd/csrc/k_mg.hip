@@ -1843,13 +1843,12 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(const MgCoarseRep*
 hipError_t mg_set_fused_lds() {
   const void* pre3[] = {(const void*)k_mg_prefused<3, true, false>, (const void*)k_mg_prefused<3, true, true>};
   const void* pre2[] = {(const void*)k_mg_prefused<2, true, false>, (const void*)k_mg_prefused<2, false, false>,
-                        (const void*)k_mg_prefused<2, true, true>, (const void*)k_mg_prefused<2, false, true>};
+                        (const void*)k_mg_prefused<2, true, true>};
   const void* post3[] = {(const void*)k_mg_postfused<3, true, true, false, double>,
                          (const void*)k_mg_postfused<3, true, true, true, float>};
   const void* post2[] = {(const void*)k_mg_postfused<2, true, false, false, double>,
                          (const void*)k_mg_postfused<2, false, false, false, double>,
-                         (const void*)k_mg_postfused<2, true, false, true, float>,
-                         (const void*)k_mg_postfused<2, false, false, true, float>};
+                         (const void*)k_mg_postfused<2, true, false, true, float>};
   hipError_t e = hipSuccess;
   auto set = [&](const void* f, int bytes) {
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -1953,8 +1952,11 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
       const MgLevel& C = mg.lev[k + 1];
       if (!L.ntiles) continue;
       if (mg.fused && L.nftiles) {
-        hca_launch(L.uniform ? k_mg_prefused<2, true, kP32> : k_mg_prefused<2, false, kP32>, dim3(L.nftiles),
-                   dim3(L.fthreads), f3_lds_pre<2>(L.fthreads), s, L, C, F3W{{wa, wb, 0.f}}, (float)(1 << k), (const float*)L.r, ss);
+        auto pre = k_mg_prefused<2, true, kP32>;
+        if constexpr (!kP32)   // (precision 32 fuses uniform levels alone)
+          if (!L.uniform) pre = k_mg_prefused<2, false, kP32>;
+        hca_launch(pre, dim3(L.nftiles), dim3(L.fthreads), f3_lds_pre<2>(L.fthreads), s, L, C, F3W{{wa, wb, 0.f}},
+                   (float)(1 << k), (const float*)L.r, ss);
         continue;
       }
       hca_launch((k_mg_pre<false, float>), dim3(grid_tiles(L.ntiles, w.max_blocks)), dim3(kBlock), 0, s, L, wa, wb,
@@ -1975,9 +1977,11 @@ void launch_mg_vcycle(hipStream_t s, const Work& w, const MgBufs& mg, const Solv
       const MgLevel& C = mg.lev[k + 1];
       if (!L.ntiles) continue;
       if (mg.fused && L.nftiles) {
-        hca_launch(L.uniform ? k_mg_postfused<2, true, false, kP32, T> : k_mg_postfused<2, false, false, kP32, T>,
-                   dim3(L.nftiles), dim3(L.fthreads), f3_lds_post<2>(L.fthreads), s, L, C, corr(k + 1), F3W{{wb, wa, 0.f}}, (float)(1 << k),
-                   (const float*)L.r, L.ualt, sb, (double*)nullptr);
+        auto post = k_mg_postfused<2, true, false, kP32, T>;
+        if constexpr (!kP32)
+          if (!L.uniform) post = k_mg_postfused<2, false, false, kP32, T>;
+        hca_launch(post, dim3(L.nftiles), dim3(L.fthreads), f3_lds_post<2>(L.fthreads), s, L, C, corr(k + 1),
+                   F3W{{wb, wa, 0.f}}, (float)(1 << k), (const float*)L.r, L.ualt, sb, (double*)nullptr);
         continue;
       }
       hca_launch((k_mg_post1<false, float>), dim3(grid_tiles(L.ntiles, w.max_blocks)), dim3(kBlock), 0, s, L, C,

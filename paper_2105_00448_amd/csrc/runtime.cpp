@@ -1855,17 +1855,13 @@ hca_status build_mg(Ctx* c) {
   if ((st = mg_alloc(c, &mg.coarse_pre, (size_t)pre_total)) != HCA_OK) return st;
   if (c->ncol && c->prm.mg_fuse && (st = mg_alloc(c, &mg.colsum, (size_t)c->ncol)) != HCA_OK) return st;
   c->mg1.colsum = mg.colsum;
-  if ((st = mg_upload(c, &mg.lev_c, pc)) != HCA_OK || (st = mg_upload(c, &mg.lev_r, pr)) != HCA_OK ||
-      (st = mg_upload(c, &mg.lev_u, pu)) != HCA_OK)
-    return st;
+  if ((st = mg_upload(c, &mg.lev_c, pc)) != HCA_OK) return st;
   c->mg1.coarse = mg.coarse;
   c->mg1.coarse_pre = mg.coarse_pre;
   c->mg1.coarse_lds_bytes = mg.coarse_lds_bytes;
   c->mg1.coarse_cells = mg.coarse_cells;
   c->mg1.coarse_flat = mg.coarse_flat;
   c->mg1.lev_c = mg.lev_c;
-  c->mg1.lev_r = mg.lev_r;
-  c->mg1.lev_u = mg.lev_u;
   return HCA_OK;
 }
 
