@@ -87,7 +87,8 @@ const double kBytesPerVoxel[KC_COUNT] = {
     9.0 + 9 * kE,   // setup_step: read L, w, K, G1, G2; write c, b of three systems
     5 * kE,         // cg_start: read x, c, b; write r, (Jacobi: dinv, z)
     4.0 + 6 * kE,   // cg_apply, multigrid: read z (4), p_old, c, x; write p_new, q, x (the
-                    // previous iteration's x += alpha p; 4 + 4 e where there is none to make)
+                    // previous iteration's x += alpha p; 4 + 4 e where there is none to make, 4 + 3 e
+                    // at a solve's first)
     6 * kE,         // cg_update, Jacobi: read r, q, z, dinv; write r, z
     49.0 + kE,      // ode: read L, K, P, Vc, phi; write P, Vc, phi
     11.0,           // ca_propose: scan (read L, phi; write code, win); the list's decisions
@@ -654,8 +655,8 @@ hca_status solve(Ctx* c, const Work& W_all, const MgBufs& mg_all, unsigned fmask
   int real = 0;
   auto iteration = [&](int it) {
     {
-      // no earlier x += alpha p to make: a solve's first apply, and those after kept z
-      ProfScope ps(c, KC_CG_APPLY, it, true, it <= c->sb.ring.n ? -kBytesApplyX : 0.0);
+      // no earlier x += alpha p to make: a solve's first apply (nor a p_old), and those after kept z
+      ProfScope ps(c, KC_CG_APPLY, it, true, it <= c->sb.ring.n ? -kBytesApplyX - (it == 0 ? kE : 0.0) : 0.0);
       launch_cg_apply(c->stream, *Wp, c->c, c->F, c->sb, it & 1);
     }
     {

@@ -18,6 +18,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -25,7 +26,7 @@ SOURCES = ["paper_2105_00448_amd/csrc/k_solver.hip", "paper_2105_00448_amd/csrc/
            "paper_2105_00448_amd/csrc/dev_util.h", "paper_2105_00448_amd/csrc/hca_internal.h"]
 COPY_KIB = 256 * 1024
 # the counter passes collect only these dispatches (--kernel-include-regex)
-PMC_REGEX = ("k_cg_update|k_cg_apply|k_cg_finish|k_mg_pre|k_mg_sweep|k_mg_restrict|k_mg_post1|k_mg_post2|"
+PMC_REGEX = ("k_cg_start|k_cg_update|k_cg_apply|k_cg_finish|k_mg_pre|k_mg_sweep|k_mg_restrict|k_mg_post1|k_mg_post2|"
              "k_mg_postfused|k_mg_coarse|k_init_cells|copyBuffer")
 # kernels priced per launch (levels below level 0, the one-workgroup coarse solve)
 PER_LAUNCH = ["k_mg_prefused<2, true, false>", "k_mg_postfused<2, true, false, false, double>",
@@ -40,13 +41,13 @@ def kernels(e):
     """Streaming kernels of the solve (demangled-name prefix -> (short name,
     algorithmic bytes per active voxel)); e = bytes of a stored field value.
     Level 0 of the multigrid is the <true, ...> instance, or the fused
-    three-stage passes k_mg_prefused<3, ...> / k_mg_postfused<3, ...> (the default)."""
+    three-stage passes k_mg_prefused<3, ...> / k_mg_postfused<3, ...> (the default).
+    The apply and the solves' end move different bytes from iteration to iteration
+    and are priced by cg_forms instead."""
     fp = "double" if e == 8 else "float"
     p32 = "false" if e == 8 else "true"   # the fused passes' precision flag
     return {
         f"k_cg_update<false, {fp}>": ("k_cg_update", 3 * e),
-        f"k_cg_apply<false, {fp}>": ("k_cg_apply", 4 + (4 if e == 8 else 6) * e),
-        f"k_cg_finish<{fp}>": ("k_cg_finish", 3 * e),
         "k_mg_pre<true, float>": ("k_mg_pre_L0", 12.0),
         "k_mg_sweep<true, float>": ("k_mg_sweep_L0", 16.0),
         "k_mg_restrict<true, float>": ("k_mg_restrict_L0", 12.5),
@@ -55,6 +56,50 @@ def kernels(e):
         f"k_mg_prefused<3, true, {p32}>": ("k_mg_prefused_L0", 12.5),
         f"k_mg_postfused<3, true, true, {p32}, {fp}>": ("k_mg_postfused_L0", 24.5 if e == 8 else 16.5),
     }
+
+
+def kept_z():
+    """Iterations whose z a precision-64 solve keeps (CgRing)."""
+    src = open(os.path.join(ROOT, "paper_2105_00448_amd/csrc/hca_internal.h")).read()
+    return int(re.search(r"constexpr int kZRing = (\d+);", src).group(1))
+
+
+def cg_forms(fetch, write, e, kept):
+    """Counted and algorithmic bytes of the apply's forms and of the solves' ends.
+
+    ``fetch`` and ``write``: (kernel, bytes) of the same dispatches of
+    k_cg_start, k_cg_apply, k_cg_update and k_cg_finish in launch order, one
+    counter each; ``e`` bytes of a stored value, ``kept`` iterations of a solve
+    keep z.  An iteration's update reads the same bytes per active voxel
+    whatever its number, so its FETCH over the largest is the share of voxels
+    still iterating.  Returns {form: [dispatches, share, FETCH, WRITE, algorithmic
+    bytes x share]}, sums over the dispatches, the bytes per voxel of all systems:
+    "first" (p = z), "kept" (x untouched), "x" (x += alpha p made too), "finish"."""
+    price = {"first": 4 + 3 * e, "kept": 4 + 4 * e, "x": 4 + 6 * e}
+    if [k for k, _ in fetch] != [k for k, _ in write]:
+        raise SystemExit("the two counter passes launched different kernels")
+    top = max(v for k, v in fetch if k == "k_cg_update")
+    out, shares, pending = collections.defaultdict(lambda: [0, 0.0, 0.0, 0.0, 0.0]), [], None
+
+    def add(form, share, f, w, bpv):
+        o = out[form]
+        for i, v in enumerate((1, share, f, w, bpv)):
+            o[i] += v
+    for (k, f), (_, w) in zip(fetch, write):
+        if k == "k_cg_start":
+            shares = []
+        elif k == "k_cg_apply":
+            pending = (f, w)
+        elif k == "k_cg_update":
+            share, it = f / top, len(shares)
+            if share >= 0.02:   # (launches that found every system finished: left out)
+                form = "first" if it == 0 else "kept" if it <= kept else "x"
+                add(form, share, *pending, price[form] * share)
+            shares.append(share)
+        elif k == "k_cg_finish":
+            at = shares + [0.0] * (kept + 1)
+            add("finish", at[0], f, w, 2 * e * at[0] + 4 * sum(at[:kept]) + e * at[kept])
+    return out
 
 
 def name(r):
@@ -139,31 +184,52 @@ def main(workload, precision, kt_dir, f_dir, w_dir, command):
         h.update(open(os.path.join(ROOT, f), "rb").read())
     table = ["| kernel | dispatches (all systems iterating) | FETCH B/voxel | WRITE B/voxel | "
              "measured B/voxel | algorithmic B/voxel | ratio |", "|---|---:|---:|---:|---:|---:|---:|"]
-    ktimes = {}
-    for full, (short, bpv) in ks.items():
-        fd = [(int(r["Dispatch_Id"]), float(r["Counter_Value"])) for r in F if name(r) == full]
-        wd = {int(r["Dispatch_Id"]): float(r["Counter_Value"]) for r in W if name(r) == full}
-        if not fd:
-            continue
-        top = max(v for _, v in fd)
-        full_disp = [(d, v) for d, v in fd if v >= 0.9 * top]   # every system still iterating
-        # the all-systems dispatches of the FETCH pass; WRITE of the same dispatch order
-        fetch = sum(v for _, v in full_disp) / len(full_disp) * 1024 * ffac
-        wvals = sorted(wd.values(), reverse=True)[:len(full_disp)]
-        write = sum(wvals) / len(wvals) * 1024 * wfac
-        vox = 3 * nvox * nrep
-        mb = (fetch + write) / vox
-        durs = [x for x in dur.get(full, [])]
-        ktimes[short] = durs
+    vox = 3 * nvox * nrep
+
+    def record(short, dispatches, fetch, write, bpv):
+        """fetch, write: bytes per voxel."""
         rec = {"kernel": short, "workload": workload, "precision": int(precision), "sources": SOURCES,
                "sources_sha256": h.hexdigest(), "fetch_factor": ffac, "write_factor": wfac,
-               "voxels_all_systems": vox, "dispatches_all_systems": len(full_disp),
-               "fetch_bytes_per_voxel": fetch / vox, "write_bytes_per_voxel": write / vox,
-               "traffic_bytes_per_voxel": mb, "algorithmic_bytes_per_voxel": bpv,
+               "voxels_all_systems": vox, "dispatches": dispatches,
+               "fetch_bytes_per_voxel": fetch, "write_bytes_per_voxel": write,
+               "traffic_bytes_per_voxel": fetch + write, "algorithmic_bytes_per_voxel": bpv,
                "commands": [pmc_command(command, "FETCH_SIZE"), pmc_command(command, "WRITE_SIZE")]}
         json.dump(rec, open(os.path.join(ROOT, "profiles", f"{short}_{tag}_traffic.json"), "w"), indent=1)
-        table.append(f"| {full} | {len(full_disp)} | {fetch / vox:.2f} | {write / vox:.2f} | {mb:.2f} | "
-                     f"{bpv:.1f} | {mb / bpv:.3f} |")
+
+    def row(label, dispatches, fetch, write, bpv):
+        return (f"| {label} | {dispatches} | {fetch:.2f} | {write:.2f} | {fetch + write:.2f} | "
+                f"{bpv:.1f} | {(fetch + write) / bpv:.3f} |")
+    for full, (short, bpv) in ks.items():
+        fd = [float(r["Counter_Value"]) for r in F if name(r) == full]
+        wd = [float(r["Counter_Value"]) for r in W if name(r) == full]
+        if not fd:
+            continue
+        fall = [v for v in fd if v >= 0.9 * max(fd)]   # every system still iterating
+        wall = sorted(wd, reverse=True)[:len(fall)]
+        fetch = sum(fall) / len(fall) * 1024 * ffac / vox
+        write = sum(wall) / len(wall) * 1024 * wfac / vox
+        record(short, len(fall), fetch, write, bpv)
+        table.append(row(full, len(fall), fetch, write, bpv))
+    # the apply's forms and the solves' ends, per active voxel of every dispatch
+    fp = "double" if e == 8 else "float"
+    cg = {f"k_cg_start<{fp}>": "k_cg_start", f"k_cg_apply<false, {fp}>": "k_cg_apply",
+          f"k_cg_update<false, {fp}>": "k_cg_update", f"k_cg_finish<{fp}>": "k_cg_finish"}
+    forms = cg_forms(*[[(cg[name(r)], float(r["Counter_Value"]) * 1024 * fac) for r in rows if name(r) in cg]
+                       for rows, fac in ((F, ffac), (W, wfac))], e, kept_z() if e == 8 else 0)
+    ftable = [table[0].replace("dispatches (all systems iterating)", "dispatches").replace("voxel", "active voxel"),
+              table[1]]
+
+    def per_voxel(o):
+        return o[0], o[2] / (o[1] * vox), o[3] / (o[1] * vox), o[4] / o[1]
+    for form in ("first", "kept", "x"):
+        if form in forms:
+            ftable.append(row(f"k_cg_apply, {form}", *per_voxel(forms[form])))
+    apply_all = [sum(v) for v in zip(*(forms[k] for k in ("first", "kept", "x") if k in forms))]
+    ftable.append(row("k_cg_apply, all", *per_voxel(apply_all)))
+    record("k_cg_apply", *per_voxel(apply_all))
+    if "finish" in forms:
+        ftable.append(row("k_cg_finish", *per_voxel(forms["finish"])))
+        record("k_cg_finish", *per_voxel(forms["finish"]))
     small = ["| kernel | dispatches | mean us | FETCH KiB/dispatch | WRITE KiB/dispatch | GB/s |",
              "|---|---:|---:|---:|---:|---:|"]
     for full in PER_LAUNCH:
@@ -186,6 +252,10 @@ def main(workload, precision, kt_dir, f_dir, w_dir, command):
           f"Per voxel of all {3 * nrep} systems ({3 * nvox * nrep} voxels), on the dispatches where every",
           "system still iterates (counter within 10 % of the kernel's largest; later",
           "dispatches skip finished systems):", ""] + table + [
+          "", "The CG's apply by its forms (a solve's first: p = z; x untouched, z kept; x += alpha p",
+          "made too) and the solves' ends, per active voxel of every dispatch that had one (the",
+          "share of voxels still iterating from the update of the same iteration; the end's",
+          "algorithmic bytes from the solve's own iterations):", ""] + ftable + [
           "", "Kernels below level 0 (latency-bound: bytes per dispatch over all systems, mean",
           "duration from the kernel trace, effective rate):", ""] + small + [
           "", "`profiles/<kernel>_" + tag + "_traffic.json` hold these numbers with the SHA-256 of the",
