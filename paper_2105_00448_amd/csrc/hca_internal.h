@@ -38,7 +38,7 @@ inline void hca_launch(F kernel, dim3 grid, dim3 block, unsigned shmem, hipStrea
   }
 }
 
-constexpr int kBlock = 256;        // threads per workgroup (all kernels but the two below)
+constexpr int kBlock = 256;        // threads per workgroup of the work-item and tile kernels
 constexpr int kF3Block = 768;      // most threads of the multigrid's fused smoothing passes
 constexpr int kRzBlock = 512;      // precision 32: columns of an r.z partial
 constexpr int kF3Group = 8;        // most planes per r.z partial of level 0's post-smoothing

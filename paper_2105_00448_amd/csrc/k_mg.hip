@@ -691,9 +691,10 @@ __global__ void __launch_bounds__(kBlock) k_mg_post2(MgLevel Lk, float omega, co
 // Layout.  A thread owns a strip of four cells in x, so that a stage's
 // neighbours in x are its own registers and, at the strip's ends, the adjacent
 // lanes' (one DPP move each); only the two neighbour rows go through LDS, as
-// 16-byte reads.  A wavefront holds frpw rows of fe strips, a workgroup of
-// eight wavefronts 8 frpw rows: the tile's columns extended by one strip on
-// either side in x and by S rows in y.  Stage s is valid on the rings up to
+// 16-byte reads.  A wavefront holds frpw rows of fe strips, a workgroup the rows of
+// its wavefronts (up to kF3Block / 64; as many as the level's largest tile needs,
+// MgLevel::fthreads): the tile's columns extended by one strip on either side in
+// x and by S rows in y.  Stage s is valid on the rings up to
 // S - s; the lanes beyond compute values that no valid cell reads, so no stage
 // is masked.  D^-1, r and u are 0 outside the lattice, which keeps every
 // stage's value there 0 and makes the neighbour sum the sum over the existing

@@ -628,7 +628,7 @@ double finish_bytes(const Ctx* c, int nsys, double& vox) {
 // system converged, the last iteration's x += alpha p is left to the ODE
 // kernel (c->fin_pending), which reads every voxel of the fields anyway; not
 // in precision 64: the kept z cost the ODE kernel's wavefronts more than a pass of
-// their own (128^3: 216 us against 151 + 51, the 64-replicate ensemble 1600
+// their own (with four kept, 128^3: 216 us against 151 + 51, the 64-replicate ensemble 1600
 // against 899 + 574, the network at 384^3 4740 against 3314 + 1313).
 // prep_o2_only: the other fields' multigrid data are current (c->fixed_ops);
 // only the oxygen systems' are rebuilt from this step's c.
@@ -1070,7 +1070,8 @@ int fused_group(int nx, int ny, int nz) { return (long long)nx * ny * nz <= 1LL 
 // 158 / 153 / 168 / 143 / 186 / 222 us (16), the 64-replicate ensemble 1171 / 982 /
 // 942 / 936 / 1322 / 1310 us (32).  Level 1 at depths 4 / 8 / 16 / 24: three systems of
 // 64^3 cells 21 / 27 / 38 / 49 us (4 taken), 59 x 52 x 46, five systems, 24 / 26 / 37 / 47 (4), the
-// ensemble 114 / 91 / 88 / 100 (8); level 2 of the ensemble 25 / 29 / 42 / 46 (4).
+// ensemble 114 / 91 / 88 / 100 (8); level 2 of the ensemble 25 / 29 / 42 / 46 (4).  The model
+// misses the best of two of these, by 7 % (181 x 150 x 133) and 3 % (the ensemble's level 1).
 int aimed_depth(const Tuning& tune, int nz, double nxy) {   // nxy: tiles per plane
   const double target = tune.fused_target > 0.0 ? tune.fused_target : 256.0;
   return std::max(tune.fused_min ? tune.fused_min : 16, std::min(64, (int)std::floor(nz * nxy / target)));
