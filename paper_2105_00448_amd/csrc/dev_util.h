@@ -135,8 +135,7 @@ __device__ inline void store_partials(double* slot, double a, double b, double c
 // The end of system sys's solve on the voxels [off, off + len): x += G_j z_j of
 // the kept iterations (CgRing) and the last iteration's x += alpha p if its z is
 // not among them.  Thread t takes the voxels t + k kBlock, kPer at a time, loads
-// before stores (four at a time measured 58 us at 128^3 with four z kept, two 51; with
-// three kept two take 45).
+// before stores (with kept z, four at a time measured 58 us at 128^3, two 51).
 template <typename T>
 __device__ inline void cg_finish_span(const CgRing& ring, const T* p0, const T* p1, const SolveScal* ss, int sys,
                                       T* x, long long off, int len) {

@@ -249,17 +249,18 @@ void launch_convert(hipStream_t s, const double* src, float* dst, long long n);
 // from 4 bytes per iteration and voxel, where x += alpha p took 16 in every
 // apply.  Iterations beyond the first n keep that form, and their z the one
 // buffer sb.z32.  The z of iterations 0 and 1 lie in the memory of b, which
-// nothing reads once the start residual is formed; iteration 2's in memory of its
-// own, which the fused smoothing passes leave over (one kernel per sweep takes
-// it for a second iterate of level 0, and two are kept).  n follows from the
-// parameters alone: it fixes the order of x's sums, and so its bits.
-constexpr int kZRing = 3;
+// nothing reads once the start residual is formed; those of iterations 2 and 3 in
+// memory of their own, which the fused smoothing passes leave over (their level 0
+// needs no second iterate, and its first lies in q; one kernel per sweep needs
+// both, and two z are kept).  n follows from the parameters alone: it fixes the
+// order of x's sums, and so its bits.
+constexpr int kZRing = 4;
 struct CgRing {
   int n;                 // iterations whose z is kept: at most kZRing
-  float *z01, *z2;       // z of iterations 0 and 1, `stride` apart, and of iteration 2
+  float *z01, *z23;      // z of iterations 0 and 1, and of 2 and 3, `stride` apart
   long long stride;
   double* hist;          // per system and kept iteration: alpha, beta, 1 / (the scale of z)
-  __host__ __device__ inline float* z(int it) const { return it < 2 ? z01 + it * stride : z2; }
+  __host__ __device__ inline float* z(int it) const { return (it < 2 ? z01 : z23) + (it & 1) * stride; }
 };
 
 // solver (k_solver.hip)

@@ -319,7 +319,7 @@ constexpr bool kSumQz = !JAC && sizeof(T) == 8;
 // and the previous iteration's x += alpha p_old where its z is not kept.
 // Bound by HBM: read z, p_old, c, write p_new, q, 36 B a voxel in precision 64
 // with z kept, 28 at a solve's first and 52 with x read and written (the mean of a
-// solve's calls, three systems of 128^3: 45.3 us, 52.7 with no z kept; of 384^3 1065
+// solve's calls, three systems of 128^3: 42.5 us, 52.7 with no z kept; of 384^3 1006
 // and 1228).
 // Precision 64 with the multigrid also sums q.z, which saves the update a read of
 // z: r_new.z_old = r.z - alpha q.z.

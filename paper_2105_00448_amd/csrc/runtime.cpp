@@ -628,7 +628,7 @@ double finish_bytes(const Ctx* c, int nsys, double& vox) {
 // system converged, the last iteration's x += alpha p is left to the ODE
 // kernel (c->fin_pending), which reads every voxel of the fields anyway; not
 // in precision 64: the kept z cost the ODE kernel's wavefronts more than a pass of
-// their own (with four kept, 128^3: 216 us against 151 + 51, the 64-replicate ensemble 1600
+// their own (128^3: 216 us against 151 + 51, the 64-replicate ensemble 1600
 // against 899 + 574, the network at 384^3 4740 against 3314 + 1313).
 // prep_o2_only: the other fields' multigrid data are current (c->fixed_ops);
 // only the oxygen systems' are rebuilt from this step's c.
@@ -1540,7 +1540,7 @@ hca_status alloc_all(Ctx* c) {
     HIPCHK(c, dalloc(&c->d_galpha, 4 * (size_t)nsys));
   }
   // Precision 64 keeps the z of a solve's first iterations (CgRing): two in b
-  // and, with the fused smoothing passes, one in memory of its own
+  // and, with the fused smoothing passes, two in memory of their own
   // (HCA_CG_KEEP: at most so many).
   if (c->use_mg && kPrecision == 64) {
     CgRing& g = c->sb.ring;
@@ -1550,7 +1550,7 @@ hca_status alloc_all(Ctx* c) {
     g.z01 = (float*)c->b;
     HIPCHK(c, dalloc(&g.hist, (size_t)nsys * 3 * kZRing));
     if (g.n > 2) {
-      hipError_t e = dalloc(&g.z2, n3);
+      hipError_t e = dalloc(&g.z23, (size_t)(g.n - 2) * zstride);
       if (e == hipErrorOutOfMemory) return fail(c, HCA_E_NOMEM, "device memory exhausted");
       HIPCHK(c, e);
     }
@@ -1765,8 +1765,14 @@ hca_status build_mg(Ctx* c) {
       L.ftiles = c->d_ftiles;
       L.nftiles = c->nftiles_all;
       const size_t n = (size_t)c->dp.nf * c->ntot;
-      if ((st = mg_alloc_level(c, &L.dinv, n)) != HCA_OK || (st = mg_alloc_level(c, &L.u, n)) != HCA_OK ||
-          (!c->prm.mg_fuse && (st = mg_alloc_level(c, &L.ualt, n)) != HCA_OK))
+      if ((st = mg_alloc_level(c, &L.dinv, n)) != HCA_OK) return st;
+      // u lives from the pre- to the post-smoothing, q from the apply to the
+      // update: precision 64's fused passes take q's memory for it (written before
+      // it is read, and what a strip load reads past a row is discarded)
+      if (c->prm.mg_fuse && kPrecision == 64)
+        L.u = reinterpret_cast<float*>(c->sb.q);
+      else if ((st = mg_alloc_level(c, &L.u, n)) != HCA_OK ||
+               (!c->prm.mg_fuse && (st = mg_alloc_level(c, &L.ualt, n)) != HCA_OK))
         return st;
     } else {
       Tile* dt = nullptr;
@@ -1897,7 +1903,7 @@ hca_status steady_oxygen(Ctx* c) {
 
 void free_all(Ctx* c) {
   void* bufs[] = {c->L, c->code, c->win, (void*)c->ca_list.cells, (void*)c->ca_list.item_n, c->w, c->P, c->Vc, c->phi, c->F, c->c, c->b,
-                  c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.ring.z2, (void*)c->sb.ring.hist, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
+                  c->sb.r, c->sb.z, (void*)c->sb.z32, (void*)c->sb.ring.z23, (void*)c->sb.ring.hist, (void*)c->sb.r32, c->sb.p0, c->sb.p1, c->sb.q, c->sb.dinv, c->sb.partial,
                   c->sb.ss, c->dose_t, c->dose_a, c->g0, c->b_o2lin, c->Fprev, c->Fprev2, c->d_gpart, c->d_galpha, (void*)c->d_fin, c->d_step,
                   c->d_reps, c->d_flat, c->d_tiles, c->d_sys, c->d_sflat, c->d_stiles, c->d_ftiles, c->d_ftiles1, c->d_rztiles, c->d_cnt, (void*)c->d_cpart,
                   c->d_bad, c->d_theta, (void*)c->d_pack, (void*)c->d_gelu, c->before,
